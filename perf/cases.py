@@ -308,28 +308,30 @@ def prepare(case, seed):
 
 
 def run(s):
+    """One pass; results of FP32 contexts are kept in FP32."""
     case, ctx = s["case"], s["ctx"]
+    real = torch.float64 if case["fp64"] else torch.float32
     if case["kind"] in ("plane", "restart"):
         ctx.rewind()
         ctx.set_initial(s["q0"])
         ctx.advance_to(s["t"])
-        return ctx.read_dofs()
+        return torch.from_numpy(ctx.read_dofs()).to(real)
     if case["kind"] in ("shot", "batch"):
         ctx.rewind()
         ctx.advance_to(s["t"])
-        return [ctx.read_receivers_device("cuda", run=r) for r in range(case["runs"])]
+        return torch.stack([ctx.read_receivers_device("cuda", run=r) for r in range(case["runs"])]).to(real)
     if case["kind"] == "autograd":
         model = [a.clone().requires_grad_() for a in s["model"]]
         seis = s["sim"].seismograms(*model)
         misfit = 0.5 * s["sample"] * ((seis - s["observed"]) ** 2).sum()
         misfit.backward()
-        return dict(seis=seis.detach(), rho=model[0].grad, vp=model[1].grad, vs=model[2].grad)
+        return dict(seis=seis.detach().to(real), **{k: a.grad.to(real) for k, a in zip(("rho", "vp", "vs"), model)})
     ctx.rewind()
     ctx.set_checkpointing(case["every"])
     ctx.advance_to(s["t"])
     seis = ctx.read_receivers_device("cuda")
     g = ctx.adjoint_device((seis - s["observed"]) * s["sample"])
-    return dict(seis=seis, rho=g["g_rho"], vp=g["g_vp"], vs=g["g_vs"])
+    return dict(seis=seis.to(real), **{k: g["g_" + k].to(real) for k in ("rho", "vp", "vs")})
 
 
 def work(case):
@@ -775,7 +777,7 @@ def exact(case, seed):
             return s.to_caller()
         rec = _receivers(case, seed)
         if not grad:
-            return [s.solve(None, _sources(case, seed, r), rec) for r in range(case["runs"])]
+            return torch.stack([s.solve(None, _sources(case, seed, r), rec) for r in range(case["runs"])])
         seis = s.solve(None, _sources(case, seed, 0), rec)
         observed = torch.as_tensor(_observed(case, seed, len(rec), s.ns), device=s.dev)
         (0.5 * s.sample * ((seis - observed) ** 2).sum()).backward()
