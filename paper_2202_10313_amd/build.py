@@ -44,7 +44,7 @@ def build(verbose: bool = False) -> str:
     _run([gen, os.path.join(CSRC, "generated", "refmats.h")] + ORDERS)
     units = [("kernels.hip", "kernels.o"), ("adjoint.hip", "adjoint.o"), ("host.cpp", "host.o"),
              ("basis.cpp", "basis.o"), ("noalloc.hip", "noalloc.o"),
-             ("materials.hip", "materials.o"), ("debug.hip", "debug.o")]
+             ("materials.hip", "materials.o"), ("layout.hip", "layout.o"), ("debug.hip", "debug.o")]
 
     def compile_unit(u):
         src, obj = u
@@ -79,7 +79,7 @@ def sanitizer_runtime() -> str:
 
 def build_sanitized_host() -> dict:
     import hashlib
-    hip_names = ("kernels.o", "adjoint.o", "debug.o", "materials.o", "noalloc.o")
+    hip_names = ("kernels.o", "adjoint.o", "debug.o", "materials.o", "layout.o", "noalloc.o")
     if not (os.path.exists(LIB) and all(os.path.exists(os.path.join(BUILD, o)) for o in hip_names)):
         build()
     san = os.path.join(BUILD, "san")

@@ -123,6 +123,8 @@ struct edg_ctx {
   bool mat_host_valid = true;
   DevBuf dmat, dflag;
   DevBuf d_i2u, d_nbr;               // internal_to_user [Kp], nbr [K][4] (int64, for device-side tables)
+  DevBuf d_u2i, d_code, d_mats;      // tables of the DOF conversion kernels (see ensure_dof_tables)
+  DevBuf dofstage;                   // staging of host DOFs (at most 64 MiB)
   int64_t hist_L0 = 0, hist_J = 0;
   int hist_run = 0;                  // the run whose level states ahist holds
   // adjoint buffers
@@ -402,47 +404,78 @@ void pack_tables(edg_ctx* c, std::vector<R>& P, std::vector<int>& FI) {
 // element e); memory variables [G][JB][m][6][63] with mode b = r + 9 jb at
 // slot 9e+r (the lane that owns mode b), JB = ceil(B/9)
 inline int jb_count(const edg_ctx* c) { return (c->B + LPE - 1) / LPE; }
-inline size_t qe_index(const edg_ctx* c, int64_t ki, int q, int b) {
-  return ((size_t)(ki / EPW) * c->B + b) * (EPW * LPE) + (ki % EPW) * LPE + q;
-}
-inline size_t qa_index(const edg_ctx* c, int64_t ki, int l, int comp, int b) {
-  const int jb = b / LPE, r = b % LPE;
-  return ((((size_t)(ki / EPW) * jb_count(c) + jb) * c->M + l) * 6 + comp) * (EPW * LPE) + (ki % EPW) * LPE + r;
-}
 inline size_t qa_size(const edg_ctx* c) {
   return c->M > 0 ? (size_t)c->G * jb_count(c) * c->M * 6 * EPW * LPE : 1;
 }
 
-// caller-order DOFs [K][NQ][B] -> the tiled layout at dqe / dqa (device);
-// the vertex-sorting basis changes are orthogonal, so adjoints convert the
-// same way
-template <class R>
-int set_dofs_to(edg_ctx* c, void* dqe, void* dqa, const double* dofs) {
-  const int B = c->B, NQ = c->NQ;
-  std::vector<R> he((size_t)c->G * B * EPW * LPE, R(0));
-  std::vector<R> ha(qa_size(c), R(0));
-  std::vector<double> row(B);
-  for (int64_t k = 0; k < c->K; ++k) {
-    const int64_t ki = c->user_to_internal[k];
-    const auto& C = perm_matrix(c, c->perm[k]);
-    for (int q = 0; q < NQ; ++q) {
-      const double* src = dofs + ((size_t)k * NQ + q) * B;
-      bool zero = true;
-      for (int bb = 0; bb < B && zero; ++bb) zero = src[bb] == 0.0;
-      if (zero) continue;   // the staging buffer is already zero
-      for (int b = 0; b < B; ++b) {
-        double s = 0.0;
-        for (int bb = 0; bb < B; ++bb) s += C[b * B + bb] * src[bb];
-        row[b] = s;
-      }
-      for (int b = 0; b < B; ++b) {
-        if (q < 9) he[qe_index(c, ki, q, b)] = R(row[b]);
-        else ha[qa_index(c, ki, (q - 9) / 6, (q - 9) % 6, b)] = R(row[b]);
-      }
+// the device tables of the DOF conversion kernels (layout.hip), uploaded on
+// first use after edg_upload_clusters
+int ensure_dof_tables(edg_ctx* c, DofTables* t) {
+  const size_t bb = (size_t)c->B * c->B;
+  if (!c->d_u2i.p || !c->d_mats.p) {
+    std::vector<unsigned char> code(c->K);
+    std::vector<double> mats(24 * 2 * bb, 0.0);
+    bool have[24] = {false};
+    for (int64_t k = 0; k < c->K; ++k) {
+      const int pc = perm_code(c->perm[k]);
+      code[k] = (unsigned char)pc;
+      if (have[pc]) continue;
+      have[pc] = true;
+      const auto& C = perm_matrix(c, c->perm[k]);
+      double* m = &mats[pc * 2 * bb];
+      for (int i = 0; i < c->B; ++i)
+        for (int j = 0; j < c->B; ++j) m[i * c->B + j] = m[bb + j * c->B + i] = C[i * c->B + j];
+    }
+    int rc;
+    if ((rc = dev_upload(c, c->d_code, code.data(), code.size())) ||
+        (rc = dev_upload(c, c->d_mats, mats.data(), mats.size() * sizeof(double))) ||
+        (rc = dev_upload(c, c->d_u2i, c->user_to_internal.data(), c->K * sizeof(int64_t)))) {
+      dev_free(c->d_u2i);
+      return rc;
     }
   }
-  HIPCHK(c, hipMemcpy(dqe, he.data(), he.size() * sizeof(R), hipMemcpyHostToDevice));
-  if (c->M > 0) HIPCHK(c, hipMemcpy(dqa, ha.data(), ha.size() * sizeof(R), hipMemcpyHostToDevice));
+  *t = DofTables{(const long long*)c->d_u2i.p, (const unsigned char*)c->d_code.p, (const double*)c->d_mats.p, c->B,
+                 c->M};
+  return 0;
+}
+
+// Elements per step of a conversion of host DOFs: a staging buffer of at most
+// 64 MiB (a host copy of that size runs at the link's rate, and the context
+// keeps the buffer), less where the device has no room for it.
+int reserve_dof_stage(edg_ctx* c, int64_t* n) {
+  const size_t per = (size_t)c->NQ * c->B * sizeof(double);
+  int64_t want = std::min<int64_t>(c->K, std::max<int64_t>(1, (int64_t)((64u << 20) / per)));
+  const std::string err = c->err;
+  int rc;
+  while ((rc = dev_reserve(c, c->dofstage, want * per)) && want > 1) want = (want + 7) / 8;
+  if (rc) return rc;
+  c->err = err;   // (the message of the last failed call)
+  *n = want;
+  return 0;
+}
+
+// caller-order DOFs [K][NQ][B] (host, or device memory with dev) -> the tiled
+// layout at dqe / dqa (device); the vertex-sorting basis changes are
+// orthogonal, so adjoints convert the same way.  Padding slots keep their
+// zeros.
+template <class R>
+int set_dofs_to(edg_ctx* c, void* dqe, void* dqa, const double* dofs, bool dev = false) {
+  DofTables t;
+  int64_t step = c->K;
+  int rc = ensure_dof_tables(c, &t);
+  if (rc || (!dev && (rc = reserve_dof_stage(c, &step)))) return rc;
+  const size_t per = (size_t)c->NQ * c->B;
+  for (int64_t k = 0; k < c->K; k += step) {
+    const int64_t n = std::min(step, c->K - k);
+    const double* src = dofs + k * per;
+    if (!dev) {
+      HIPCHK(c, hipMemcpyAsync(c->dofstage.p, src, n * per * sizeof(double), hipMemcpyHostToDevice, c->stream));
+      src = (const double*)c->dofstage.p;
+    }
+    if ((rc = launch_set_dofs<R>(t, k, n, src, (R*)dqe, (R*)dqa, c->stream)))
+      return fail(c, EDG_EHIP, std::string("DOF conversion kernel: ") + hipGetErrorString((hipError_t)rc));
+  }
+  HIPCHK(c, hipStreamSynchronize(c->stream));
   return 0;
 }
 
@@ -452,34 +485,20 @@ int set_dofs_t(edg_ctx* c, int run, const double* dofs) {
 }
 
 template <class R>
-int get_dofs_from(edg_ctx* c, const void* dqe, const void* dqa, double* out) {
-  const int B = c->B, NQ = c->NQ;
-  std::vector<R> he((size_t)c->G * B * EPW * LPE);
-  std::vector<R> ha(qa_size(c));
-  HIPCHK(c, hipMemcpy(he.data(), dqe, he.size() * sizeof(R), hipMemcpyDeviceToHost));
-  if (c->M > 0) HIPCHK(c, hipMemcpy(ha.data(), dqa, ha.size() * sizeof(R), hipMemcpyDeviceToHost));
-  std::vector<double> row(B);
-  for (int64_t k = 0; k < c->K; ++k) {
-    const int64_t ki = c->user_to_internal[k];
-    const auto& C = perm_matrix(c, c->perm[k]);
-    for (int q = 0; q < NQ; ++q) {
-      bool zero = true;
-      for (int b = 0; b < B; ++b) {
-        row[b] = q < 9 ? (double)he[qe_index(c, ki, q, b)] : (double)ha[qa_index(c, ki, (q - 9) / 6, (q - 9) % 6, b)];
-        zero = zero && row[b] == 0.0;
-      }
-      double* dst = out + ((size_t)k * NQ + q) * B;
-      if (zero) {
-        for (int bb = 0; bb < B; ++bb) dst[bb] = 0.0;
-        continue;
-      }
-      for (int bb = 0; bb < B; ++bb) {
-        double s = 0.0;
-        for (int b = 0; b < B; ++b) s += C[b * B + bb] * row[b];
-        dst[bb] = s;
-      }
-    }
+int get_dofs_from(edg_ctx* c, const void* dqe, const void* dqa, double* out, bool dev = false) {
+  DofTables t;
+  int64_t step = c->K;
+  int rc = ensure_dof_tables(c, &t);
+  if (rc || (!dev && (rc = reserve_dof_stage(c, &step)))) return rc;
+  const size_t per = (size_t)c->NQ * c->B;
+  for (int64_t k = 0; k < c->K; k += step) {
+    const int64_t n = std::min(step, c->K - k);
+    double* dst = dev ? out + k * per : (double*)c->dofstage.p;
+    if ((rc = launch_get_dofs<R>(t, k, n, dst, (const R*)dqe, (const R*)dqa, c->stream)))
+      return fail(c, EDG_EHIP, std::string("DOF conversion kernel: ") + hipGetErrorString((hipError_t)rc));
+    if (!dev) HIPCHK(c, hipMemcpyAsync(out + k * per, dst, n * per * sizeof(double), hipMemcpyDeviceToHost, c->stream));
   }
+  HIPCHK(c, hipStreamSynchronize(c->stream));
   return 0;
 }
 
@@ -845,7 +864,7 @@ int launch_timed(edg_ctx* c, const Fns& fn, const KPtrs& p, const LevelArgs& a, 
 edg_ctx::~edg_ctx() {
   for (DevBuf* b : {&Qe, &Qa, &P, &FI, &T1, &T2, &T3, &RecD, &s_run, &s_elem, &s_kind, &s_par, &s_mom, &s_phi,
                     &s_idet, &r_elem, &r_slot, &r_phi, &r_out, &dclock, &aLe, &aLa, &aS0, &aS1, &aS2, &aS3, &aDe, &aDa,
-                    &agacc, &arecDb, &aseis, &ahist, &afinal, &amat, &agrad, &dmat, &dflag, &d_i2u, &d_nbr, &dbg})
+                    &agacc, &arecDb, &aseis, &ahist, &afinal, &amat, &agrad, &dmat, &dflag, &d_i2u, &d_nbr, &dbg, &d_u2i, &d_code, &d_mats, &dofstage})
     dev_free(*b);
   for (auto& ck : ckpts) dev_free(ck.second);
   for (auto& b : ckpt_pool) dev_free(b);
@@ -1154,6 +1173,7 @@ int edg_upload_clusters(edg_ctx* c, const int32_t* cluster) {
   }
   // device state: tables shared by the runs, then every run's state
   const size_t rs = c->cfg.fp64 ? sizeof(double) : sizeof(float);
+  dev_free(c->d_u2i);   // (the tables of the DOF conversion are rebuilt on their next use)
   if ((rc = dev_upload(c, c->d_i2u, c->internal_to_user.data(), c->Kp * sizeof(int64_t))) ||
       (rc = dev_upload(c, c->d_nbr, c->nbr.data(), c->nbr.size() * sizeof(int64_t))))
     return rc;
@@ -1951,14 +1971,7 @@ int adjoint_sweep(edg_ctx* c, const double* dj_seis, const double* dj_q, double*
     for (DevBuf* b : {&c->aLe, &c->aLa, &c->aseis}) HIPCHK(c, hipMemsetAsync(b->p, 0, b->bytes, c->stream));
     HIPCHK(c, hipStreamSynchronize(c->stream));
     if (dj_q) {
-      const double* q = dj_q + run * nqb;
-      if (dev) {   // the DOF layout conversion runs on the host: stage through host memory
-        std::vector<double> h(nqb);
-        HIPCHK(c, hipMemcpy(h.data(), q, nqb * sizeof(double), hipMemcpyDeviceToHost));
-        if ((rc = set_dofs_to<R>(c, c->aLe.p, c->aLa.p, h.data()))) return rc;
-      } else if ((rc = set_dofs_to<R>(c, c->aLe.p, c->aLa.p, q))) {
-        return rc;
-      }
+      if ((rc = set_dofs_to<R>(c, c->aLe.p, c->aLa.p, dj_q + run * nqb, dev))) return rc;
     }
     if (dj_seis && c->n_rec > 0) {
       const double* sb = dj_seis + run * nsb;
@@ -2017,16 +2030,7 @@ int adjoint_sweep(edg_ctx* c, const double* dj_seis, const double* dj_q, double*
       }
       HIPCHK(c, hipStreamSynchronize(c->stream));
     }
-    if (g_q0) {
-      double* out = g_q0 + run * nqb;
-      if (dev) {
-        std::vector<double> h(nqb);
-        if ((rc = get_dofs_from<R>(c, c->aLe.p, c->aLa.p, h.data()))) return rc;
-        HIPCHK(c, hipMemcpy(out, h.data(), nqb * sizeof(double), hipMemcpyHostToDevice));
-      } else if ((rc = get_dofs_from<R>(c, c->aLe.p, c->aLa.p, out))) {
-        return rc;
-      }
-    }
+    if (g_q0 && (rc = get_dofs_from<R>(c, c->aLe.p, c->aLa.p, g_q0 + run * nqb, dev))) return rc;
   }
   if (g_rho || g_vp || g_vs) {
     // chain rule on the device (gathers over face neighbours), then reorder

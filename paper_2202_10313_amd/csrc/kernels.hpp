@@ -119,6 +119,23 @@ int launch_pack_materials(const MatIn& m, int M, long long Kp, const long long* 
 int launch_scatter_gradient(const double* g, const long long* i2u, long long Kp, double* g_rho, double* g_vp,
                             double* g_vs, hipStream_t st);
 
+// DOF conversion (layout.hip): u2i [K] internal slot and code [K] vertex order
+// of each caller element; mats [24][2][B][B]: per vertex order the matrix from
+// the caller's modes to the sorted frame's, C[b][bb], and its transpose
+struct DofTables {
+  const long long* u2i;
+  const unsigned char* code;
+  const double* mats;
+  int B, M;
+};
+// dofs: device FP64 [n][9 + 6M][B] of caller elements k0 .. k0 + n - 1; Qe, Qa:
+// one run's state (the matrices are orthogonal, so adjoints convert the same way)
+template <class R>
+int launch_set_dofs(const DofTables& t, long long k0, long long n, const double* dofs, R* Qe, R* Qa, hipStream_t st);
+template <class R>
+int launch_get_dofs(const DofTables& t, long long k0, long long n, double* dofs, const R* Qe, const R* Qa,
+                    hipStream_t st);
+
 template <class R, int O, int M>
 int launch_level(const KPtrs& p, const LevelArgs& a, int runs, hipStream_t st);
 int launch_tick(long long* clock, long long d, hipStream_t st);
