@@ -21,7 +21,9 @@ LIB = os.path.join(LIBDIR, "libedge_lts.so")
 ORDERS = ["2", "3", "4", "5"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
-HIPFLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
+# contraction within an expression only, as the source writes it: instances of a
+# kernel (launch kinds, wave splits) then round alike, whatever code surrounds them
+HIPFLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-ffp-contract=on",
             "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
             "-I", CSRC, "-I", INCLUDE]
 

@@ -979,7 +979,7 @@ struct AdjLds2 {
 template <int O, int M>
 struct AdjScratch2 {
   using RF = edg_gen::Ref<O>;
-  static constexpr int NB0 = RF::MB1, NB1 = RF::B - RF::MB1;
+  static constexpr int NB0 = RF::mb(2, 1), NB1 = RF::B - RF::mb(2, 1);
   static constexpr int NBX = NB0 > NB1 ? NB0 : NB1;
   static constexpr int JW = (NBX + LPE - 1) / LPE;
   static constexpr int MM = M > 0 ? M : 1;
@@ -1036,7 +1036,7 @@ void k_adjoint2(KPtrs p, APtrs ad, LevelArgs a) {
   using L = AdjLds2<R, O, M>;
   constexpr int B = RF::B, F = RF::F, FP = RF::FP;
   constexpr int MM = M > 0 ? M : 1;
-  constexpr int NB0 = RF::MB1, NB1 = B - RF::MB1;
+  constexpr int NB0 = RF::mb(2, 1), NB1 = B - RF::mb(2, 1);
   constexpr int NBX = NB0 > NB1 ? NB0 : NB1;
   constexpr int JW = (NBX + LPE - 1) / LPE;      // owned memory modes per lane
   constexpr int JB = (B + LPE - 1) / LPE;        // memory-variable layout
@@ -1063,7 +1063,7 @@ void k_adjoint2(KPtrs p, APtrs ad, LevelArgs a) {
   // the long loops, so the compiler recomputes addresses there instead of
   // hoisting (and spilling) one per access
   int slot = ec * LPE + q;
-  int base = w ? RF::MB1 : 0;                      // opaque at the loop tops (see slot)
+  int base = w ? RF::mb(2, 1) : 0;                      // opaque at the loop tops (see slot)
   int jb0 = (base + q) / LPE;                      // memory-variable block of the lane's first owned mode
   const int nb = w ? NB1 : NB0;
   R* const reg = lds + ec * L::REGION;
@@ -1213,8 +1213,7 @@ void k_adjoint2(KPtrs p, APtrs ad, LevelArgs a) {
         R full[B];
 #pragma unroll
         for (int b = 0; b < B; ++b) full[b] = rx[q * BS + b];
-        if (w == 0) RF::ck_grad_p0(full, G, gw0, gw1, gw2);
-        else RF::ck_grad_p1(full, G, gw0, gw1, gw2);
+        RF::template ck_grad_w<2>(w, full, G, gw0, gw1, gw2);
       }
       __syncthreads();
       if (M > 0) {
@@ -1303,12 +1302,12 @@ void k_adjoint2(KPtrs p, APtrs ad, LevelArgs a) {
       R full[B], pt[2 * FP];
 #pragma unroll
       for (int b = 0; b < B; ++b) full[b] = rx[q * BS + b];
-      if (w == 0) RF::trace_p0(full, pt); else RF::trace_p1(full, pt);
+      RF::template trace_w<2>(w, full, pt);
       if (act)
 #pragma unroll
         for (int ii = 0; ii < 2; ++ii)
 #pragma unroll
-          for (int f = 0; f < FP; ++f) pm[(RF::tface(w, ii) * LPE + q) * FS + f] = pt[ii * FP + f];
+          for (int f = 0; f < FP; ++f) pm[(RF::template tchunk<2>(w, ii * (FP / 4)) / (FP / 4) * LPE + q) * FS + f] = pt[ii * FP + f];
     }
     __syncthreads();
     // items (face i, mode f) of the whole group, one 16-lane DPP row per
@@ -1435,13 +1434,8 @@ void k_adjoint2(KPtrs p, APtrs ad, LevelArgs a) {
       for (int i = 0; i < 4; ++i)
 #pragma unroll
         for (int f = 0; f < FP; ++f) pf[i * FP + f] = pm[(i * LPE + q) * FS + f];
-      // lifted into a fresh array, then added: accumulating into acc inside
-      // the two branches lets the compiler merge their first accesses through
-      // a pointer select, which keeps two entries of acc in scratch memory
       R lr[NBX];
-#pragma unroll
-      for (int lb = 0; lb < NBX; ++lb) lr[lb] = R(0);
-      if (w == 0) RF::lift_p0(pf, lr); else RF::lift_p1(pf, lr);
+      RF::template lift_w<2>(w, pf, lr);
 #pragma unroll
       for (int lb = 0; lb < NBX; ++lb) acc[lb] += lr[lb];
     }
@@ -1466,8 +1460,7 @@ void k_adjoint2(KPtrs p, APtrs ad, LevelArgs a) {
     R full[B];
 #pragma unroll
     for (int b = 0; b < B; ++b) full[b] = rx[q * BS + b];
-    if (w == 0) RF::vol_grad_p0(full, G, gw0, gw1, gw2);
-    else RF::vol_grad_p1(full, G, gw0, gw1, gw2);
+    RF::template vol_grad_w<2>(w, full, G, gw0, gw1, gw2);
   }
   if (threadIdx.x < 64 && act)      // zero row for the transposed products (written once, never overwritten)
     for (int b = q; b < BS; b += LPE) grad[19 * BS + b] = R(0);
@@ -1611,8 +1604,7 @@ void k_adjoint2(KPtrs p, APtrs ad, LevelArgs a) {
   };
   write_gb(R(-1));
   __syncthreads();
-  if (w == 0) RF::vol_grad_T_p0(gt0, gt1, gt2, G, lte);
-  else RF::vol_grad_T_p1(gt0, gt1, gt2, G, lte);
+  RF::template vol_grad_T_w<2>(w, gt0, gt1, gt2, G, lte);
   // the time-integral adjoints wait in memory (re-read with each
   // derivative's data), so they hold no registers across the loop below
   stE(SC::DT, lte);
@@ -1668,8 +1660,7 @@ void k_adjoint2(KPtrs p, APtrs ad, LevelArgs a) {
       __syncthreads();
       write_gb(R(1));
       __syncthreads();
-      if (w == 0) RF::ck_grad_T_p0(gt0, gt1, gt2, G, cur);
-      else RF::ck_grad_T_p1(gt0, gt1, gt2, G, cur);
+      RF::template ck_grad_T_w<2>(w, gt0, gt1, gt2, G, cur);
       // (no barrier: the coupling block below writes the wave's own modes of
       // the exchange and coupling rows, which the transposed product does
       // not read; the next iteration's products follow its first barrier)

@@ -39,7 +39,7 @@ static void term(std::string& s, bool& first, double c, const std::string& var) 
   first = false;
 }
 
-// faces traced by wave P of the two-wave split, in output order (see tface)
+// faces traced by wave P of the two-wave split, in output order
 static const int TFACE[2][2] = {{0, 3}, {1, 2}};
 
 int main(int argc, char** argv) {
@@ -182,11 +182,83 @@ int main(int argc, char** argv) {
       if (!first) std::fprintf(f, "    acc[%d] += %s;\n", b, s.c_str());
     }
     std::fprintf(f, "  }\n");
-    // ---- two-wave split: wave P owns elementwise modes [MB[P], MB[P+1]),
-    // computes stiffness outputs [SC[P], SC[P+1]) (time kernel) and
-    // [SV[P], SV[P+1]) (volume kernel), and the traces of faces 2P, 2P+1.
-    const int B0 = 9 * std::max(1, (B + 9) / 18);
-    auto split = [&](bool vol) {
+    // ---- W-wave splits (W = 2, 4): wave P of W owns the elementwise modes
+    // [mb(W, P), mb(W, P + 1)), computes a contiguous range of stiffness
+    // outputs balanced by cost and the trace chunks tchunk(W, P, .).
+    // X_w<W>(w, ...) runs wave w's part of X.
+    const int NCH = FP / 4;   // chunks of four face modes per face
+    std::vector<int> mbs[5], chunks[5][4];
+    for (int W = 2; W <= 4; W += 2) {
+      // modes: blocks of nine where they divide evenly enough (a memory-
+      // variable mode is owned by one of nine lanes), else equal parts
+      mbs[W].assign(W + 1, B);
+      for (int P = 0; P < W; ++P)
+        mbs[W][P] = W == 2 ? (P == 0 ? 0 : (B >= 18 ? 9 * ((B + 9) / 18) : (B + 1) / 2))
+                           : (B > 27 ? 9 * P : (P * B + W - 1) / W);
+      // trace chunks: W = 2 takes one of the two dense faces (0 and 1, the
+      // faces through the reference vertex's two first edges) and one of the
+      // sparse ones (2, 3) per wave; W = 4 deals chunks out, largest first
+      if (W == 2) {
+        for (int P = 0; P < 2; ++P)
+          for (int ii = 0; ii < 2; ++ii)
+            for (int k = 0; k < NCH; ++k) chunks[2][P].push_back(TFACE[P][ii] * NCH + k);
+      } else {
+        std::vector<std::pair<int, int>> cost;
+        for (int c = 0; c < 4 * NCH; ++c) {
+          int nz = 4;   // the chunk's stores
+          for (int ff = 4 * (c % NCH); ff < std::min(F, 4 * (c % NCH) + 4); ++ff)
+            for (int bb = 0; bb < B; ++bb) nz += std::fabs(M.Ft[(c / NCH * B + bb) * F + ff]) > ZERO_TOL;
+          cost.push_back({-nz, c});
+        }
+        std::sort(cost.begin(), cost.end());
+        int load[4] = {0, 0, 0, 0};
+        for (auto& x : cost) {
+          const int P = (int)(std::min_element(load, load + 4) - load);
+          load[P] -= x.first;
+          chunks[4][P].push_back(x.second);
+        }
+      }
+    }
+    size_t ntc[5] = {0};
+    for (int W = 2; W <= 4; W += 2)
+      for (int P = 0; P < W; ++P) ntc[W] = std::max(ntc[W], chunks[W][P].size());
+    std::fprintf(f, "  // first mode of wave p of W (p = W: B); largest and smallest number of modes of a wave; every first mode a multiple of 9\n");
+    std::fprintf(f, "  __host__ __device__ static constexpr int mb(int W, int p) { return W == 2 ? (p == 0 ? 0 : p == 1 ? %d : %d) : (p == 0 ? 0 : p == 1 ? %d : p == 2 ? %d : p == 3 ? %d : %d); }\n",
+                 mbs[2][1], B, mbs[4][1], mbs[4][2], mbs[4][3], B);
+    for (int W = 2; W <= 4; W += 2) {
+      int nbx = 0, nbn = B, tn = 99;
+      bool al = true;
+      for (int P = 0; P < W; ++P) {
+        nbx = std::max(nbx, mbs[W][P + 1] - mbs[W][P]);
+        nbn = std::min(nbn, mbs[W][P + 1] - mbs[W][P]);
+        tn = std::min(tn, (int)chunks[W][P].size());
+        al = al && mbs[W][P] % 9 == 0;
+      }
+      std::fprintf(f, "  static constexpr int NBX%d = %d, NBN%d = %d, NTN%d = %d;\n  static constexpr bool NINES%d = %s;\n", W, nbx,
+                   W, nbn, W, tn, W, al ? "true" : "false");
+    }
+    std::fprintf(f, "  template <int W> static constexpr int nbx = W == 2 ? NBX2 : NBX4;\n");
+    std::fprintf(f, "  template <int W> static constexpr int nbn = W == 2 ? NBN2 : NBN4;\n  template <int W> static constexpr int ntn = W == 2 ? NTN2 : NTN4;\n");
+    std::fprintf(f, "  template <int W> static constexpr bool nines = W == 2 ? NINES2 : NINES4;\n");
+    std::fprintf(f, "  // trace chunks (four face modes each) of wave p of W: their number, at most ntc, at least ntn; chunk ii is face tchunk / %d, modes 4 (tchunk %% %d) ..\n", NCH, NCH);
+    std::fprintf(f, "  template <int W> static constexpr int ntc = W == 2 ? %d : %d;\n", (int)ntc[2], (int)ntc[4]);
+    std::fprintf(f, "  // (-1: none); 6 bits per entry\n");
+    std::fprintf(f, "  template <int W> __device__ static __forceinline__ int tchunk(int p, int ii) {\n");
+    for (int W = 2; W <= 4; W += 2) {
+      std::fprintf(f, "    if (W == %d) {\n", W);
+      for (int P = 0; P < W; ++P) {
+        unsigned long long w = 0;
+        for (size_t ii = 0; ii < ntc[W]; ++ii)
+          w |= (unsigned long long)(ii < chunks[W][P].size() ? chunks[W][P][ii] : 63) << (6 * ii);
+        std::fprintf(f, "      %sconst unsigned long long t%d = 0x%llxull;\n", "", P, w);
+      }
+      if (W == 2) std::fprintf(f, "      const unsigned long long t = p == 0 ? t0 : t1;\n");
+      else std::fprintf(f, "      const unsigned long long t = p == 0 ? t0 : p == 1 ? t1 : p == 2 ? t2 : t3;\n");
+      std::fprintf(f, "      const int c = (int)((t >> (6 * ii)) & 63);\n      return c == 63 ? -1 : c;\n    }\n");
+    }
+    std::fprintf(f, "    return -1;\n  }\n");
+    // stiffness output ranges, balanced by cost
+    auto split = [&](bool vol, int W) {
       std::vector<int> nz(B, 0);
       for (int b = 0; b < B; ++b)
         for (int c = 0; c < 3; ++c)
@@ -199,110 +271,135 @@ int main(int argc, char** argv) {
       std::vector<double> cost(B);
       double tot = 0;
       for (int b = 0; b < B; ++b) { cost[b] = nz[b] ? nz[b] + 9.0 : 3.0; tot += cost[b]; }
+      std::vector<int> cut(1, 0);
       double acc = 0;
       int s = 0;
-      while (s < B && acc + cost[s] / 2 < tot / 2) acc += cost[s++];
-      return s;
+      for (int P = 1; P < W; ++P) {
+        while (s < B && acc + cost[s] / 2 < tot * P / W) acc += cost[s++];
+        cut.push_back(s);
+      }
+      cut.push_back(B);
+      return cut;
     };
-    const int SC = split(false), SV = split(true);
-    std::fprintf(f, "  static constexpr int MB1 = %d;  // wave 1 owns modes [MB1, B)\n", B0 < B ? B0 : B);
-    // traces of the two-wave split: faces 0 and 1 carry most non-zeros (the
-    // faces through the reference vertex's two first edges), so each wave
-    // takes one of them and one of the sparse faces 2, 3
-    std::fprintf(f, "  // wave w traces faces tface(w, 0) and tface(w, 1)\n");
-    std::fprintf(f, "  __host__ __device__ static constexpr int tface(int w, int ii) { return w == 0 ? (ii == 0 ? 0 : 3) : (ii == 0 ? 1 : 2); }\n");
-    std::fprintf(f, "  static constexpr int SC1 = %d, SV1 = %d;\n", SC, SV);
-    for (int vol = 0; vol < 2; ++vol)
-      for (int P = 0; P < 2; ++P) {
-        const int lo = P == 0 ? 0 : (vol ? SV : SC), hi = P == 0 ? (vol ? SV : SC) : B;
-        std::fprintf(f, "  template <class R> __device__ static __forceinline__ void %s_p%d(const R* __restrict__ d, const R* __restrict__ G, R* g0, R* g1, R* g2) {\n",
-                     vol ? "vol_grad" : "ck_grad", P);
-        for (int b = lo; b < hi; ++b) {
-          bool any = false;
-          for (int c = 0; c < 3; ++c) {
+    // emits X_w<W>(w, ...), the dispatch over the waves of both splits
+    auto dispatch = [&](const char* name, const char* params, const char* call) {
+      std::fprintf(f, "  template <int W, class R> __device__ static __forceinline__ void %s_w(int w, %s) {\n", name, params);
+      std::fprintf(f, "    if constexpr (W == 2) {\n      if (w == 0) %s_w2p0(%s); else %s_w2p1(%s);\n    } else {\n", name, call,
+                   name, call);
+      std::fprintf(f, "      if (w < 2) { if (w == 0) %s_w4p0(%s); else %s_w4p1(%s); }\n", name, call, name, call);
+      std::fprintf(f, "      else { if (w == 2) %s_w4p2(%s); else %s_w4p3(%s); }\n    }\n  }\n", name, call, name, call);
+    };
+    for (int W = 2; W <= 4; W += 2)
+      for (int vol = 0; vol < 2; ++vol) {
+        const std::vector<int> cut = split(vol != 0, W);
+        for (int P = 0; P < W; ++P) {
+          std::fprintf(f, "  template <class R> __device__ static __forceinline__ void %s_w%dp%d(const R* __restrict__ d, const R* __restrict__ G, R* g0, R* g1, R* g2) {\n",
+                       vol ? "vol_grad" : "ck_grad", W, P);
+          for (int b = cut[P]; b < cut[P + 1]; ++b) {
+            bool any = false;
+            for (int c = 0; c < 3; ++c) {
+              std::string t;
+              bool first = true;
+              for (int bb = 0; bb < B; ++bb) {
+                const double k = vol ? Kd[(c * B + bb) * B + b] : Kd[(c * B + b) * B + bb];
+                if (std::fabs(k) > ZERO_TOL) term(t, first, k, "d[" + std::to_string(bb) + "]");
+              }
+              if (first) t = "R(0)";
+              else any = true;
+              std::fprintf(f, "    const R x%d_%d = %s;\n", c, b, t.c_str());
+            }
+            if (any) {
+              std::fprintf(f, "    g0[%d] = G[0]*x0_%d + G[3]*x1_%d + G[6]*x2_%d;\n", b, b, b, b);
+              std::fprintf(f, "    g1[%d] = G[1]*x0_%d + G[4]*x1_%d + G[7]*x2_%d;\n", b, b, b, b);
+              std::fprintf(f, "    g2[%d] = G[2]*x0_%d + G[5]*x1_%d + G[8]*x2_%d;\n", b, b, b, b);
+            } else {
+              std::fprintf(f, "    g0[%d] = R(0); g1[%d] = R(0); g2[%d] = R(0);\n", b, b, b);
+            }
+          }
+          std::fprintf(f, "  }\n");
+        }
+      }
+    for (int W = 2; W <= 4; W += 2)
+      for (int P = 0; P < W; ++P) {
+        std::fprintf(f, "  template <class R> __device__ static __forceinline__ void trace_w%dp%d(const R* __restrict__ t, R* __restrict__ p) {\n", W, P);
+        for (size_t ii = 0; ii < ntc[W]; ++ii)
+          for (int k = 0; k < 4; ++k) {
             std::string t;
             bool first = true;
-            for (int bb = 0; bb < B; ++bb) {
-              const double k = vol ? Kd[(c * B + bb) * B + b] : Kd[(c * B + b) * B + bb];
-              if (std::fabs(k) > ZERO_TOL) term(t, first, k, "d[" + std::to_string(bb) + "]");
+            if (ii < chunks[W][P].size()) {
+              const int c = chunks[W][P][ii], i = c / NCH, ff = 4 * (c % NCH) + k;
+              if (ff < F)
+                for (int b = 0; b < B; ++b) {
+                  const double v = M.Ft[(i * B + b) * F + ff];
+                  if (std::fabs(v) > ZERO_TOL) term(t, first, v, "t[" + std::to_string(b) + "]");
+                }
             }
             if (first) t = "R(0)";
-            else any = true;
-            std::fprintf(f, "    const R x%d_%d = %s;\n", c, b, t.c_str());
+            std::fprintf(f, "    p[%d] = %s;\n", (int)(4 * ii) + k, t.c_str());
           }
-          if (any) {
-            std::fprintf(f, "    g0[%d] = G[0]*x0_%d + G[3]*x1_%d + G[6]*x2_%d;\n", b, b, b, b);
-            std::fprintf(f, "    g1[%d] = G[1]*x0_%d + G[4]*x1_%d + G[7]*x2_%d;\n", b, b, b, b);
-            std::fprintf(f, "    g2[%d] = G[2]*x0_%d + G[5]*x1_%d + G[8]*x2_%d;\n", b, b, b, b);
-          } else {
-            std::fprintf(f, "    g0[%d] = R(0); g1[%d] = R(0); g2[%d] = R(0);\n", b, b, b);
-          }
-        }
         std::fprintf(f, "  }\n");
-      }
-    for (int P = 0; P < 2; ++P) {
-      std::fprintf(f, "  template <class R> __device__ static __forceinline__ void trace_p%d(const R* __restrict__ t, R* __restrict__ p) {\n", P);
-      for (int ii = 0; ii < 2; ++ii) {
-        const int i = TFACE[P][ii];
-        for (int ff = 0; ff < FP; ++ff) {
+        const int lo = mbs[W][P], hi = mbs[W][P + 1];
+        // (assigned, not accumulated, and to all entries up to the largest
+        // wave's: waves that touch different entries of a caller's array let
+        // the compiler merge their accesses through a pointer select, which
+        // keeps entries of it in scratch memory)
+        std::fprintf(f, "  template <class R> __device__ static __forceinline__ void lift_w%dp%d(const R* __restrict__ p, R* __restrict__ out) {\n", W, P);
+        int nbx = 0;
+        for (int P2 = 0; P2 < W; ++P2) nbx = std::max(nbx, mbs[W][P2 + 1] - mbs[W][P2]);
+        for (int lb = 0; lb < nbx; ++lb) {
+          const int b = mbs[W][P] + lb;
           std::string t;
           bool first = true;
-          if (ff < F)
-            for (int b = 0; b < B; ++b) {
-              const double v = M.Ft[(i * B + b) * F + ff];
-              if (std::fabs(v) > ZERO_TOL) term(t, first, v, "t[" + std::to_string(b) + "]");
-            }
+          if (b < mbs[W][P + 1])
+            for (int i = 0; i < 4; ++i)
+              for (int ff = 0; ff < F; ++ff) {
+                const double v = M.Ft[(i * B + b) * F + ff];
+                if (std::fabs(v) > ZERO_TOL) term(t, first, v, "p[" + std::to_string(i * FP + ff) + "]");
+              }
           if (first) t = "R(0)";
-          std::fprintf(f, "    p[%d] = %s;\n", ii * FP + ff, t.c_str());
-        }
-      }
-      std::fprintf(f, "  }\n");
-      const int lo = P == 0 ? 0 : std::min(B0, B), hi = P == 0 ? std::min(B0, B) : B;
-      std::fprintf(f, "  template <class R> __device__ static __forceinline__ void lift_p%d(const R* __restrict__ p, R* __restrict__ acc) {\n", P);
-      for (int b = lo; b < hi; ++b) {
-        std::string t;
-        bool first = true;
-        for (int i = 0; i < 4; ++i)
-          for (int ff = 0; ff < F; ++ff) {
-            const double v = M.Ft[(i * B + b) * F + ff];
-            if (std::fabs(v) > ZERO_TOL) term(t, first, v, "p[" + std::to_string(i * FP + ff) + "]");
-          }
-        if (!first) std::fprintf(f, "    acc[%d] += %s;\n", b - lo, t.c_str());
-      }
-      std::fprintf(f, "  }\n");
-    }
-    // transposed stiffness for the two-wave split: full input rows g0, g1,
-    // g2 (one per physical direction), outputs for the wave's own modes
-    // [0, MB1) or [MB1, B), written relative to the first
-    for (int vol = 0; vol < 2; ++vol)
-      for (int P = 0; P < 2; ++P) {
-        const int mb = B0 < B ? B0 : B;
-        const int lo = P == 0 ? 0 : mb, hi = P == 0 ? mb : B;
-        std::fprintf(f, "  template <class R> __device__ static __forceinline__ void %s_p%d(const R* g0, const R* g1, const R* g2, const R* __restrict__ G, R* __restrict__ acc) {\n",
-                     vol ? "vol_grad_T" : "ck_grad_T", P);
-        for (int c = 0; c < 3; ++c) {
-          for (int b = 0; b < B; ++b) {
-            bool used = false;
-            for (int bb = lo; bb < hi && !used; ++bb) {
-              const double k = vol ? Kd[(c * B + bb) * B + b] : Kd[(c * B + b) * B + bb];
-              used = std::fabs(k) > ZERO_TOL;
-            }
-            if (used)
-              std::fprintf(f, "    const R y%d_%d = G[%d]*g0[%d] + G[%d]*g1[%d] + G[%d]*g2[%d];\n", c, b, 3 * c, b,
-                           3 * c + 1, b, 3 * c + 2, b);
-          }
-          for (int bb = lo; bb < hi; ++bb) {
-            std::string t;
-            bool first = true;
-            for (int b = 0; b < B; ++b) {
-              const double k = vol ? Kd[(c * B + bb) * B + b] : Kd[(c * B + b) * B + bb];
-              if (std::fabs(k) > ZERO_TOL) term(t, first, k, "y" + std::to_string(c) + "_" + std::to_string(b));
-            }
-            if (!first) std::fprintf(f, "    acc[%d] += %s;\n", bb - lo, t.c_str());
-          }
+          std::fprintf(f, "    out[%d] = %s;\n", lb, t.c_str());
         }
         std::fprintf(f, "  }\n");
       }
+    // transposed stiffness: full input rows g0, g1, g2 (one per physical
+    // direction), outputs for the wave's own modes, relative to its first
+    for (int W = 2; W <= 4; W += 2)
+      for (int vol = 0; vol < 2; ++vol)
+        for (int P = 0; P < W; ++P) {
+          const int lo = mbs[W][P], hi = mbs[W][P + 1];
+          std::fprintf(f, "  template <class R> __device__ static __forceinline__ void %s_w%dp%d(const R* g0, const R* g1, const R* g2, const R* __restrict__ G, R* __restrict__ acc) {\n",
+                       vol ? "vol_grad_T" : "ck_grad_T", W, P);
+          for (int c = 0; c < 3; ++c) {
+            for (int b = 0; b < B; ++b) {
+              bool used = false;
+              for (int bb = lo; bb < hi && !used; ++bb) {
+                const double k = vol ? Kd[(c * B + bb) * B + b] : Kd[(c * B + b) * B + bb];
+                used = std::fabs(k) > ZERO_TOL;
+              }
+              if (used)
+                std::fprintf(f, "    const R y%d_%d = G[%d]*g0[%d] + G[%d]*g1[%d] + G[%d]*g2[%d];\n", c, b, 3 * c, b,
+                             3 * c + 1, b, 3 * c + 2, b);
+            }
+            for (int bb = lo; bb < hi; ++bb) {
+              std::string t;
+              bool first = true;
+              for (int b = 0; b < B; ++b) {
+                const double k = vol ? Kd[(c * B + bb) * B + b] : Kd[(c * B + b) * B + bb];
+                if (std::fabs(k) > ZERO_TOL) term(t, first, k, "y" + std::to_string(c) + "_" + std::to_string(b));
+              }
+              if (!first) std::fprintf(f, "    acc[%d] += %s;\n", bb - lo, t.c_str());
+            }
+          }
+          std::fprintf(f, "  }\n");
+        }
+    const char* gp = "const R* __restrict__ d, const R* __restrict__ G, R* g0, R* g1, R* g2";
+    dispatch("ck_grad", gp, "d, G, g0, g1, g2");
+    dispatch("vol_grad", gp, "d, G, g0, g1, g2");
+    const char* gtp = "const R* g0, const R* g1, const R* g2, const R* __restrict__ G, R* __restrict__ acc";
+    dispatch("ck_grad_T", gtp, "g0, g1, g2, G, acc");
+    dispatch("vol_grad_T", gtp, "g0, g1, g2, G, acc");
+    dispatch("trace", "const R* __restrict__ t, R* __restrict__ p", "t, p");
+    dispatch("lift", "const R* __restrict__ p, R* __restrict__ out", "p, out");
     std::fprintf(f, "};\n");
   }
   std::fprintf(f, "}  // namespace edg_gen\n");

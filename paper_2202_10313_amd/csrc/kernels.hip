@@ -5,15 +5,16 @@
 // ader_derivative_anelastic, volume, local/neigh surface kernels, update) and
 // Sec. V-B (Buffers and Algorithm; eq. lts_buffers and the buffer consumption rules).
 //
-// Work mapping.  One wave (64 lanes) owns 7 elements; lane = 9*e + q holds the
-// modal row q (0..5 stresses xx,yy,zz,xy,yz,xz; 6..8 velocities u,v,w) of
-// element e, and all 6m memory variables of the modes b = q + 9 jb (the
-// anelastic terms act mode by mode, so this spreads them evenly over the 9
-// lanes and keeps each mechanism's trace inside one lane).  Reference-matrix
-// products (K_c, F~_i, F^_i) act inside a row, so every lane applies the same
-// sparse matrix: they are straight-line FMAs with compile-time constants
-// (generated/refmats.h).  Products that mix rows (Jacobians, star matrices,
-// flux solvers, anelastic coupling) go through a per-wave LDS exchange.
+// Work mapping.  A workgroup of W waves (2 or 4) owns 7 elements; in each wave
+// lane = 9*e + q holds part of the modal row q (0..5 stresses
+// xx,yy,zz,xy,yz,xz; 6..8 velocities u,v,w) of element e: the modes are split
+// between the waves, and the memory variables of a mode belong to one lane of
+// the wave that owns it (the anelastic terms act mode by mode, so this spreads
+// them evenly over the 9 lanes and keeps each mechanism's trace inside one
+// lane).  Reference-matrix products (K_c, F~_i, F^_i) act inside a row, so
+// every lane applies the same sparse matrix: they are straight-line FMAs with
+// compile-time constants (generated/refmats.h).  Products that mix rows
+// (Jacobians, star matrices, flux solvers, anelastic coupling) go through LDS.
 // Lane 63 repeats lane 54's work and never writes global memory.
 //
 // Differences from the paper's own kernel layout (prior art for Xeon):
@@ -45,425 +46,22 @@ namespace edg {
 
 namespace {
 
-template <class R, int O, int M>
-struct LdsLayout {
-  using RF = edg_gen::Ref<O>;
-  static constexpr int B = RF::B, FP = RF::FP;
-  static constexpr int FACE = 4 * 2 * LPE * FP;          // [face][side][row][f]
-  static constexpr int GRAD = LPE * 3 * B;                // [row][dir][b]
-  static constexpr int COUP = M > 0 ? 6 * B : 0;          // [stress comp][b]
-  static constexpr int REGION = FACE > GRAD + COUP ? FACE : GRAD + COUP;
-  static constexpr int TOTAL = EPW * REGION;              // lane 63 shares element 6's region
-};
-
-template <class R, int O, int M>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(1, 2)))
-void k_level(KPtrs p, LevelArgs a) {
-  using RF = edg_gen::Ref<O>;
-  using L = LdsLayout<R, O, M>;
-  constexpr int B = RF::B, F = RF::F, FP = RF::FP;
-  constexpr int MM = M > 0 ? M : 1;
-  constexpr int JB = (B + LPE - 1) / LPE;   // modes owned per lane for the memory variables
-  __shared__ R lds[L::TOTAL];
-
-  const int lane = threadIdx.x;
-  const int e = lane / LPE, r = lane % LPE;
-  const int ec = e < EPW ? e : EPW - 1;     // lane 63 duplicates lane 54 (same element, same row)
-  const int q = e < EPW ? r : 0;
-  int g, run;
-  group_and_run(a, g, run);
-  select_run<R>(p, run);
-  const int elem = g * EPW + ec;
-  const int cl = cluster_of(a, g * EPW);        // one cluster per workgroup (uniform)
-  const bool valid = (e < EPW) && (elem < a.cl_vend[cl]);
-  const int slot = ec * LPE + q;
-  R* const reg = lds + ec * L::REGION;
-
-  R* Qe = reinterpret_cast<R*>(p.Qe);
-  R* Qa = reinterpret_cast<R*>(p.Qa);
-  const R* P = reinterpret_cast<const R*>(p.P) + (size_t)elem * NPARAM;
-  const int* FI = p.FI + (size_t)elem * FI_WORDS;
-  const size_t Kp = (size_t)p.Kp;
-  const size_t tstride = (size_t)4 * LPE * FP;   // per element in a trace slot
-
-  const bool is_stress = q < 6;
-  int qi = 0, qj = 0;                        // stress component (i, j) of this row
-  if (q < 3) { qi = q; qj = q; }
-  else if (q == 3) { qi = 0; qj = 1; }
-  else if (q == 4) { qi = 1; qj = 2; }
-  else if (q == 5) { qi = 0; qj = 2; }
-  const R delta = q < 3 ? R(1) : R(0);
-
-  // element parameters
-  R G[9];
-#pragma unroll
-  for (int c = 0; c < 9; ++c) G[c] = P[c];
-  const R rho_inv = P[9], lam = P[10], mu = P[11], zp = P[12], zs = P[13];
-  R al[MM], bl[MM], om[MM];
-#pragma unroll
-  for (int l = 0; l < MM; ++l) {
-    al[l] = M > 0 ? P[14 + 2 * l] : R(0);
-    bl[l] = M > 0 ? P[15 + 2 * l] : R(0);
-    om[l] = M > 0 ? R(a.omega[l]) : R(0);
-  }
-
-  // elastic DOFs: this lane's row, all modes.  Memory variables: all
-  // 6m components of the modes b = q + 9 jb owned by this lane.
-  R qe[B];
-  const size_t gbase = (size_t)g * B;
-#pragma unroll
-  for (int b = 0; b < B; ++b) qe[b] = Qe[(gbase + b) * NSLOT + slot];
-
-  // rows of the gradient exchange this lane reads
-  int rA = 0, rB = 0, rC = 0;   // velocity lane: sigma_{i,d} along d
-  if (!is_stress) {
-    const int i = q - 6;
-    rA = sym_index(i, 0) * 3 * B + 0 * B;
-    rB = sym_index(i, 1) * 3 * B + 1 * B;
-    rC = sym_index(i, 2) * 3 * B + 2 * B;
-  }
-  const int eA = (6 + qi) * 3 * B + qj * B;   // d v_i / d x_j
-  const int eB = (6 + qj) * 3 * B + qi * B;   // d v_j / d x_i
-  const int d0 = 6 * 3 * B + 0 * B, d1 = 7 * 3 * B + 1 * B, d2 = 8 * 3 * B + 2 * B;
-  R* const grad = reg;
-  R* const coup = reg + L::GRAD;
-
-  // ------------------------------------------------ surface: finish step n
-  // (the memory variables are loaded afterwards; their surface term goes
-  // through the LDS area `coup`)
-  bool coup_pending = false;
-  if (a.kind != KIND_PREDICT) {
-    const int n = step_fin_of(a, cl);
-    const R* T1 = reinterpret_cast<const R*>(p.T1);
-    const R* T2 = reinterpret_cast<const R*>(p.T2);
-    const R* T3 = reinterpret_cast<const R*>(p.T3);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int nb = FI[3 * i];
-      const int code = FI[3 * i + 1];
-      const size_t aux = (size_t)FI[3 * i + 2];
-      const int j = code & 15, rel = ((code >> 8) & 15) - 1;
-      const R* own = T1 + ((size_t)(n & 1) * Kp + elem) * tstride + (size_t)(i * LPE + q) * FP;
-      R* dmn = reg + ((i * 2 + 0) * LPE + q) * FP;
-      R* dpl = reg + ((i * 2 + 1) * LPE + q) * FP;
-#pragma unroll
-      for (int f = 0; f < FP; ++f) dmn[f] = own[f];
-      if (nb >= 0) {
-        const size_t nbo = (size_t)nb * tstride + (size_t)(j * LPE + q) * FP;
-        if (rel == 0) {
-          const R* s = T1 + (size_t)(n & 1) * Kp * tstride + nbo;
-#pragma unroll
-          for (int f = 0; f < FP; ++f) dpl[f] = s[f];
-        } else if (rel < 0) {       // finer neighbour: its accumulated B3
-          const R* s = T3 + ((size_t)(n & 1) * p.N3 + aux) * tstride + (size_t)(j * LPE + q) * FP;
-#pragma unroll
-          for (int f = 0; f < FP; ++f) dpl[f] = s[f];
-        } else {                    // coarser neighbour: B2, then B1 - B2
-          const int c = (n >> 1) & 1;
-          const R* s2 = T2 + ((size_t)c * p.N2 + aux) * tstride + (size_t)(j * LPE + q) * FP;
-          if ((n & 1) == 0) {
-#pragma unroll
-            for (int f = 0; f < FP; ++f) dpl[f] = s2[f];
-          } else {
-            const R* s1 = T1 + (size_t)c * Kp * tstride + nbo;
-#pragma unroll
-            for (int f = 0; f < FP; ++f) dpl[f] = s1[f] - s2[f];
-          }
-        }
-      } else {
-#pragma unroll
-        for (int f = 0; f < FP; ++f) dpl[f] = R(0);
-      }
-    }
-    __syncthreads();
-    // Godunov solves: 4F (face, mode) items spread over the element's 9 lanes
-#pragma unroll 1
-    for (int rr = 0; rr < (4 * F + LPE - 1) / LPE; ++rr) {
-      const int t = q + LPE * rr;
-      if (t < 4 * F) {
-        const int i = t / F, f = t % F;
-        const int code = FI[3 * i + 1];
-        const int bc = (code >> 4) & 15;
-        const R* fp = P + 20 + 6 * i;
-        R qm[9], qp[9], out[15];
-#pragma unroll
-        for (int k = 0; k < 9; ++k) {
-          qm[k] = reg[((i * 2 + 0) * LPE + k) * FP + f];
-          qp[k] = reg[((i * 2 + 1) * LPE + k) * FP + f];
-        }
-        const R zpp = bc == 0 ? fp[4] : zp, zsp = bc == 0 ? fp[5] : zs;
-        godunov<R>(qm, qp, fp[0], fp[1], fp[2], zp, zs, zpp, zsp, lam, mu, rho_inv, fp[3], bc, out);
-#pragma unroll
-        for (int k = 0; k < 15; ++k) reg[((i * 2 + k / 9) * LPE + k % 9) * FP + f] = out[k];
-      }
-    }
-    __syncthreads();
-    R da[B];
-    {
-      R pf[4 * FP];
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int f = 0; f < FP; ++f) pf[i * FP + f] = reg[((i * 2 + 0) * LPE + q) * FP + f];
-      RF::lift(pf, qe);
-      if (M > 0) {
-#pragma unroll
-        for (int b = 0; b < B; ++b) da[b] = R(0);
-        if (is_stress) {
-#pragma unroll
-          for (int i = 0; i < 4; ++i)
-#pragma unroll
-            for (int f = 0; f < FP; ++f) pf[i * FP + f] = reg[((i * 2 + 1) * LPE + q) * FP + f];
-          RF::lift(pf, da);
-        }
-      }
-    }
-    if (M > 0) {
-      // the strain-rate flux of stress component q, lifted, reaches the
-      // memory variables of that component through the mode owners
-      __syncthreads();
-      if (is_stress && e < EPW)
-#pragma unroll
-        for (int b = 0; b < B; ++b) coup[q * B + b] = da[b];
-      coup_pending = true;
-    }
-    __syncthreads();
-  }
-
-  R qa[JB][MM][6];
-#pragma unroll
-  for (int jb = 0; jb < JB; ++jb) {
-    const int b = q + LPE * jb;
-#pragma unroll
-    for (int l = 0; l < MM; ++l)
-#pragma unroll
-      for (int c = 0; c < 6; ++c) {
-        qa[jb][l][c] = M > 0 ? Qa[((((size_t)g * JB + jb) * MM + l) * 6 + c) * NSLOT + slot] : R(0);
-        if (M > 0 && coup_pending && b < B) qa[jb][l][c] += om[l] * coup[c * B + b];
-      }
-  }
-  if (M > 0 && coup_pending) __syncthreads();
-
-  if (a.kind == KIND_NEIGHBOR) {
-    if (valid) {
-#pragma unroll
-      for (int b = 0; b < B; ++b) Qe[(gbase + b) * NSLOT + slot] = qe[b];
-      if (M > 0)
-#pragma unroll
-        for (int jb = 0; jb < JB; ++jb)
-#pragma unroll
-          for (int l = 0; l < MM; ++l)
-#pragma unroll
-            for (int c = 0; c < 6; ++c) Qa[((((size_t)g * JB + jb) * MM + l) * 6 + c) * NSLOT + slot] = qa[jb][l][c];
-    }
-    return;
-  }
-
-  // the start-of-step state, recorded for the reverse sweep when asked
-  // (every element slot of the group; padding slots get the zeros their state holds)
-  if (a.rec_e != nullptr && e < EPW) {
-    R* const Re = reinterpret_cast<R*>(a.rec_e);
-#pragma unroll
-    for (int b = 0; b < B; ++b) Re[(gbase + b) * NSLOT + slot] = valid ? qe[b] : R(0);
-    if (M > 0) {
-      R* const Ra = reinterpret_cast<R*>(a.rec_a);
-#pragma unroll
-      for (int jb = 0; jb < JB; ++jb)
-#pragma unroll
-        for (int l = 0; l < MM; ++l)
-#pragma unroll
-          for (int c = 0; c < 6; ++c)
-            Ra[((((size_t)g * JB + jb) * MM + l) * 6 + c) * NSLOT + slot] = valid ? qa[jb][l][c] : R(0);
-    }
-  }
-
-  // ------------------------------------------------ time kernel: predict step nn
-  const int nn = step_new_of(a, cl);
-  const int eflags = FI[12];
-  const bool need_b2 = __any((eflags & EF_HAS_FINER) != 0);
-  const int rec_slot = FI[15];
-  R de[B], te[B], t2[B];
-  R dm[JB][MM][6];
-#pragma unroll
-  for (int b = 0; b < B; ++b) { de[b] = qe[b]; te[b] = R(0); t2[b] = R(0); }
-#pragma unroll
-  for (int jb = 0; jb < JB; ++jb)
-#pragma unroll
-    for (int l = 0; l < MM; ++l)
-#pragma unroll
-      for (int c = 0; c < 6; ++c) dm[jb][l][c] = qa[jb][l][c];
-
-#pragma unroll 1
-  for (int d = 0; d < O; ++d) {
-    const R c_d = R(a.tc[cl][d]), h_d = R(a.th[cl][d]);
-    const bool more = d + 1 < O;
-#pragma unroll
-    for (int b = 0; b < B; ++b) te[b] += c_d * de[b];
-    if (need_b2)
-#pragma unroll
-      for (int b = 0; b < B; ++b) t2[b] += h_d * de[b];
-    if (rec_slot >= 0 && valid) {
-      R* rd = reinterpret_cast<R*>(p.recD) + (((size_t)rec_slot * O + d) * LPE + q) * B;
-#pragma unroll
-      for (int b = 0; b < B; ++b) rd[b] = de[b];
-    }
-    if (more) RF::ck_grad(de, G, grad + q * 3 * B);
-    __syncthreads();
-    if (M > 0) {
-      // memory variables of the owned modes: coupling into the stresses
-      // (-sum_l a_l tr(theta^l) I + b_l theta^l), the volume term
-      // -omega_l T^{a,l}, and the next derivative omega_l (eps - theta^l)
-#pragma unroll
-      for (int jb = 0; jb < JB; ++jb) {
-        const int b = q + LPE * jb;
-        if (b < B) {
-          R eps[6];
-          if (more) {
-            eps[0] = grad[6 * 3 * B + 0 * B + b];
-            eps[1] = grad[7 * 3 * B + 1 * B + b];
-            eps[2] = grad[8 * 3 * B + 2 * B + b];
-            eps[3] = R(0.5) * (grad[6 * 3 * B + 1 * B + b] + grad[7 * 3 * B + 0 * B + b]);
-            eps[4] = R(0.5) * (grad[7 * 3 * B + 2 * B + b] + grad[8 * 3 * B + 1 * B + b]);
-            eps[5] = R(0.5) * (grad[6 * 3 * B + 2 * B + b] + grad[8 * 3 * B + 0 * B + b]);
-          }
-          R cp[6] = {R(0), R(0), R(0), R(0), R(0), R(0)};
-#pragma unroll
-          for (int l = 0; l < MM; ++l) {
-            const R tr = dm[jb][l][0] + dm[jb][l][1] + dm[jb][l][2];
-#pragma unroll
-            for (int c = 0; c < 6; ++c) cp[c] -= bl[l] * dm[jb][l][c] + (c < 3 ? al[l] * tr : R(0));
-#pragma unroll
-            for (int c = 0; c < 6; ++c) {
-              qa[jb][l][c] -= om[l] * c_d * dm[jb][l][c];
-              if (more) dm[jb][l][c] = om[l] * (eps[c] - dm[jb][l][c]);
-            }
-          }
-          if (e < EPW)
-#pragma unroll
-            for (int c = 0; c < 6; ++c) coup[c * B + b] = cp[c];
-        }
-      }
-      __syncthreads();
-    }
-    if (is_stress) {
-#pragma unroll
-      for (int b = 0; b < B; ++b) {
-        const R cq = M > 0 ? coup[q * B + b] : R(0);
-        if (M > 0) qe[b] += c_d * cq;                 // volume: E^l T^{a,l}
-        if (more) {
-          const R eps = R(0.5) * (grad[eA + b] + grad[eB + b]);
-          const R div = grad[d0 + b] + grad[d1 + b] + grad[d2 + b];
-          de[b] = lam * delta * div + R(2) * mu * eps + cq;
-        }
-      }
-    } else if (more) {
-#pragma unroll
-      for (int b = 0; b < B; ++b) de[b] = rho_inv * (grad[rA + b] + grad[rB + b] + grad[rC + b]);
-    }
-    __syncthreads();
-  }
-
-  // ------------------------------------------------ buffers as face traces
-  {
-    R pt[4 * FP];
-    RF::trace(te, pt);
-    const size_t own = ((size_t)(nn & 1) * Kp + elem) * tstride + (size_t)q * FP;
-    if (valid) {
-      R* T1 = reinterpret_cast<R*>(p.T1);
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int f = 0; f < FP; ++f) T1[own + (size_t)i * LPE * FP + f] = pt[i * FP + f];
-    }
-    if (eflags & EF_HAS_COARSER) {     // B3: restart on even steps, accumulate on odd
-      R* T3 = reinterpret_cast<R*>(p.T3);
-      const size_t o3 = ((size_t)((nn >> 1) & 1) * p.N3 + (size_t)FI[14]) * tstride + (size_t)q * FP;
-      if (valid) {
-        if ((nn & 1) == 0) {
-#pragma unroll
-          for (int i = 0; i < 4; ++i)
-#pragma unroll
-            for (int f = 0; f < FP; ++f) T3[o3 + (size_t)i * LPE * FP + f] = pt[i * FP + f];
-        } else {
-#pragma unroll
-          for (int i = 0; i < 4; ++i)
-#pragma unroll
-            for (int f = 0; f < FP; ++f) T3[o3 + (size_t)i * LPE * FP + f] += pt[i * FP + f];
-        }
-      }
-    }
-    if (need_b2) {                      // B2: half-step integral
-      RF::trace(t2, pt);
-      if (valid && (eflags & EF_HAS_FINER)) {
-        R* T2 = reinterpret_cast<R*>(p.T2);
-        const size_t o2 = ((size_t)(nn & 1) * p.N2 + (size_t)FI[13]) * tstride + (size_t)q * FP;
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-#pragma unroll
-          for (int f = 0; f < FP; ++f) T2[o2 + (size_t)i * LPE * FP + f] = pt[i * FP + f];
-      }
-    }
-  }
-
-  // ------------------------------------------------ volume kernel
-  RF::vol_grad(te, G, grad + q * 3 * B);
-  __syncthreads();
-  if (M > 0) {
-#pragma unroll
-    for (int jb = 0; jb < JB; ++jb) {
-      const int b = q + LPE * jb;
-      if (b < B) {
-        R eps[6];
-        eps[0] = grad[6 * 3 * B + 0 * B + b];
-        eps[1] = grad[7 * 3 * B + 1 * B + b];
-        eps[2] = grad[8 * 3 * B + 2 * B + b];
-        eps[3] = R(0.5) * (grad[6 * 3 * B + 1 * B + b] + grad[7 * 3 * B + 0 * B + b]);
-        eps[4] = R(0.5) * (grad[7 * 3 * B + 2 * B + b] + grad[8 * 3 * B + 1 * B + b]);
-        eps[5] = R(0.5) * (grad[6 * 3 * B + 2 * B + b] + grad[8 * 3 * B + 0 * B + b]);
-#pragma unroll
-        for (int l = 0; l < MM; ++l)
-#pragma unroll
-          for (int c = 0; c < 6; ++c) qa[jb][l][c] -= om[l] * eps[c];
-      }
-    }
-  }
-  if (is_stress) {
-#pragma unroll
-    for (int b = 0; b < B; ++b) {
-      const R eps = R(0.5) * (grad[eA + b] + grad[eB + b]);
-      const R div = grad[d0 + b] + grad[d1 + b] + grad[d2 + b];
-      qe[b] -= lam * delta * div + R(2) * mu * eps;
-    }
-  } else {
-#pragma unroll
-    for (int b = 0; b < B; ++b) qe[b] -= rho_inv * (grad[rA + b] + grad[rB + b] + grad[rC + b]);
-  }
-
-  if (valid) {
-#pragma unroll
-    for (int b = 0; b < B; ++b) Qe[(gbase + b) * NSLOT + slot] = qe[b];
-    if (M > 0)
-#pragma unroll
-      for (int jb = 0; jb < JB; ++jb)
-#pragma unroll
-        for (int l = 0; l < MM; ++l)
-#pragma unroll
-          for (int c = 0; c < 6; ++c) Qa[((((size_t)g * JB + jb) * MM + l) * 6 + c) * NSLOT + slot] = qa[jb][l][c];
-  }
-}
-
 // ---------------------------------------------------------------------------
-// Two-wave variant (O = 4, 5, FP32): a workgroup of two waves owns 7
-// elements.  Lane (e, q) of wave w keeps row q of element e for the modes
-// [MB_w, MB_w+1) only (elementwise state halves, no register spill, two
-// workgroups per SIMD); the reference-matrix products that need a whole row
-// read it from the LDS row exchange RX, and their outputs are split between
-// the waves (stiffness outputs balanced by non-zero count, two faces each for
-// the traces, the wave's own modes for the lift).  The gradient exchange
-// holds only the 18 (row, direction) pairs that are read: all three
-// directions of the velocities, d_i sigma_ij of each stress row.
+// The element update: a workgroup of W waves owns 7 elements.  Lane (e, q) of
+// wave w keeps row q of element e for the modes [mb(w), mb(w + 1)) only
+// (elementwise state is split W ways: no register spill, several workgroups
+// per SIMD); the reference-matrix products that need a whole row read it from
+// the LDS row exchange RX, and their outputs are split between the waves
+// (stiffness and trace outputs balanced by non-zero count, the wave's own
+// modes for the lift).  The gradient exchange holds only the 18 (row,
+// direction) pairs that are read: all three directions of the velocities,
+// d_i sigma_ij of each stress row.
+//
+// W (see launch_level): a group's critical path shortens with more waves and the
+// registers of a wave shrink, while what every wave repeats (parameters,
+// addresses, whole-row reads) grows.
 template <class R, int O, int M>
-struct Lds2 {
+struct LevelLds {
   // Bank-conflict-free strides: with a row stride RS and an element stride
   // ES = 9 RS (mod 32), lane 9e+q addresses bank RS (9e + q) (mod 32), a
   // bijection for odd RS over the 63 working lanes.
@@ -507,7 +105,7 @@ __device__ __forceinline__ int fresh(int v) {
 // The assignment is the one with the fewest LDS bank conflicts (over the
 // stiffness output writes, the strain reads of the memory variables and the
 // star-product reads of a time-kernel step) found by a search over slot
-// permutations for the strides above (one table per layout of Lds2).
+// permutations for the strides above (one table per layout of LevelLds).
 template <int O>
 __device__ __forceinline__ int gslot(int row, int dir) {
   constexpr int T4[9][3] = {{1, 18, 18}, {18, 6, 18}, {18, 18, 13}, {17, 12, 18}, {18, 14, 7},
@@ -525,15 +123,16 @@ __device__ __forceinline__ int gslot(int row, int dir) {
 // of the fused path free of the neighbour-only exit.  TM: the traces of faces
 // 0 and 1 (the two densest) as one dense product on the matrix cores.
 typedef float floatx16 __attribute__((ext_vector_type(16)));
-template <class R, int O, int M, int KIND, bool TM = false>
-__global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(2, 4)))
-void k_level2(KPtrs p, LevelArgs a) {
+template <class R, int O, int M, int KIND, int W, bool TM = false>
+__global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2, 4)))
+void k_level(KPtrs p, LevelArgs a) {
   using RF = edg_gen::Ref<O>;
-  using L = Lds2<R, O, M>;
+  using L = LevelLds<R, O, M>;
   constexpr int B = RF::B, F = RF::F, FP = RF::FP;
   constexpr int MM = M > 0 ? M : 1;
-  constexpr int NB0 = RF::MB1, NB1 = B - RF::MB1;
-  constexpr int NBX = NB0 > NB1 ? NB0 : NB1;
+  constexpr int NBX = RF::template nbx<W>;
+  constexpr int NFW = 4 / W;                     // faces gathered per wave
+  constexpr int NTC = RF::template ntc<W>, NCH = FP / 4;   // trace chunks per wave and per face
   constexpr int JW = (NBX + LPE - 1) / LPE;      // owned memory modes per lane
   constexpr int JB = (B + LPE - 1) / LPE;        // memory-variable layout
   __shared__ R lds[L::TOTAL];
@@ -557,8 +156,16 @@ void k_level2(KPtrs p, LevelArgs a) {
   const int cl = cluster_of(a, g * EPW);        // one cluster per workgroup (uniform)
   const bool valid = (e < EPW) && (elem < a.cl_vend[cl]);
   const int slot = ec * LPE + q;
-  const int base = w ? RF::MB1 : 0;
-  const int nb = w ? NB1 : NB0;
+  const int base = RF::mb(W, w);
+  const int nb = RF::mb(W, w + 1) - base;
+  // the wave has its mode lb / the lane owns memory mode lb = q + 9 jw:
+  // uniform (and decided here) but for the modes only some waves have
+  auto has = [&](int lb) { return lb < RF::template nbn<W> || lb < nb; };
+  auto owns = [&](int jw, int lb) { return LPE * jw + LPE <= RF::template nbn<W> || lb < nb; };
+  // slot of owned mode b = base + q + 9 jw in the memory-variable layout:
+  // lane b mod 9 of the element (the lane itself where waves start at
+  // multiples of nine modes)
+  const int mslot = RF::template nines<W> ? slot : ec * LPE + (base + q) % LPE;
   constexpr int BS = L::BS, FS = L::FS;
   R* const fac = lds + ec * L::FACE;          // face area (surface phase only)
   R* const grad = lds + L::GOFF + ec * L::GSTR;
@@ -579,15 +186,15 @@ void k_level2(KPtrs p, LevelArgs a) {
   // The face records of the wave's two faces (and the face word codes to be
   // staged) are the first loads of the kernel: the neighbour gathers depend
   // on them, and loads complete in issue order.
-  int fnb[2] = {-1, -1}, fcd[2] = {0, 0}, fax[2] = {0, 0};
+  int fnb[NFW], fcd[NFW], fax[NFW];
   int fcode = 0;
   const bool stage = KIND != KIND_PREDICT && w == 0 && q < 4 && e < EPW;
   if constexpr (KIND != KIND_PREDICT) {
 #pragma unroll
-    for (int ii = 0; ii < 2; ++ii) {
-      fnb[ii] = FI[3 * (2 * w + ii)];
-      fcd[ii] = FI[3 * (2 * w + ii) + 1];
-      fax[ii] = FI[3 * (2 * w + ii) + 2];
+    for (int ii = 0; ii < NFW; ++ii) {
+      fnb[ii] = FI[3 * (NFW * w + ii)];
+      fcd[ii] = FI[3 * (NFW * w + ii) + 1];
+      fax[ii] = FI[3 * (NFW * w + ii) + 2];
     }
     if (stage) fcode = FI[3 * q + 1];
   }
@@ -643,7 +250,7 @@ void k_level2(KPtrs p, LevelArgs a) {
   auto load_state = [&]() {
 #pragma unroll
     for (int lb = 0; lb < NBX; ++lb)
-      qe[lb] = lb < nb ? Qg[(base + lb) * NSLOT + slot] : R(0);
+      qe[lb] = has(lb) ? Qg[(base + lb) * NSLOT + slot] : R(0);
 #pragma unroll
     for (int jw = 0; jw < JW; ++jw) {
       const int lb = q + LPE * jw, b = base + lb;
@@ -652,7 +259,7 @@ void k_level2(KPtrs p, LevelArgs a) {
       for (int l = 0; l < MM; ++l)
 #pragma unroll
         for (int c = 0; c < 6; ++c)
-          qa[jw][l][c] = (M > 0 && lb < nb) ? Qag[((jb * MM + l) * 6 + c) * NSLOT + slot] : R(0);
+          qa[jw][l][c] = (M > 0 && owns(jw, lb)) ? Qag[((jb * MM + l) * 6 + c) * NSLOT + mslot] : R(0);
     }
   };
   if constexpr (KIND == KIND_PREDICT) load_state();
@@ -675,11 +282,11 @@ void k_level2(KPtrs p, LevelArgs a) {
     // coarser: its B2 in the first half step, B1 - B2 in the second; none:
     // zeros) and every load of both faces is issued before any is used, so
     // the memory latency is paid once rather than once per source kind.
-    R vown[2][FP], v1[2][FP], v2[2][FP];
-    bool none[2];
+    R vown[NFW][FP], v1[NFW][FP], v2[NFW][FP];
+    bool none[NFW];
 #pragma unroll
-    for (int ii = 0; ii < 2; ++ii) {
-      const int i = 2 * w + ii;
+    for (int ii = 0; ii < NFW; ++ii) {
+      const int i = NFW * w + ii;
       const int nbr = fnb[ii];
       const int code = fcd[ii];
       const size_t aux = (size_t)fax[ii];
@@ -713,8 +320,8 @@ void k_level2(KPtrs p, LevelArgs a) {
       fbc[ec * 4 + q] = fcode;
     }
 #pragma unroll
-    for (int ii = 0; ii < 2; ++ii) {
-      const int i = 2 * w + ii;
+    for (int ii = 0; ii < NFW; ++ii) {
+      const int i = NFW * w + ii;
       R* dmn = fac + ((i * 2 + 0) * LPE + q) * FS;
       R* dpl = fac + ((i * 2 + 1) * LPE + q) * FS;
 #pragma unroll
@@ -729,8 +336,8 @@ void k_level2(KPtrs p, LevelArgs a) {
     load_state();
     __syncthreads();
 #pragma unroll 2
-    for (int rr = 0; rr < (4 * F + 2 * LPE - 1) / (2 * LPE); ++rr) {
-      const int t = q + LPE * (w + 2 * rr);
+    for (int rr = 0; rr < (4 * F + W * LPE - 1) / (W * LPE); ++rr) {
+      const int t = q + LPE * (w + W * rr);
       if (t < 4 * F) {
         const int i = t / F, f = t % F;
         const int bc = (fbc[ec * 4 + i] >> 4) & 15;
@@ -755,7 +362,9 @@ void k_level2(KPtrs p, LevelArgs a) {
       for (int i = 0; i < 4; ++i)
 #pragma unroll
         for (int f = 0; f < FP; ++f) pf[i * FP + f] = fac[((i * 2 + 0) * LPE + q) * FS + f];
-      if (w == 0) RF::lift_p0(pf, qe); else RF::lift_p1(pf, qe);
+      RF::template lift_w<W>(w, pf, da);
+#pragma unroll
+      for (int lb = 0; lb < NBX; ++lb) qe[lb] += da[lb];
       if (M > 0) {
 #pragma unroll
         for (int lb = 0; lb < NBX; ++lb) da[lb] = R(0);
@@ -764,7 +373,7 @@ void k_level2(KPtrs p, LevelArgs a) {
           for (int i = 0; i < 4; ++i)
 #pragma unroll
             for (int f = 0; f < FP; ++f) pf[i * FP + f] = fac[((i * 2 + 1) * LPE + q) * FS + f];
-          if (w == 0) RF::lift_p0(pf, da); else RF::lift_p1(pf, da);
+          RF::template lift_w<W>(w, pf, da);
         }
       }
     }
@@ -773,7 +382,7 @@ void k_level2(KPtrs p, LevelArgs a) {
       if (is_stress && e < EPW)
 #pragma unroll
         for (int lb = 0; lb < NBX; ++lb)
-          if (lb < nb) coup[q * BS + base + lb] = da[lb];
+          if (has(lb)) coup[q * BS + base + lb] = da[lb];
       coup_pending = true;
       // the mode owners below read the coupling rows of their own wave's modes
       wave_lds_sync();
@@ -786,7 +395,7 @@ void k_level2(KPtrs p, LevelArgs a) {
 #pragma unroll
     for (int jw = 0; jw < JW; ++jw) {
       const int lb = q + LPE * jw, b = base + lb;
-      if (lb < nb)
+      if (owns(jw, lb))
 #pragma unroll
         for (int l = 0; l < MM; ++l)
 #pragma unroll
@@ -799,16 +408,16 @@ void k_level2(KPtrs p, LevelArgs a) {
     if (valid) {
 #pragma unroll
       for (int lb = 0; lb < NBX; ++lb)
-        if (lb < nb) Qg[(base + lb) * NSLOT + slot] = qe[lb];
+        if (has(lb)) Qg[(base + lb) * NSLOT + slot] = qe[lb];
       if (M > 0)
 #pragma unroll
         for (int jw = 0; jw < JW; ++jw) {
           const int lb = q + LPE * jw, b = base + lb, jb = b / LPE;
-          if (lb < nb)
+          if (owns(jw, lb))
 #pragma unroll
             for (int l = 0; l < MM; ++l)
 #pragma unroll
-              for (int c = 0; c < 6; ++c) Qag[((jb * MM + l) * 6 + c) * NSLOT + slot] = qa[jw][l][c];
+              for (int c = 0; c < 6; ++c) Qag[((jb * MM + l) * 6 + c) * NSLOT + mslot] = qa[jw][l][c];
         }
     }
     return;
@@ -820,17 +429,17 @@ void k_level2(KPtrs p, LevelArgs a) {
     R* const Re = reinterpret_cast<R*>(a.rec_e) + (size_t)g * B * NSLOT;
 #pragma unroll
     for (int lb = 0; lb < NBX; ++lb)
-      if (lb < nb) Re[(base + lb) * NSLOT + slot] = valid ? qe[lb] : R(0);
+      if (has(lb)) Re[(base + lb) * NSLOT + slot] = valid ? qe[lb] : R(0);
     if (M > 0) {
       R* const Ra = reinterpret_cast<R*>(a.rec_a) + (size_t)g * JB * MM * 6 * NSLOT;
 #pragma unroll
       for (int jw = 0; jw < JW; ++jw) {
         const int lb = q + LPE * jw, b = base + lb, jb = b / LPE;
-        if (lb < nb)
+        if (owns(jw, lb))
 #pragma unroll
           for (int l = 0; l < MM; ++l)
 #pragma unroll
-            for (int c = 0; c < 6; ++c) Ra[((jb * MM + l) * 6 + c) * NSLOT + slot] = valid ? qa[jw][l][c] : R(0);
+            for (int c = 0; c < 6; ++c) Ra[((jb * MM + l) * 6 + c) * NSLOT + mslot] = valid ? qa[jw][l][c] : R(0);
       }
     }
   }
@@ -855,7 +464,7 @@ void k_level2(KPtrs p, LevelArgs a) {
   for (int lb = 0; lb < NBX; ++lb) {
     te[lb] = R(0);
     t2[lb] = R(0);
-    if (lb < nb) rx[q * BS + base + lb] = qe[lb];
+    if (has(lb)) rx[q * BS + base + lb] = qe[lb];
   }
 #pragma unroll
   for (int jw = 0; jw < JW; ++jw)
@@ -872,7 +481,7 @@ void k_level2(KPtrs p, LevelArgs a) {
     {
       R dv[NBX];
 #pragma unroll
-      for (int lb = 0; lb < NBX; ++lb) dv[lb] = lb < nb ? rx[q * BS + base + lb] : R(0);
+      for (int lb = 0; lb < NBX; ++lb) dv[lb] = has(lb) ? rx[q * BS + base + lb] : R(0);
 #pragma unroll
       for (int lb = 0; lb < NBX; ++lb) te[lb] += c_d * dv[lb];
       if (need_b2)
@@ -882,22 +491,21 @@ void k_level2(KPtrs p, LevelArgs a) {
         R* rd = reinterpret_cast<R*>(p.recD) + (((size_t)rec_slot * O + d) * LPE + q) * B + base;
 #pragma unroll
         for (int lb = 0; lb < NBX; ++lb)
-          if (lb < nb) rd[lb] = dv[lb];
+          if (has(lb)) rd[lb] = dv[lb];
       }
     }
     if (more) {
       R full[B];
 #pragma unroll
       for (int b = 0; b < B; ++b) full[b] = rx[q * BS + b];
-      if (w == 0) RF::ck_grad_p0(full, G, gw0, gw1, gw2);
-      else RF::ck_grad_p1(full, G, gw0, gw1, gw2);
+      RF::template ck_grad_w<W>(w, full, G, gw0, gw1, gw2);
     }
     __syncthreads();
     if (M > 0) {
 #pragma unroll
       for (int jw = 0; jw < JW; ++jw) {
         const int lb = q + LPE * jw, b = base + lb;
-        if (lb < nb) {
+        if (owns(jw, lb)) {
           R eps[6];
           if (more) {
             eps[0] = grad[gslot<O>(6, 0) * BS + b];
@@ -939,7 +547,7 @@ void k_level2(KPtrs p, LevelArgs a) {
       for (int k = 0; k < CH; ++k) {
         const int lb = l0 + k, b = base + lb;
         nx[k] = R(0);
-        if (lb < NBX && lb < nb) {
+        if (lb < NBX && has(lb)) {
           const R cq = M > 0 ? wc * coup[cs + b] : R(0);
           if (M > 0) qe[lb] += c_d * cq;
           nx[k] = wabc * (grad[sa + b] + grad[sb + b] + grad[sc + b]) + wde * (grad[sd + b] + grad[se + b]) + cq;
@@ -948,13 +556,18 @@ void k_level2(KPtrs p, LevelArgs a) {
       if (more)
 #pragma unroll
         for (int k = 0; k < CH; ++k)
-          if (l0 + k < NBX && l0 + k < nb) rx[q * BS + base + l0 + k] = nx[k];
+          if (l0 + k < NBX && has(l0 + k)) rx[q * BS + base + l0 + k] = nx[k];
     }
   }
   // (the barrier after the last loop's products orders every read of RX
   // before the time integral is written there)
 
   // ------------------------------------------------ traces and volume
+  // word offset of this wave's trace chunk ii in an element's trace (-1: none)
+  auto chunk_off = [&](int ii) {
+    const int c = RF::template tchunk<W>(w, ii);
+    return ii >= RF::template ntn<W> && c < 0 ? -1 : (c / NCH) * LPE * FP + 4 * (c % NCH);
+  };
   // (the matrix-core trace's coefficients are requested before the barrier,
   // so their latency overlaps it)
   float ftb[TM ? RF::MK : 1];
@@ -963,35 +576,38 @@ void k_level2(KPtrs p, LevelArgs a) {
     for (int st = 0; st < RF::MK; ++st) ftb[st] = RF::FT01[st * 64 + lane];
 #pragma unroll
   for (int lb = 0; lb < NBX; ++lb)
-    if (lb < nb) rx[q * BS + base + lb] = te[lb];
+    if (has(lb)) rx[q * BS + base + lb] = te[lb];
   __syncthreads();
   {
     R full[B];
 #pragma unroll
     for (int b = 0; b < B; ++b) full[b] = rx[q * BS + b];
     if constexpr (!TM) {
-    R pt[2 * FP];
-    if (w == 0) RF::trace_p0(full, pt); else RF::trace_p1(full, pt);
+    R pt[4 * NTC];
+    RF::template trace_w<W>(w, full, pt);
     const int own = fresh(ec * TS + q * FP);
     if (valid) {
       R* T1 = reinterpret_cast<R*>(p.T1) + (size_t)(nn & 1) * Kp * tstride + tg;
 #pragma unroll
-      for (int ii = 0; ii < 2; ++ii)
+      for (int ii = 0; ii < NTC; ++ii)
+        if (const int o = chunk_off(ii); ii < RF::template ntn<W> || o >= 0)
 #pragma unroll
-        for (int f = 0; f < FP; ++f) T1[own + RF::tface(w, ii) * LPE * FP + f] = pt[ii * FP + f];
+          for (int k = 0; k < 4; ++k) T1[own + o + k] = pt[4 * ii + k];
     }
     if ((eflags & EF_HAS_COARSER) && valid) {
       R* T3 = reinterpret_cast<R*>(p.T3) + ((size_t)((nn >> 1) & 1) * p.N3 + (size_t)FI[14]) * tstride;
       if ((nn & 1) == 0) {
 #pragma unroll
-        for (int ii = 0; ii < 2; ++ii)
+        for (int ii = 0; ii < NTC; ++ii)
+          if (const int o = chunk_off(ii); ii < RF::template ntn<W> || o >= 0)
 #pragma unroll
-          for (int f = 0; f < FP; ++f) T3[q * FP + RF::tface(w, ii) * LPE * FP + f] = pt[ii * FP + f];
+            for (int k = 0; k < 4; ++k) T3[q * FP + o + k] = pt[4 * ii + k];
       } else {
 #pragma unroll
-        for (int ii = 0; ii < 2; ++ii)
+        for (int ii = 0; ii < NTC; ++ii)
+          if (const int o = chunk_off(ii); ii < RF::template ntn<W> || o >= 0)
 #pragma unroll
-          for (int f = 0; f < FP; ++f) T3[q * FP + RF::tface(w, ii) * LPE * FP + f] += pt[ii * FP + f];
+            for (int k = 0; k < 4; ++k) T3[q * FP + o + k] += pt[4 * ii + k];
       }
     }
     } else {
@@ -999,7 +615,7 @@ void k_level2(KPtrs p, LevelArgs a) {
       // [32 w, 32 w + 32) (row 9 e + q of the exchange; row 63 is padding) by
       // the two faces' trace coefficients, 32 columns (face, face mode), two
       // modes per step; its sparse face (3, or 2) stays on the vector ALUs
-      static_assert(sizeof(R) == 4 && FP <= 16, "matrix-core trace: FP32, at most 16 face modes");
+      static_assert(W == 2 && sizeof(R) == 4 && FP <= 16, "matrix-core trace: FP32, at most 16 face modes");
       floatx16 acc;
 #pragma unroll
       for (int j = 0; j < 16; ++j) acc[j] = 0.f;
@@ -1048,15 +664,14 @@ void k_level2(KPtrs p, LevelArgs a) {
           }
         }
     }
-    if (w == 0) RF::vol_grad_p0(full, G, gw0, gw1, gw2);
-    else RF::vol_grad_p1(full, G, gw0, gw1, gw2);
+    RF::template vol_grad_w<W>(w, full, G, gw0, gw1, gw2);
   }
   __syncthreads();
   if (M > 0) {
 #pragma unroll
     for (int jw = 0; jw < JW; ++jw) {
       const int lb = q + LPE * jw, b = base + lb;
-      if (lb < nb) {
+      if (owns(jw, lb)) {
         R eps[6];
         eps[0] = grad[gslot<O>(6, 0) * BS + b];
         eps[1] = grad[gslot<O>(7, 1) * BS + b];
@@ -1074,43 +689,45 @@ void k_level2(KPtrs p, LevelArgs a) {
 #pragma unroll
   for (int lb = 0; lb < NBX; ++lb) {
     const int b = base + lb;
-    if (lb < nb)
+    if (has(lb))
       qe[lb] -= wabc * (grad[sa + b] + grad[sb + b] + grad[sc + b]) + wde * (grad[sd + b] + grad[se + b]);
   }
   if (need_b2) {   // B2 traces from the half-step integral (RX is free again)
 #pragma unroll
     for (int lb = 0; lb < NBX; ++lb)
-      if (lb < nb) rx[q * BS + base + lb] = t2[lb];
+      if (has(lb)) rx[q * BS + base + lb] = t2[lb];
     __syncthreads();
     R full[B];
 #pragma unroll
     for (int b = 0; b < B; ++b) full[b] = rx[q * BS + b];
-    R pt[2 * FP];
-    if (w == 0) RF::trace_p0(full, pt); else RF::trace_p1(full, pt);
+    R pt[4 * NTC];
+    RF::template trace_w<W>(w, full, pt);
     if (valid && (eflags & EF_HAS_FINER)) {
       R* T2 = reinterpret_cast<R*>(p.T2) + ((size_t)(nn & 1) * p.N2 + (size_t)FI[13]) * tstride;
       const int own = fresh(q * FP);
 #pragma unroll
-      for (int ii = 0; ii < 2; ++ii)
+      for (int ii = 0; ii < NTC; ++ii)
+        if (const int o = chunk_off(ii); ii < RF::template ntn<W> || o >= 0)
 #pragma unroll
-        for (int f = 0; f < FP; ++f) T2[own + RF::tface(w, ii) * LPE * FP + f] = pt[ii * FP + f];
+          for (int k = 0; k < 4; ++k) T2[own + o + k] = pt[4 * ii + k];
     }
   }
 
   if (valid) {
     const int sl = fresh(slot);
+    const int msl = RF::template nines<W> ? sl : fresh(mslot);
 #pragma unroll
     for (int lb = 0; lb < NBX; ++lb)
-      if (lb < nb) Qg[(base + lb) * NSLOT + sl] = qe[lb];
+      if (has(lb)) Qg[(base + lb) * NSLOT + sl] = qe[lb];
     if (M > 0)
 #pragma unroll
       for (int jw = 0; jw < JW; ++jw) {
         const int lb = q + LPE * jw, b = base + lb, jb = b / LPE;
-        if (lb < nb)
+        if (owns(jw, lb))
 #pragma unroll
           for (int l = 0; l < MM; ++l)
 #pragma unroll
-            for (int c = 0; c < 6; ++c) Qag[((jb * MM + l) * 6 + c) * NSLOT + sl] = qa[jw][l][c];
+            for (int c = 0; c < 6; ++c) Qag[((jb * MM + l) * 6 + c) * NSLOT + msl] = qa[jw][l][c];
       }
   }
 }
@@ -1221,24 +838,50 @@ int launch_zero_words(void* p, size_t words, hipStream_t st) {
   return (int)hipGetLastError();
 }
 
+// Waves per workgroup, measured in us per LTS cycle of three clusters (one
+// wave was the form before, two at FP32 O >= 4):
+//   O = 5  four: FP32 m=3 2k / 41k / 300k / 997k tets 115 / 553 / 2,924 /
+//          9,628 against 144 / 613 / 3,038 / 9,860 with two; m=0 300k 1,954
+//          against 2,216.  FP64 m=3 2k / 41k 238 / 1,872 against 245 / 1,733
+//          (one wave, spilling 2.4 KB a lane: 1,010 / 9,471), m=0 41k 921
+//          against 1,216
+//   O = 4  four while the launch is small or elastic: FP32 m=3 2k / 41k / 300k
+//          85 / 374 / 2,053 against 100 / 404 / 2,012, m=0 300k 1,265 against
+//          1,284; FP64 m=3 41k 750 against 1,078 (one: 2,322)
+//   O <= 3 two: FP32 m=3 300k O=3 1,050 against 1,313 (one: 3,212), O=2 605
+//          against 891 (one: 1,094); FP64 O=3 m=3 41k 410 against 508 (783)
+// Every split gives the same bits (no contraction across expressions), so the
+// choice may follow the size of the launch.
+constexpr long long W4_MAX_GROUPS_O4 = 16384;
+
+template <class R, int O, int M, int W, bool TM = false>
+static void launch_kind(const LevelArgs& a, dim3 grid, const KPtrs& p, hipStream_t st) {
+  if (a.kind == KIND_FUSED)
+    hipLaunchKernelGGL((k_level<R, O, M, KIND_FUSED, W, TM>), grid, dim3(64 * W), 0, st, p, a);
+  else if (a.kind == KIND_PREDICT)
+    hipLaunchKernelGGL((k_level<R, O, M, KIND_PREDICT, W, TM>), grid, dim3(64 * W), 0, st, p, a);
+  else
+    hipLaunchKernelGGL((k_level<R, O, M, KIND_NEIGHBOR, W>), grid, dim3(64 * W), 0, st, p, a);
+}
+
 template <class R, int O, int M>
 int launch_level(const KPtrs& p, const LevelArgs& a, int runs, hipStream_t st) {
   const int groups = (a.end + EPW - 1) / EPW;
   if (groups <= 0 || runs <= 0) return 0;
   const dim3 grid(groups, runs);
   if constexpr (std::is_same<R, float>::value && O >= 4) {
-    if (a.kind == KIND_FUSED && a.trace_mfma)
-      hipLaunchKernelGGL((k_level2<R, O, M, KIND_FUSED, true>), grid, dim3(128), 0, st, p, a);
-    else if (a.kind == KIND_PREDICT && a.trace_mfma)
-      hipLaunchKernelGGL((k_level2<R, O, M, KIND_PREDICT, true>), grid, dim3(128), 0, st, p, a);
-    else if (a.kind == KIND_FUSED)
-      hipLaunchKernelGGL((k_level2<R, O, M, KIND_FUSED>), grid, dim3(128), 0, st, p, a);
-    else if (a.kind == KIND_PREDICT)
-      hipLaunchKernelGGL((k_level2<R, O, M, KIND_PREDICT>), grid, dim3(128), 0, st, p, a);
-    else
-      hipLaunchKernelGGL((k_level2<R, O, M, KIND_NEIGHBOR>), grid, dim3(128), 0, st, p, a);
-  } else
-    hipLaunchKernelGGL((k_level<R, O, M>), grid, dim3(64), 0, st, p, a);
+    if (a.trace_mfma) {
+      launch_kind<R, O, M, 2, true>(a, grid, p, st);
+      return (int)hipGetLastError();
+    }
+  }
+  if constexpr (O == 4 && M > 0 && std::is_same<R, float>::value) {
+    if ((long long)groups * runs > W4_MAX_GROUPS_O4) {
+      launch_kind<R, O, M, 2>(a, grid, p, st);
+      return (int)hipGetLastError();
+    }
+  }
+  launch_kind<R, O, M, O >= 4 ? 4 : 2>(a, grid, p, st);
   return (int)hipGetLastError();
 }
 
