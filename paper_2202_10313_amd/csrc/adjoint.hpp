@@ -5,9 +5,11 @@
 namespace edg {
 
 // ---- discrete adjoint (one run)
-constexpr int KIND_ADJ_PREDICT = 3;  // transpose of a step's prediction (+ volume, own surface part)
-constexpr int KIND_ADJ_UPDATE = 4;   // transpose of the neighbour-data part of a step's surface update
-constexpr int ADJ_ROWS = 15;         // adjoint face rows: 9 elastic + 6 omega-weighted memory-variable sums
+constexpr int KIND_ADJ_PREDICT = 3;  // transposed predictions only (start of a segment)
+constexpr int KIND_ADJ_UPDATE = 4;   // transposed surface updates only (end of a segment)
+constexpr int KIND_ADJ_FUSED = 5;    // transposed predictions, then transposed updates, of the same elements
+// adjoint face rows: 9 elastic + 6 omega-weighted memory-variable sums (anelastic only)
+constexpr int adj_rows(int M) { return M > 0 ? 15 : 9; }
 // Per-element gradient words (internal order, FP64): derivatives of the
 // adjoint pairing in the parameters the kernels read.
 //   [0] 1/rho  [1] lam  [2] mu  [3] Zp  [4] Zs  [5+2l] a_l  [6+2l] b_l
@@ -21,12 +23,9 @@ struct APtrs {
   void* La;          // adjoint of the memory variables (Qa layout)
   const void* Se;    // forward state at the start of the step (Qe layout)
   const void* Sa;    // (Qa layout)
-  void* S0;          // [Kp][4][15][FP] face adjoints of the element's own flux (its last finished step)
-  void* S1;          // [Kp][4][15][FP] adjoint face data for the element's B1 (per own face)
-  void* S2;          // [N2][4][15][FP] for B2
-  void* S3;          // [N3][4][15][FP] for B3
-  void* De;          // scratch: adjoint_scratch_floats() words per element group
-  void* Da;          // scratch: [G][O][JB][m][6][63]
+  void* S0;          // [2][Kp][4][adj_rows][FP] face adjoints of each element's last steps (step parity)
+  void* S3;          // [4][N3][4][adj_rows][FP] the same of the elements with a coarser neighbour (step mod 4)
+  void* De;          // scratch: adjoint_scratch_words() words per element group
   double* gacc;      // [Kp][NG]
   void* recDb;       // [slots][O][9][B] adjoint of the receiver derivatives
 };
@@ -38,9 +37,9 @@ int launch_material_gradient(const double* gacc, const int* FI, const double* ma
 
 template <class R, int O, int M>
 int launch_adjoint(const KPtrs& p, const APtrs& ad, const LevelArgs& a, hipStream_t st);
-// words of De per element group for the transposed prediction of this variant
+// words of De per element group of this variant
 template <class R, int O, int M>
-size_t adjoint_scratch_floats();
+size_t adjoint_scratch_words();
 template <class R, int O, int M>
 int launch_receivers_adj(const KPtrs& p, const APtrs& ad, const LevelArgs& a, const RecArgs& r, const double* seis_b,
                          hipStream_t st);

@@ -113,8 +113,8 @@ struct edg_ctx {
   // hist_J levels, the state at the start of every level's predictions (the
   // final segment of a checkpointed advance records it; a replay rewrites it)
   bool hist_valid = false;
-  // the adjoint face slots and receiver derivatives hold zeros (left so by a
-  // completed reverse sweep: each is cleared by its reader)
+  // the receiver derivatives' adjoint holds zeros (left so by a completed
+  // reverse sweep: each is cleared by its reader)
   bool adj_clean = false;
   bool amat_valid = false;           // amat holds the materials of the current upload, internal order
   // materials uploaded from device memory: a device copy in caller order
@@ -128,7 +128,7 @@ struct edg_ctx {
   int64_t hist_L0 = 0, hist_J = 0;
   int hist_run = 0;                  // the run whose level states ahist holds
   // adjoint buffers
-  DevBuf aLe, aLa, aS0, aS1, aS2, aS3, aDe, aDa, agacc, arecDb, aseis, ahist, afinal, amat, agrad;
+  DevBuf aLe, aLa, aS0, aS3, aDe, agacc, arecDb, aseis, ahist, afinal, amat, agrad;
 
   bool timing = false;
   std::vector<std::pair<hipEvent_t, hipEvent_t>> ev_pool;
@@ -863,7 +863,7 @@ int launch_timed(edg_ctx* c, const Fns& fn, const KPtrs& p, const LevelArgs& a, 
 
 edg_ctx::~edg_ctx() {
   for (DevBuf* b : {&Qe, &Qa, &P, &FI, &T1, &T2, &T3, &RecD, &s_run, &s_elem, &s_kind, &s_par, &s_mom, &s_phi,
-                    &s_idet, &r_elem, &r_slot, &r_phi, &r_out, &dclock, &aLe, &aLa, &aS0, &aS1, &aS2, &aS3, &aDe, &aDa,
+                    &s_idet, &r_elem, &r_slot, &r_phi, &r_out, &dclock, &aLe, &aLa, &aS0, &aS3, &aDe,
                     &agacc, &arecDb, &aseis, &ahist, &afinal, &amat, &agrad, &dmat, &dflag, &d_i2u, &d_nbr, &dbg, &d_u2i, &d_code, &d_mats, &dofstage})
     dev_free(*b);
   for (auto& ck : ckpts) dev_free(ck.second);
@@ -1842,11 +1842,9 @@ namespace {
 template <class R, int O, int M>
 int adjoint_sweep(edg_ctx* c, const double* dj_seis, const double* dj_q, double* g_q0, double* g_rho, double* g_vp,
                   double* g_vs, bool dev) {
-  const int Nc = c->cfg.n_clusters, FP = c->FP, JB = jb_count(c);
+  const int Nc = c->cfg.n_clusters, FP = c->FP;
   const size_t rs = sizeof(R), we = c->run_qe, wa = c->run_qa;
-  const size_t slot_words = (size_t)4 * ADJ_ROWS * FP;
-  // Da is the one-wave kernel's (the two-wave kernel keeps its scratch in De)
-  const bool two_wave = std::is_same<R, float>::value && O >= 4;
+  const size_t slot_words = (size_t)4 * adj_rows(M) * FP;
   const int64_t L_end = c->level;
   const size_t nck = c->ckpts.size();
   int64_t jmax = 1;
@@ -1856,31 +1854,25 @@ int adjoint_sweep(edg_ctx* c, const double* dj_seis, const double* dj_q, double*
   }
   int rc;
   const size_t n_hist = (size_t)jmax;   // levels 0 .. J-1 of the longest segment
-  const void* const slots_before[5] = {c->aS0.p, c->aS1.p, c->aS2.p, c->aS3.p, c->arecDb.p};
+  const void* const rec_before = c->arecDb.p;
   if ((rc = dev_reserve(c, c->aLe, we * rs)) || (rc = dev_reserve(c, c->aLa, std::max<size_t>(wa, 1) * rs)) ||
-      (rc = dev_reserve(c, c->aS0, (size_t)c->Kp * slot_words * rs)) ||
-      (rc = dev_reserve(c, c->aS1, (size_t)c->Kp * slot_words * rs)) ||
-      (rc = dev_reserve(c, c->aS2, (size_t)c->N2 * slot_words * rs)) ||
-      (rc = dev_reserve(c, c->aS3, (size_t)c->N3 * slot_words * rs)) ||
-      (rc = dev_reserve(c, c->aDe, (size_t)c->G * adjoint_scratch_floats<R, O, M>() * rs)) ||
-      (rc = dev_reserve(c, c->aDa, std::max<size_t>(two_wave ? 0 : (size_t)c->G * O * JB * M * 6 * EPW * LPE, 1) * rs)) ||
+      (rc = dev_reserve(c, c->aS0, 2 * (size_t)c->Kp * slot_words * rs)) ||
+      (rc = dev_reserve(c, c->aS3, 4 * (size_t)c->N3 * slot_words * rs)) ||
+      (rc = dev_reserve(c, c->aDe, (size_t)c->G * adjoint_scratch_words<R, O, M>() * rs)) ||
       (rc = dev_reserve(c, c->agacc, (size_t)c->Kp * NG * sizeof(double))) ||
       (rc = dev_reserve(c, c->arecDb, std::max<size_t>(c->run_recd, 1) * rs)) ||
       (rc = dev_reserve(c, c->aseis, std::max<size_t>((size_t)c->n_rec * c->rec_ns * LPE, 1) * sizeof(double))) ||
       (rc = hist_reserve(c, (int64_t)n_hist)) || (rc = dev_reserve(c, c->afinal, (we + wa) * rs)))
     return rc;
-  // the slots and receiver derivatives return to zero at the end of every
-  // sweep (each is cleared by its reader; S0 is written before it is read);
-  // they are cleared here after a (re)allocation and after a failed sweep
-  const void* const slots_now[5] = {c->aS0.p, c->aS1.p, c->aS2.p, c->aS3.p, c->arecDb.p};
-  bool clean = c->adj_clean;
-  for (int i = 0; i < 5; ++i) clean = clean && slots_before[i] == slots_now[i];
+  // the face slots are written before they are read in every sweep; the
+  // receiver derivatives return to zero at the end of a sweep (each is cleared
+  // by its reader) and are cleared here after a (re)allocation and after a
+  // failed sweep
+  const bool clean = c->adj_clean && rec_before == c->arecDb.p;
   c->adj_clean = false;
   // the gradient words sum over the runs: J is the sum of the runs' misfits
   HIPCHK(c, hipMemsetAsync(c->agacc.p, 0, c->agacc.bytes, c->stream));
-  if (!clean)
-    for (DevBuf* b : {&c->aS0, &c->aS1, &c->aS2, &c->aS3, &c->arecDb})
-      HIPCHK(c, hipMemsetAsync(b->p, 0, b->bytes, c->stream));
+  if (!clean) HIPCHK(c, hipMemsetAsync(c->arecDb.p, 0, c->arecDb.bytes, c->stream));
   HIPCHK(c, hipStreamSynchronize(c->stream));
   // the replays run on a state of their own, so the context's DOFs stay
   // those of the final time; one run at a time, so the run stride of the
@@ -1896,11 +1888,8 @@ int adjoint_sweep(edg_ctx* c, const double* dj_seis, const double* dj_q, double*
   ad.Le = c->aLe.p;
   ad.La = c->aLa.p;
   ad.S0 = c->aS0.p;
-  ad.S1 = c->aS1.p;
-  ad.S2 = c->aS2.p;
   ad.S3 = c->aS3.p;
   ad.De = c->aDe.p;
-  ad.Da = c->aDa.p;
   ad.gacc = (double*)c->agacc.p;
   ad.recDb = c->arecDb.p;
   const double* seis_b = (const double*)c->aseis.p;
@@ -1909,27 +1898,24 @@ int adjoint_sweep(edg_ctx* c, const double* dj_seis, const double* dj_q, double*
   auto chk = [&](int e, const char* what) {
     return e ? fail(c, EDG_EHIP, std::string(what) + ": " + hipGetErrorString((hipError_t)e)) : 0;
   };
-  // the levels of a segment backwards: transposed predictions, then
-  // transposed updates (kernel launches only)
+  // the levels of a segment backwards: at each the transposed predictions and
+  // the transposed updates of the same elements, one launch (kernel launches
+  // only)
   auto backward = [&](LevelArgs a, int64_t J) {
     int e;
     for (int64_t j = J; j >= 0; --j) {
       const int lmax = (j == 0 || j == J) ? Nc - 1 : level_lmax(c, j);
       a.jrel = (int)j;
       a.end = c->cl_end[lmax];
+      a.kind = j == J ? KIND_ADJ_UPDATE : j > 0 ? KIND_ADJ_FUSED : KIND_ADJ_PREDICT;
       if (j < J) {
         if (c->n_rec > 0 && dj_seis &&
             (e = chk(launch_receivers_adj<R, O, M>(p, ad, a, A0.ra, seis_b, c->stream), "receiver adjoint kernel")))
           return e;
         ad.Se = hist_e(j);
         ad.Sa = hist_a(j);
-        a.kind = KIND_ADJ_PREDICT;
-        if ((e = chk(launch_adjoint<R, O, M>(p, ad, a, c->stream), "adjoint kernel"))) return e;
       }
-      if (j > 0) {
-        a.kind = KIND_ADJ_UPDATE;
-        if ((e = chk(launch_adjoint<R, O, M>(p, ad, a, c->stream), "adjoint kernel"))) return e;
-      }
+      if ((e = chk(launch_adjoint<R, O, M>(p, ad, a, c->stream), "adjoint kernel"))) return e;
     }
     return 0;
   };

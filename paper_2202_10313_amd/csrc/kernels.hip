@@ -124,7 +124,7 @@ __device__ __forceinline__ int gslot(int row, int dir) {
 // 0 and 1 (the two densest) as one dense product on the matrix cores.
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 template <class R, int O, int M, int KIND, int W, bool TM = false>
-__global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2, 4)))
+__global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(sizeof(R) == 8 && O >= 4 ? 1 : 2, 4)))
 void k_level(KPtrs p, LevelArgs a) {
   using RF = edg_gen::Ref<O>;
   using L = LevelLds<R, O, M>;
