@@ -38,14 +38,13 @@ __device__ __forceinline__ int cluster_of(const LevelArgs& a, int elem) {
   return c;
 }
 
-// Godunov flux of one face mode: qm / qp are the 9 elastic trace coefficients
-// of this element and of the outside state; writes s * (A_n q*) for the 9
-// elastic rows and s * (strain-rate flux) for the 6 memory-variable rows
-// (unscaled by omega), where s = 2|S_i| / |det J| (the surface kernel's
-// -(1/|det J|) int_face phi ... with the sign folded in).
+// Godunov state of one face mode: qm / qp are the 9 elastic trace coefficients
+// of this element and of the outside state, ip = 1 / (zpm + zpp) and is = 1 /
+// (zsm + zsp); writes the velocity v (and in v[3] its normal component) and the traction t
+// of the solved state.
 template <class R>
-__host__ __device__ __forceinline__ void godunov(const R* qm, const R* qp, R nx, R ny, R nz, R zpm, R zsm, R zpp, R zsp,
-                                        R lam, R mu, R rho_inv, R s, int bc, R* out) {
+__host__ __device__ __forceinline__ void godunov_state(const R* qm, const R* qp, R nx, R ny, R nz, R zpm, R zsm, R zpp,
+                                                       R zsp, R ip, R is, int bc, R* v, R* t) {
   // tractions sigma n and velocities
   const R tmx = qm[0] * nx + qm[3] * ny + qm[5] * nz;
   const R tmy = qm[3] * nx + qm[1] * ny + qm[4] * nz;
@@ -66,7 +65,6 @@ __host__ __device__ __forceinline__ void godunov(const R* qm, const R* qp, R nx,
   }
   const R tnm = tmx * nx + tmy * ny + tmz * nz, vnm = vmx * nx + vmy * ny + vmz * nz;
   const R tnp = tpx * nx + tpy * ny + tpz * nz, vnp = vpx * nx + vpy * ny + vpz * nz;
-  const R ip = R(1) / (zpm + zpp), is = R(1) / (zsm + zsp);
   const R vn = (zpm * vnm + zpp * vnp + tnp - tnm) * ip;
   const R tn = (zpp * tnm + zpm * tnp + zpm * zpp * (vnp - vnm)) * ip;
   // tangential parts
@@ -75,34 +73,59 @@ __host__ __device__ __forceinline__ void godunov(const R* qm, const R* qp, R nx,
   const R tTpx = tpx - tnp * nx, tTpy = tpy - tnp * ny, tTpz = tpz - tnp * nz;
   const R vTpx = vpx - vnp * nx, vTpy = vpy - vnp * ny, vTpz = vpz - vnp * nz;
   const R zz = zsm * zsp;
-  const R vx = vn * nx + (zsm * vTmx + zsp * vTpx + tTpx - tTmx) * is;
-  const R vy = vn * ny + (zsm * vTmy + zsp * vTpy + tTpy - tTmy) * is;
-  const R vz = vn * nz + (zsm * vTmz + zsp * vTpz + tTpz - tTmz) * is;
-  const R tx = tn * nx + (zsp * tTmx + zsm * tTpx + zz * (vTpx - vTmx)) * is;
-  const R ty = tn * ny + (zsp * tTmy + zsm * tTpy + zz * (vTpy - vTmy)) * is;
-  const R tz = tn * nz + (zsp * tTmz + zsm * tTpz + zz * (vTpz - vTmz)) * is;
-  // flux A_n q*: stresses -(lam (v.n) I + mu (n v^T + v n^T)), velocities -t/rho;
-  // multiplied by -s for the surface term: +s (...)
-  const R lvn = lam * vn;
-  const R ms = mu * s;
-  out[0] = s * lvn + R(2) * ms * nx * vx;
-  out[1] = s * lvn + R(2) * ms * ny * vy;
-  out[2] = s * lvn + R(2) * ms * nz * vz;
-  out[3] = ms * (nx * vy + ny * vx);
-  out[4] = ms * (ny * vz + nz * vy);
-  out[5] = ms * (nx * vz + nz * vx);
-  const R sr = s * rho_inv;
-  out[6] = sr * tx;
-  out[7] = sr * ty;
-  out[8] = sr * tz;
-  // memory-variable rows: -(1/2)(n v^T + v n^T), times -s
+  v[0] = vn * nx + (zsm * vTmx + zsp * vTpx + tTpx - tTmx) * is;
+  v[1] = vn * ny + (zsm * vTmy + zsp * vTpy + tTpy - tTmy) * is;
+  v[2] = vn * nz + (zsm * vTmz + zsp * vTpz + tTpz - tTmz) * is;
+  t[0] = tn * nx + (zsp * tTmx + zsm * tTpx + zz * (vTpx - vTmx)) * is;
+  t[1] = tn * ny + (zsp * tTmy + zsm * tTpy + zz * (vTpy - vTmy)) * is;
+  t[2] = tn * nz + (zsp * tTmz + zsm * tTpz + zz * (vTpz - vTmz)) * is;
+  v[3] = vn;
+}
+
+// Surface rows of a solved state (v, t), with s = 2|S_i| / |det J| (the surface
+// kernel's -(1/|det J|) int_face phi ... with the sign folded in): the six
+// strain-rate rows s sym(n v), which the memory variables take (times omega)
+// and whose stress is lam tr I + 2 mu times them ...
+template <class R>
+__host__ __device__ __forceinline__ void flux_strain(const R* v, R nx, R ny, R nz, R s, R* out) {
   const R hs = R(0.5) * s;
-  out[9] = s * nx * vx;
-  out[10] = s * ny * vy;
-  out[11] = s * nz * vz;
-  out[12] = hs * (nx * vy + ny * vx);
-  out[13] = hs * (ny * vz + nz * vy);
-  out[14] = hs * (nx * vz + nz * vx);
+  out[0] = s * nx * v[0];
+  out[1] = s * ny * v[1];
+  out[2] = s * nz * v[2];
+  out[3] = hs * (nx * v[1] + ny * v[0]);
+  out[4] = hs * (ny * v[2] + nz * v[1]);
+  out[5] = hs * (nx * v[2] + nz * v[0]);
+}
+// ... the six stress rows ...
+template <class R>
+__host__ __device__ __forceinline__ void flux_stress(const R* v, R nx, R ny, R nz, R lam, R mu, R s, R* out) {
+  const R lvn = lam * v[3];
+  const R ms = mu * s;
+  out[0] = s * lvn + R(2) * ms * nx * v[0];
+  out[1] = s * lvn + R(2) * ms * ny * v[1];
+  out[2] = s * lvn + R(2) * ms * nz * v[2];
+  out[3] = ms * (nx * v[1] + ny * v[0]);
+  out[4] = ms * (ny * v[2] + nz * v[1]);
+  out[5] = ms * (nx * v[2] + nz * v[0]);
+}
+// ... and the three velocity rows.
+template <class R>
+__host__ __device__ __forceinline__ void flux_velocity(const R* t, R rho_inv, R s, R* out) {
+  const R sr = s * rho_inv;
+  out[0] = sr * t[0];
+  out[1] = sr * t[1];
+  out[2] = sr * t[2];
+}
+
+// The whole flux: 9 elastic rows, then the 6 strain-rate rows (unscaled by omega).
+template <class R>
+__host__ __device__ __forceinline__ void godunov(const R* qm, const R* qp, R nx, R ny, R nz, R zpm, R zsm, R zpp, R zsp,
+                                                 R lam, R mu, R rho_inv, R s, int bc, R* out) {
+  R v[4], t[3];
+  godunov_state<R>(qm, qp, nx, ny, nz, zpm, zsm, zpp, zsp, R(1) / (zpm + zpp), R(1) / (zsm + zsp), bc, v, t);
+  flux_stress<R>(v, nx, ny, nz, lam, mu, s, out);
+  flux_velocity<R>(t, rho_inv, s, out + 6);
+  flux_strain<R>(v, nx, ny, nz, s, out + 9);
 }
 
 // Orders the LDS accesses of one wave: every lane's LDS stores before it are

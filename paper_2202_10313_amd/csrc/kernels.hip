@@ -57,9 +57,17 @@ namespace {
 // direction) pairs that are read: all three directions of the velocities,
 // d_i sigma_ij of each stress row.
 //
-// W (see launch_level): a group's critical path shortens with more waves and the
+// W (see LEVEL_W): a group's critical path shortens with more waves and the
 // registers of a wave shrink, while what every wave repeats (parameters,
 // addresses, whole-row reads) grows.
+//
+// What bounds it (O = 5, m = 3, FP32, 62k tets): latency at three waves per
+// SIMD (168 registers; 128 spill: 4,493 us per cycle at 300k against 2,881).
+// Of a wave's cycles vector issue takes 22% (66% of the SIMD's), LDS about 56%
+// of its unit's, 43% wait on LDS, memory or barriers; 3.1-3.4 TB/s of memory
+// traffic.  Fewer instructions alone (3,300 -> 3,053 a wave: one lift per face
+// row, the memory recursion as one multiply-add) gain little at O = 5, but at
+// O = 4 they brought a fourth wave per SIMD (41k tets 372 -> 341 us).
 template <class R, int O, int M>
 struct LevelLds {
   // Bank-conflict-free strides: with a row stride RS and an element stride
@@ -137,8 +145,9 @@ void k_level(KPtrs p, LevelArgs a) {
   constexpr int JB = (B + LPE - 1) / LPE;        // memory-variable layout
   __shared__ R lds[L::TOTAL];
   // per element and face: normal, area ratio, neighbour impedances (the face
-  // words of the parameter table) and the boundary kind, staged for the
-  // Godunov items of the surface phase
+  // words of the parameter table; a boundary face holds the element's own),
+  // the inverse sums of both sides' impedances and the boundary kind, staged
+  // for the Godunov items of the surface phase
   __shared__ R fdat[KIND != KIND_PREDICT ? EPW * 4 * 8 : 1];
   __shared__ int fbc[KIND != KIND_PREDICT ? EPW * 4 : 1];
   // per element: flags and own B3 slot, for the matrix-core trace's exports
@@ -317,6 +326,8 @@ void k_level(KPtrs p, LevelArgs a) {
       R* d = fdat + (ec * 4 + q) * 8;
 #pragma unroll
       for (int k = 0; k < 6; ++k) d[k] = fw[k];
+      d[6] = R(1) / (zp + fw[4]);
+      d[7] = R(1) / (zs + fw[5]);
       fbc[ec * 4 + q] = fcode;
     }
 #pragma unroll
@@ -342,16 +353,18 @@ void k_level(KPtrs p, LevelArgs a) {
         const int i = t / F, f = t % F;
         const int bc = (fbc[ec * 4 + i] >> 4) & 15;
         const R* fp = fdat + (ec * 4 + i) * 8;
-        R qm[9], qp[9], out[15];
+        R qm[9], qp[9], v[4], tr[3], out[9];
 #pragma unroll
         for (int k = 0; k < 9; ++k) {
           qm[k] = fac[((i * 2 + 0) * LPE + k) * FS + f];
           qp[k] = fac[((i * 2 + 1) * LPE + k) * FS + f];
         }
-        const R zpp = bc == 0 ? fp[4] : zp, zsp = bc == 0 ? fp[5] : zs;
-        godunov<R>(qm, qp, fp[0], fp[1], fp[2], zp, zs, zpp, zsp, lam, mu, rho_inv, fp[3], bc, out);
+        godunov_state<R>(qm, qp, fp[0], fp[1], fp[2], zp, zs, fp[4], fp[5], fp[6], fp[7], bc, v, tr);
+        if (M > 0) flux_strain<R>(v, fp[0], fp[1], fp[2], fp[3], out);
+        else flux_stress<R>(v, fp[0], fp[1], fp[2], lam, mu, fp[3], out);
+        flux_velocity<R>(tr, rho_inv, fp[3], out + 6);
 #pragma unroll
-        for (int k = 0; k < 15; ++k) fac[((i * 2 + k / 9) * LPE + k % 9) * FS + f] = out[k];
+        for (int k = 0; k < 9; ++k) fac[((i * 2 + 0) * LPE + k) * FS + f] = out[k];
       }
     }
     __syncthreads();
@@ -363,30 +376,28 @@ void k_level(KPtrs p, LevelArgs a) {
 #pragma unroll
         for (int f = 0; f < FP; ++f) pf[i * FP + f] = fac[((i * 2 + 0) * LPE + q) * FS + f];
       RF::template lift_w<W>(w, pf, da);
-#pragma unroll
-      for (int lb = 0; lb < NBX; ++lb) qe[lb] += da[lb];
-      if (M > 0) {
-#pragma unroll
-        for (int lb = 0; lb < NBX; ++lb) da[lb] = R(0);
-        if (is_stress) {
-#pragma unroll
-          for (int i = 0; i < 4; ++i)
-#pragma unroll
-            for (int f = 0; f < FP; ++f) pf[i * FP + f] = fac[((i * 2 + 1) * LPE + q) * FS + f];
-          RF::template lift_w<W>(w, pf, da);
-        }
-      }
     }
     if (M > 0) {
+      // the stress lanes hold the lifted strain-rate rows: the memory
+      // variables of a mode take them (times omega) in the lane that owns the
+      // mode, the stresses are lam tr I + 2 mu times them
       __syncthreads();
       if (is_stress && e < EPW)
 #pragma unroll
         for (int lb = 0; lb < NBX; ++lb)
           if (has(lb)) coup[q * BS + base + lb] = da[lb];
       coup_pending = true;
-      // the mode owners below read the coupling rows of their own wave's modes
+      // coupling rows are read by their own wave (its modes)
       wave_lds_sync();
+      const R w1 = is_stress ? R(2) * mu : R(1), w3 = is_stress ? wabc : R(0);
+#pragma unroll
+      for (int lb = 0; lb < NBX; ++lb) {
+        const int b = base + lb;
+        if (has(lb)) qe[lb] += w1 * da[lb] + w3 * (coup[b] + coup[BS + b] + coup[2 * BS + b]);
+      }
     } else {
+#pragma unroll
+      for (int lb = 0; lb < NBX; ++lb) qe[lb] += da[lb];
       __syncthreads();
     }
   }
@@ -446,8 +457,9 @@ void k_level(KPtrs p, LevelArgs a) {
 
   // ------------------------------------------------ time kernel: predict step nn
   // The current derivative d^d Q lives only in the row exchange RX: each lane
-  // writes its own modes of the next derivative there and reads them back for
-  // the time integrals, so no register copy of it is kept across the loop.
+  // adds its own modes of a new derivative to the time integrals when it forms
+  // them and writes them there, so no register copy of it is kept across the
+  // loop.
   const int nn = step_new_of(a, cl);
   const int eflags = FI[12];
   if constexpr (TM) {
@@ -460,12 +472,20 @@ void k_level(KPtrs p, LevelArgs a) {
   const int rec_slot = FI[15];
   R te[NBX], t2[NBX];
   R dm[JW][MM][6];
+  {
+    const R c_0 = R(a.tc[cl][0]), h_0 = R(a.th[cl][0]);
 #pragma unroll
-  for (int lb = 0; lb < NBX; ++lb) {
-    te[lb] = R(0);
-    t2[lb] = R(0);
-    if (has(lb)) rx[q * BS + base + lb] = qe[lb];
+    for (int lb = 0; lb < NBX; ++lb) {
+      te[lb] = c_0 * qe[lb];
+      t2[lb] = h_0 * qe[lb];
+      if (has(lb)) rx[q * BS + base + lb] = qe[lb];
+    }
   }
+  R* const rd = reinterpret_cast<R*>(p.recD) + ((size_t)(rec_slot >= 0 ? rec_slot : 0) * O * LPE + q) * B + base;
+  if (rec_slot >= 0 && valid)
+#pragma unroll
+    for (int lb = 0; lb < NBX; ++lb)
+      if (has(lb)) rd[lb] = qe[lb];
 #pragma unroll
   for (int jw = 0; jw < JW; ++jw)
 #pragma unroll
@@ -473,34 +493,24 @@ void k_level(KPtrs p, LevelArgs a) {
 #pragma unroll
       for (int c = 0; c < 6; ++c) dm[jw][l][c] = qa[jw][l][c];
 
+  // dm holds theta^l at d = 0 and z = (d^d theta^l) / omega_l after it, so that
+  // its recursion, d^{d+1} theta = omega (d^d eps - d^d theta), is one
+  // multiply-add z' = eps - omega z (the first step eps - theta); the weights
+  // of the coupling carry the omega from then on
 #pragma unroll 1
   for (int d = 0; d < O; ++d) {
-    const R c_d = R(a.tc[cl][d]), h_d = R(a.th[cl][d]);
+    const R c_d = R(a.tc[cl][d]);
     const bool more = d + 1 < O;
-    __syncthreads();
-    {
-      R dv[NBX];
-#pragma unroll
-      for (int lb = 0; lb < NBX; ++lb) dv[lb] = has(lb) ? rx[q * BS + base + lb] : R(0);
-#pragma unroll
-      for (int lb = 0; lb < NBX; ++lb) te[lb] += c_d * dv[lb];
-      if (need_b2)
-#pragma unroll
-        for (int lb = 0; lb < NBX; ++lb) t2[lb] += h_d * dv[lb];
-      if (rec_slot >= 0 && valid) {
-        R* rd = reinterpret_cast<R*>(p.recD) + (((size_t)rec_slot * O + d) * LPE + q) * B + base;
-#pragma unroll
-        for (int lb = 0; lb < NBX; ++lb)
-          if (has(lb)) rd[lb] = dv[lb];
-      }
-    }
     if (more) {
-      R full[B];
+      __syncthreads();
+      {
+        R full[B];
 #pragma unroll
-      for (int b = 0; b < B; ++b) full[b] = rx[q * BS + b];
-      RF::template ck_grad_w<W>(w, full, G, gw0, gw1, gw2);
+        for (int b = 0; b < B; ++b) full[b] = rx[q * BS + b];
+        RF::template ck_grad_w<W>(w, full, G, gw0, gw1, gw2);
+      }
+      __syncthreads();
     }
-    __syncthreads();
     if (M > 0) {
 #pragma unroll
       for (int jw = 0; jw < JW; ++jw) {
@@ -518,13 +528,14 @@ void k_level(KPtrs p, LevelArgs a) {
           R cp[6] = {R(0), R(0), R(0), R(0), R(0), R(0)};
 #pragma unroll
           for (int l = 0; l < MM; ++l) {
+            const R wz = d == 0 ? R(1) : om[l], wq = om[l] * c_d * wz;
             const R tr = dm[jw][l][0] + dm[jw][l][1] + dm[jw][l][2];
 #pragma unroll
             for (int c = 0; c < 6; ++c) cp[c] -= bl[l] * dm[jw][l][c] + (c < 3 ? al[l] * tr : R(0));
 #pragma unroll
             for (int c = 0; c < 6; ++c) {
-              qa[jw][l][c] -= om[l] * c_d * dm[jw][l][c];
-              if (more) dm[jw][l][c] = om[l] * (eps[c] - dm[jw][l][c]);
+              qa[jw][l][c] -= wq * dm[jw][l][c];
+              if (more) dm[jw][l][c] = eps[c] - wz * dm[jw][l][c];
             }
           }
           if (e < EPW)
@@ -532,6 +543,12 @@ void k_level(KPtrs p, LevelArgs a) {
             for (int c = 0; c < 6; ++c) coup[c * BS + b] = cp[c];
         }
       }
+      if (d == 0)
+#pragma unroll
+        for (int l = 0; l < MM; ++l) {
+          al[l] *= om[l];
+          bl[l] *= om[l];
+        }
       // the coupling rows of a mode are read by the stress rows of the same
       // wave (the wave that owns the mode)
       wave_lds_sync();
@@ -539,6 +556,8 @@ void k_level(KPtrs p, LevelArgs a) {
     // reads of three modes, then their stores of the next derivative (a store
     // into the row exchange between reads would, for the compiler, possibly
     // alias the next mode's reads and put an LDS wait behind every mode)
+    const R c_n = more ? R(a.tc[cl][d + 1]) : R(0), h_n = more ? R(a.th[cl][d + 1]) : R(0);
+    const R wcd = wc * c_d;
     constexpr int CH = 3;
 #pragma unroll
     for (int l0 = 0; l0 < NBX; l0 += CH) {
@@ -548,19 +567,32 @@ void k_level(KPtrs p, LevelArgs a) {
         const int lb = l0 + k, b = base + lb;
         nx[k] = R(0);
         if (lb < NBX && has(lb)) {
-          const R cq = M > 0 ? wc * coup[cs + b] : R(0);
-          if (M > 0) qe[lb] += c_d * cq;
-          nx[k] = wabc * (grad[sa + b] + grad[sb + b] + grad[sc + b]) + wde * (grad[sd + b] + grad[se + b]) + cq;
+          const R cq = M > 0 ? coup[cs + b] : R(0);
+          if (M > 0) qe[lb] += wcd * cq;
+          if (more) {
+            nx[k] = wabc * (grad[sa + b] + grad[sb + b] + grad[sc + b]) + wde * (grad[sd + b] + grad[se + b]);
+            if (M > 0) nx[k] += wc * cq;
+          }
         }
       }
       if (more)
 #pragma unroll
-        for (int k = 0; k < CH; ++k)
-          if (l0 + k < NBX && has(l0 + k)) rx[q * BS + base + l0 + k] = nx[k];
+        for (int k = 0; k < CH; ++k) {
+          const int lb = l0 + k;
+          if (lb < NBX && has(lb)) {
+            rx[q * BS + base + lb] = nx[k];
+            te[lb] += c_n * nx[k];
+            t2[lb] += h_n * nx[k];
+          }
+        }
     }
+    if (more && rec_slot >= 0 && valid)
+#pragma unroll
+      for (int lb = 0; lb < NBX; ++lb)
+        if (has(lb)) rd[(size_t)(d + 1) * LPE * B + lb] = rx[q * BS + base + lb];
   }
-  // (the barrier after the last loop's products orders every read of RX
-  // before the time integral is written there)
+  // (the barrier after the last products orders every read of RX before the
+  // time integral is written there)
 
   // ------------------------------------------------ traces and volume
   // word offset of this wave's trace chunk ii in an element's trace (-1: none)
@@ -840,19 +872,16 @@ int launch_zero_words(void* p, size_t words, hipStream_t st) {
 
 // Waves per workgroup, measured in us per LTS cycle of three clusters (one
 // wave was the form before, two at FP32 O >= 4):
-//   O = 5  four: FP32 m=3 2k / 41k / 300k / 997k tets 115 / 553 / 2,924 /
-//          9,628 against 144 / 613 / 3,038 / 9,860 with two; m=0 300k 1,954
-//          against 2,216.  FP64 m=3 2k / 41k 238 / 1,872 against 245 / 1,733
-//          (one wave, spilling 2.4 KB a lane: 1,010 / 9,471), m=0 41k 921
-//          against 1,216
-//   O = 4  four while the launch is small or elastic: FP32 m=3 2k / 41k / 300k
-//          85 / 374 / 2,053 against 100 / 404 / 2,012, m=0 300k 1,265 against
-//          1,284; FP64 m=3 41k 750 against 1,078 (one: 2,322)
-//   O <= 3 two: FP32 m=3 300k O=3 1,050 against 1,313 (one: 3,212), O=2 605
-//          against 891 (one: 1,094); FP64 O=3 m=3 41k 410 against 508 (783)
-// Every split gives the same bits (no contraction across expressions), so the
-// choice may follow the size of the launch.
-constexpr long long W4_MAX_GROUPS_O4 = 16384;
+//   O >= 4  four: FP32 O=5 m=3 2k / 41k / 300k tets 112 / 541 / 2,881 against
+//           144 / 613 / 3,038 with two, m=0 300k 1,931 against 2,216; O=4 m=3
+//           84 / 341 / 1,810 against 100 / 404 / 1,966, 16 runs of 18k 1,879
+//           against 2,037.  FP64 m=3 41k O=5 1,776 against 1,733 (one wave,
+//           spilling 2.4 KB a lane: 9,475), O=4 720 against 1,078 (2,315)
+//   O <= 3  two: FP32 m=3 300k O=3 1,062 against 1,313 (one: 3,207), O=2 631
+//           against 891 (one: 1,092); FP64 O=3 m=3 41k 412 against 508 (785)
+// Every split gives the same bits (no contraction across expressions).
+template <int O>
+constexpr int LEVEL_W = O >= 4 ? 4 : 2;
 
 template <class R, int O, int M, int W, bool TM = false>
 static void launch_kind(const LevelArgs& a, dim3 grid, const KPtrs& p, hipStream_t st) {
@@ -875,13 +904,7 @@ int launch_level(const KPtrs& p, const LevelArgs& a, int runs, hipStream_t st) {
       return (int)hipGetLastError();
     }
   }
-  if constexpr (O == 4 && M > 0 && std::is_same<R, float>::value) {
-    if ((long long)groups * runs > W4_MAX_GROUPS_O4) {
-      launch_kind<R, O, M, 2>(a, grid, p, st);
-      return (int)hipGetLastError();
-    }
-  }
-  launch_kind<R, O, M, O >= 4 ? 4 : 2>(a, grid, p, st);
+  launch_kind<R, O, M, LEVEL_W<O>>(a, grid, p, st);
   return (int)hipGetLastError();
 }
 
