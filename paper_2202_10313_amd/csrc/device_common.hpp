@@ -139,9 +139,9 @@ __device__ __forceinline__ void wave_lds_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// Steps of cluster cl at the processed level (see LevelArgs::clock).
-__device__ __forceinline__ int step_new_of(const LevelArgs& a, int cl) {
-  return (int)((*a.clock + a.jrel) >> cl);
+// Steps of cluster cl at the processed level (see LevelArgs::clock), dl levels on.
+__device__ __forceinline__ int step_new_of(const LevelArgs& a, int cl, int dl = 0) {
+  return (int)((*a.clock + a.level + dl) >> cl);
 }
 __device__ __forceinline__ int step_fin_of(const LevelArgs& a, int cl) { return step_new_of(a, cl) - 1; }
 

@@ -100,7 +100,7 @@ struct edg_ctx {
   edg_plan plan{0, 0, 0};
   uint64_t shuf_seq = 0;             // launches shuffled so far (EDG_FLAG_SHUFFLE)
   DevBuf dbg;                        // non-finite count and first index (EDG_FLAG_CHECK_FINITE)
-  DevBuf dclock;                     // level at the start of the current cycle (device)
+  DevBuf dclock;                     // captured cycles: the level they start from, tickets; a zero (device)
   hipGraphExec_t cycle_exec = nullptr;
   hipGraph_t cycle_graph = nullptr;
 
@@ -654,22 +654,17 @@ struct Launch {
   static int level(const KPtrs& p, const LevelArgs& a, int runs, hipStream_t s) {
     return launch_level<R, O, M>(p, a, runs, s);
   }
-  static int src(const KPtrs& p, const LevelArgs& a, const SrcArgs& sa, hipStream_t s) {
-    return launch_sources<R, O, M>(p, a, sa, s);
-  }
-  static int rec(const KPtrs& p, const LevelArgs& a, const RecArgs& ra, int runs, hipStream_t s) {
-    return launch_receivers<R, O, M>(p, a, ra, runs, s);
+  static int pts(const KPtrs& p, const LevelArgs& a, const PointArgs& q, hipStream_t s) {
+    return launch_points<R, O, M>(p, a, q, s);
   }
 };
 
 typedef int (*LevelFn)(const KPtrs&, const LevelArgs&, int, hipStream_t);
-typedef int (*SrcFn)(const KPtrs&, const LevelArgs&, const SrcArgs&, hipStream_t);
-typedef int (*RecFn)(const KPtrs&, const LevelArgs&, const RecArgs&, int, hipStream_t);
+typedef int (*PtsFn)(const KPtrs&, const LevelArgs&, const PointArgs&, hipStream_t);
 
 struct Fns {
   LevelFn level = nullptr;
-  SrcFn src = nullptr;
-  RecFn rec = nullptr;
+  PtsFn pts = nullptr;
 };
 
 Fns pick(int fp64, int O, int M) {
@@ -677,8 +672,7 @@ Fns pick(int fp64, int O, int M) {
 #define EDG_PICK(R, OO, MM)                                                         \
   if ((std::is_same<R, double>::value == (fp64 != 0)) && O == OO && M == MM) {      \
     f.level = &Launch<R, OO, MM>::level;                                            \
-    f.src = &Launch<R, OO, MM>::src;                                                \
-    f.rec = &Launch<R, OO, MM>::rec;                                                \
+    f.pts = &Launch<R, OO, MM>::pts;                                                \
   }
   EDG_FOR_EACH_VARIANT(EDG_PICK)
 #undef EDG_PICK
@@ -723,7 +717,8 @@ LevelArgs base_args(const edg_ctx* c) {
     }
   }
   for (int l = 0; l < c->M; ++l) a.omega[l] = c->omega[l];
-  a.clock = (const long long*)c->dclock.p;
+  a.clock = (const long long*)c->dclock.p + 2;   // a zero
+  a.level = c->level;
   a.xcd_remap = c->plan.xcd_remap;
   a.trace_mfma = c->plan.trace_mfma;
   return a;
@@ -1211,8 +1206,8 @@ int edg_upload_clusters(edg_ctx* c, const int32_t* cluster) {
   c->n_src = 0;
   for (auto& v : c->src_of_run) v.clear();
   drop_graph(c);
-  if ((rc = dev_alloc(c, c->dclock, sizeof(long long)))) return rc;
-  HIPCHK(c, hipMemset(c->dclock.p, 0, sizeof(long long)));
+  if ((rc = dev_alloc(c, c->dclock, 3 * sizeof(long long)))) return rc;
+  HIPCHK(c, hipMemset(c->dclock.p, 0, c->dclock.bytes));
   if ((c->cfg.flags & EDG_FLAG_CHECK_FINITE) && !c->dbg.p &&
       (rc = dev_alloc(c, c->dbg, 2 * sizeof(unsigned long long))))
     return rc;
@@ -1398,7 +1393,7 @@ AdvanceArgs advance_args(edg_ctx* c) {
   A.ra.phi = (const double*)c->r_phi.p;
   A.ra.dt_sample = c->rec_dt;
   A.ra.ns = c->rec_ns;
-  A.ra.run0 = 0;
+  A.ra.runs = c->runs;
   A.ra.out = (double*)c->r_out.p;
   return A;
 }
@@ -1417,21 +1412,38 @@ int64_t level_updates(const edg_ctx* c, int lmax) {
   return u;
 }
 
-// The launches of one LTS cycle (Sec. V-B: per finest level, the sources of
-// the steps that end there, the fused finish-and-predict launch, the
-// receivers of the new predictions), then the device clock tick.  `last`:
-// the final level only finishes (no prediction is needed after the advance).
-// `timed`: per-level events (not inside a graph capture).
-int emit_cycle(edg_ctx* c, const AdvanceArgs& A, bool last, bool timed) {
+// The receivers of level j's predictions (if asked), then the sources of the
+// steps that end at level j + 1: one launch (see PointArgs).  a: level j's
+// arguments.
+int launch_points_after(edg_ctx* c, const AdvanceArgs& A, const KPtrs& p, const LevelArgs& a, int64_t j, bool receivers,
+                        int64_t tick = 0) {
+  PointArgs q;
+  q.r = A.ra;
+  if (!receivers) q.r.n = 0;
+  q.s = A.sa;
+  q.src_end = c->cl_end[level_lmax(c, j + 1)];
+  q.tick = tick ? (long long*)c->dclock.p : nullptr;
+  q.tick_by = tick;
+  const int rc = A.fn.pts(p, a, q, c->stream);
+  return rc ? fail(c, EDG_EHIP, std::string("point kernel: ") + hipGetErrorString((hipError_t)rc)) : 0;
+}
+
+// The launches of one LTS cycle (Sec. V-B: per finest level the fused
+// finish-and-predict launch, then the receivers of the new predictions and the
+// sources of the steps that end at the next level), j0 levels after the level
+// the arguments count from.  `last`: the final level only finishes (no
+// prediction is needed after the advance).  `timed`: per-level events.
+// `captured`: levels count from the device clock, which the cycle's last
+// launch moves on.
+int emit_cycle(edg_ctx* c, const AdvanceArgs& A, int64_t j0, bool last, bool timed, bool captured) {
   const int64_t per = (int64_t)1 << (c->cfg.n_clusters - 1);
   int rc;
   for (int64_t j = 1; j <= per; ++j) {
     const int lmax = level_lmax(c, j);
     LevelArgs a = base_args(c);
-    a.jrel = (int)j;
+    if (captured) a.clock = (const long long*)c->dclock.p;
+    a.level = (captured ? 0 : c->level + j0) + j;
     a.end = c->cl_end[lmax];
-    if (c->n_src > 0 && (rc = A.fn.src(A.p, a, A.sa, c->stream)))
-      return fail(c, EDG_EHIP, std::string("source kernel: ") + hipGetErrorString((hipError_t)rc));
     const bool fin = last && j == per;
     a.kind = fin ? KIND_NEIGHBOR : KIND_FUSED;
     if (timed) {
@@ -1440,11 +1452,8 @@ int emit_cycle(edg_ctx* c, const AdvanceArgs& A, bool last, bool timed) {
       return rc;
     }
     if ((rc = poison_after(c, A.p, a))) return rc;
-    if (!fin && c->n_rec > 0 && (rc = A.fn.rec(A.p, a, A.ra, c->runs, c->stream)))
-      return fail(c, EDG_EHIP, std::string("receiver kernel: ") + hipGetErrorString((hipError_t)rc));
+    if (!fin && (rc = launch_points_after(c, A, A.p, a, j, true, captured && j == per ? per : 0))) return rc;
   }
-  if ((rc = launch_tick((long long*)c->dclock.p, per, c->stream)))
-    return fail(c, EDG_EHIP, std::string("clock kernel: ") + hipGetErrorString((hipError_t)rc));
   return 0;
 }
 
@@ -1460,7 +1469,7 @@ int64_t cycle_updates(const edg_ctx* c) {
 int capture_cycle(edg_ctx* c, const AdvanceArgs& A) {
   drop_graph(c);
   HIPCHK(c, hipStreamBeginCapture(c->stream, hipStreamCaptureModeThreadLocal));
-  const int rc = emit_cycle(c, A, false, false);
+  const int rc = emit_cycle(c, A, 0, false, false, true);
   hipGraph_t g = nullptr;
   const hipError_t e = hipStreamEndCapture(c->stream, &g);
   if (rc) {
@@ -1506,14 +1515,14 @@ int advance_cycles(edg_ctx* c, int64_t nc, char* traces = nullptr) {
   // predict every element at the start (level offset 0)
   LevelArgs a = base_args(c);
   a.kind = KIND_PREDICT;
-  a.jrel = 0;
   a.end = c->cl_end[Nc - 1];
   int rc = poison_all(c, A.p);
   if (rc) return rc;
   rc = timed ? launch_timed(c, A.fn, A.p, a, 0) : launch_runs(c, A.fn, A.p, a);
   if (rc) return rc;
-  if (c->n_rec > 0 && (rc = A.fn.rec(A.p, a, A.ra, c->runs, c->stream)))
-    return fail(c, EDG_EHIP, std::string("receiver kernel: ") + hipGetErrorString((hipError_t)rc));
+  if ((rc = launch_points_after(c, A, A.p, a, 0, true))) return rc;
+  if (graph && nc > 1 && (rc = launch_clock((long long*)c->dclock.p, (long long)c->level, 0, c->stream)))
+    return fail(c, EDG_EHIP, std::string("clock kernel: ") + hipGetErrorString((hipError_t)rc));
   for (int64_t k = 0; k < nc; ++k) {
     const bool last = k + 1 == nc;
     if (graph && !last) {
@@ -1521,7 +1530,7 @@ int advance_cycles(edg_ctx* c, int64_t nc, char* traces = nullptr) {
       if ((rc = timed_begin(c, cycle_updates(c), (int)per))) return rc;
       HIPCHK(c, hipGraphLaunch(c->cycle_exec, c->stream));
       if ((rc = timed_end(c))) return rc;
-    } else if ((rc = emit_cycle(c, A, last, timed))) {
+    } else if ((rc = emit_cycle(c, A, k * per, last, timed, false))) {
       return rc;
     }
     c->updates += cycle_updates(c);
@@ -1607,13 +1616,13 @@ int hist_reserve(edg_ctx* c, int64_t levels) {
   return 0;
 }
 
-// The J levels of a segment from a synchronisation point, on the state p:
+// The J levels of a segment from the synchronisation point L0, on the state p:
 // a predict-only launch, fused finish + predict launches, a finish-only
 // launch, each predicting launch also writing the state at the start of its
 // predictions into level j's record of ahist.  The context's own advance
 // (own = true) also samples the receivers and finishes the last steps; a
 // replay stops after the last prediction (the finish is not needed).
-int run_recorded_levels(edg_ctx* c, const AdvanceArgs& A, const KPtrs& p, int64_t J, bool own) {
+int run_recorded_levels(edg_ctx* c, const AdvanceArgs& A, const KPtrs& p, int64_t L0, int64_t J, bool own) {
   const int Nc = c->cfg.n_clusters;
   const size_t wa = c->run_qa;
   auto chk = [&](int e, const char* what) {
@@ -1625,26 +1634,21 @@ int run_recorded_levels(edg_ctx* c, const AdvanceArgs& A, const KPtrs& p, int64_
   if ((rc = poison_all(c, p))) return rc;
   for (int64_t j = 0; j <= (own ? J : J - 1); ++j) {
     const int lmax = (j == 0 || j == J) ? Nc - 1 : level_lmax(c, j);
-    a.jrel = (int)j;
+    a.level = L0 + j;
     a.end = c->cl_end[lmax];
-    if (j > 0 && c->n_src > 0 && (rc = chk(A.fn.src(p, a, A.sa, c->stream), "source kernel"))) return rc;
     a.kind = j == 0 ? KIND_PREDICT : (j == J ? KIND_NEIGHBOR : KIND_FUSED);
     a.rec_e = j < J ? (void*)hist_rec_e(c, j) : nullptr;
     a.rec_a = (j < J && wa) ? (void*)hist_rec_a(c, j) : nullptr;
     shuffle_args(c, a, 1);
     if ((rc = chk(A.fn.level(p, a, 1, c->stream), "level kernel"))) return rc;
     if ((rc = poison_after(c, p, a))) return rc;
-    if (own && j < J && c->n_rec > 0 && (rc = chk(A.fn.rec(p, a, A.ra, c->runs, c->stream), "receiver kernel")))
-      return rc;
+    if (j < (own ? J : J - 1) && (rc = launch_points_after(c, A, p, a, j, own))) return rc;
   }
   return 0;
 }
 
 // nc >= 1 cycles as one segment whose level states the reverse sweep can use
-// without a replay: every level runs as the neighbour-data update, the copy
-// of the predicting groups' state into ahist, then the prediction (the
-// forward split where the plain advance fuses it), with the level clock held
-// at the segment start and the level offset counted over the segment
+// without a replay
 int advance_recorded(edg_ctx* c, int64_t nc) {
   const int Nc = c->cfg.n_clusters;
   const int64_t per = (int64_t)1 << (Nc - 1), J = nc * per;
@@ -1655,11 +1659,7 @@ int advance_recorded(edg_ctx* c, int64_t nc) {
   c->ev_updates.clear();
   c->ev_launches.clear();
   const AdvanceArgs A = advance_args(c);
-  auto chk = [&](int e, const char* what) {
-    return e ? fail(c, EDG_EHIP, std::string(what) + ": " + hipGetErrorString((hipError_t)e)) : 0;
-  };
-  if ((rc = run_recorded_levels(c, A, A.p, J, true))) return rc;
-  if ((rc = chk(launch_tick((long long*)c->dclock.p, J, c->stream), "clock kernel"))) return rc;
+  if ((rc = run_recorded_levels(c, A, A.p, c->level, J, true))) return rc;
   c->updates += nc * cycle_updates(c);
   c->hist_L0 = c->level;
   c->hist_J = J;
@@ -1828,7 +1828,6 @@ int edg_rewind(edg_ctx* c) {
   HIPCHK(c, hipStreamSynchronize(c->stream));
   for (DevBuf* b : {&c->Qe, &c->Qa, &c->T1, &c->T2, &c->T3, &c->RecD, &c->r_out})
     if (b->p) HIPCHK(c, hipMemset(b->p, 0, b->bytes));
-  HIPCHK(c, hipMemset(c->dclock.p, 0, sizeof(long long)));
   c->level = 0;
   for (int l = 0; l < MAX_CLUSTERS; ++l) c->nstep[l] = 0;
   return EDG_OK;
@@ -1901,11 +1900,11 @@ int adjoint_sweep(edg_ctx* c, const double* dj_seis, const double* dj_q, double*
   // the levels of a segment backwards: at each the transposed predictions and
   // the transposed updates of the same elements, one launch (kernel launches
   // only)
-  auto backward = [&](LevelArgs a, int64_t J) {
+  auto backward = [&](LevelArgs a, int64_t L0, int64_t J) {
     int e;
     for (int64_t j = J; j >= 0; --j) {
       const int lmax = (j == 0 || j == J) ? Nc - 1 : level_lmax(c, j);
-      a.jrel = (int)j;
+      a.level = L0 + j;
       a.end = c->cl_end[lmax];
       a.kind = j == J ? KIND_ADJ_UPDATE : j > 0 ? KIND_ADJ_FUSED : KIND_ADJ_PREDICT;
       if (j < J) {
@@ -1972,9 +1971,6 @@ int adjoint_sweep(edg_ctx* c, const double* dj_seis, const double* dj_q, double*
       const int64_t L0 = c->ckpts[si].first;
       const int64_t J = (si + 1 < nck ? c->ckpts[si + 1].first : L_end) - L0;
       if (J <= 0) continue;
-      const long long clock0 = (long long)L0;
-      HIPCHK(c, hipMemcpyAsync(c->dclock.p, &clock0, sizeof clock0, hipMemcpyHostToDevice, c->stream));
-      HIPCHK(c, hipStreamSynchronize(c->stream));
       LevelArgs a = base_args(c);
       a.run0 = 0;
       if (!(c->hist_valid && c->hist_L0 == L0 && c->hist_J == J && c->hist_run == run)) {
@@ -1988,7 +1984,7 @@ int adjoint_sweep(edg_ctx* c, const double* dj_seis, const double* dj_q, double*
         if (wa)
           HIPCHK(c, hipMemcpyAsync(rep_state + we * rs, ck + (c->runs * we + run * wa) * rs, wa * rs,
                                    hipMemcpyDeviceToDevice, c->stream));
-        if ((rc = run_recorded_levels(c, A, p, J, false))) return rc;
+        if ((rc = run_recorded_levels(c, A, p, L0, J, false))) return rc;
         HIPCHK(c, hipStreamSynchronize(c->stream));
         c->hist_L0 = L0;
         c->hist_J = J;
@@ -2003,15 +1999,18 @@ int adjoint_sweep(edg_ctx* c, const double* dj_seis, const double* dj_q, double*
         while (gi < graphs.size() && graphs[gi].J != J) ++gi;
         if (gi == graphs.size()) {
           graphs.push_back({J, nullptr, nullptr});
+          LevelArgs ag = a;
+          ag.clock = (const long long*)c->dclock.p;
           HIPCHK(c, hipStreamBeginCapture(c->stream, hipStreamCaptureModeThreadLocal));
-          rc = backward(a, J);
+          rc = backward(ag, 0, J);
           const hipError_t e = hipStreamEndCapture(c->stream, &graphs[gi].g);
           if (rc) return rc;
           if (e != hipSuccess) return fail(c, EDG_EHIP, std::string("adjoint graph capture: ") + hipGetErrorString(e));
           HIPCHK(c, hipGraphInstantiate(&graphs[gi].x, graphs[gi].g, nullptr, nullptr, 0));
         }
+        if ((rc = chk(launch_clock((long long*)c->dclock.p, (long long)L0, 0, c->stream), "clock kernel"))) return rc;
         HIPCHK(c, hipGraphLaunch(graphs[gi].x, c->stream));
-      } else if ((rc = backward(a, J))) {
+      } else if ((rc = backward(a, L0, J))) {
         return rc;
       }
       HIPCHK(c, hipStreamSynchronize(c->stream));
@@ -2062,8 +2061,6 @@ int adjoint_sweep(edg_ctx* c, const double* dj_seis, const double* dj_q, double*
       }
     }
   }
-  const long long clock_end = (long long)L_end;
-  HIPCHK(c, hipMemcpy(c->dclock.p, &clock_end, sizeof clock_end, hipMemcpyHostToDevice));
   c->adj_clean = true;
   return EDG_OK;
 }

@@ -126,13 +126,24 @@ __device__ __forceinline__ int gslot(int row, int dir) {
   return (int)((w >> (5 * row)) & 31);
 }
 
+// Waves per SIMD the registers are budgeted for: four where the update fits 128
+// registers without spills (left to itself the compiler takes up to 144 at
+// O = 4 m=3, three waves: 16 runs of 18k tets 2,037 us per cycle against
+// 1,879), two at O = 5 m=3 (it takes 168, three waves) and for the two-wave form
+// of O >= 4; FP64 O >= 4 one, so that nothing spills (41k tets O = 5 m=0 919 ->
+// 884 us, m=3 1,862 -> 1,835).
+template <class R, int O, int M, int W>
+constexpr int level_occ() {
+  return sizeof(R) == 8 ? (O >= 4 ? 1 : 2) : (O <= 3 || (W == 4 && !(O == 5 && M > 0))) ? 4 : 2;
+}
+
 // KIND is the launch kind (KIND_PREDICT, KIND_FUSED, KIND_NEIGHBOR) as a
 // template parameter: one code path per kernel keeps the register allocation
 // of the fused path free of the neighbour-only exit.  TM: the traces of faces
 // 0 and 1 (the two densest) as one dense product on the matrix cores.
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 template <class R, int O, int M, int KIND, int W, bool TM = false>
-__global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(sizeof(R) == 8 && O >= 4 ? 1 : 2, 4)))
+__global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(level_occ<R, O, M, W>(), 4)))
 void k_level(KPtrs p, LevelArgs a) {
   using RF = edg_gen::Ref<O>;
   using L = LevelLds<R, O, M>;
@@ -779,82 +790,106 @@ __device__ double stf_antiderivative(int kind, double p0, double p1, double t) {
   return (tau - p1 / (2.0 * M_PI) * sin(2.0 * M_PI * tau / p1)) / p1;
 }
 
+// The points of a mesh between two levels (see PointArgs), one launch: sources
+// and receivers touch different data, and at small meshes each launch costs as
+// much as a sixth of a level (5k tets, O = 4: level 17 us, source and receiver
+// kernels 3.4 and 4.5 us, clock tick 3.9 us per cycle when they ran apart).
+// Blocks [0, rec_blocks): one wave per receiver and run, its lanes (d, q)
+// forming the O x 9 derivative values before nine of them sample; the others:
+// one block per source.
+constexpr int PT_WAVES = 4;
 template <class R, int O, int M>
-__global__ void k_sources(KPtrs p, LevelArgs a, SrcArgs s) {
+__global__ __launch_bounds__(64 * PT_WAVES) void k_points(KPtrs p, LevelArgs a, PointArgs pt, int rec_blocks) {
   constexpr int B = edg_gen::Ref<O>::B;
-  constexpr int MM = M > 0 ? M : 1;
-  (void)MM;
-  const int t = blockIdx.x * blockDim.x + threadIdx.x;
-  const int src = t / (6 * B);
-  if (src >= s.n) return;
-  const int qb = t % (6 * B), qq = qb / B, b = qb % B;
-  const int elem = s.elem[src];
-  if (elem >= a.end) return;
-  const int cl = cluster_of(a, elem);
-  const double dt = a.dt[cl];
-  const int n = step_fin_of(a, cl);
-  const double t0 = (double)n * dt, t1 = (double)(n + 1) * dt;
-  const double w = stf_antiderivative(s.kind[src], s.par[2 * src], s.par[2 * src + 1], t1) -
-                   stf_antiderivative(s.kind[src], s.par[2 * src], s.par[2 * src + 1], t0);
-  const double inc = -s.moment[6 * src + qq] * s.phi[(size_t)src * B + b] * s.inv_det[src] * w;
-  const int g = elem / EPW, e = elem % EPW;
-  R* Qe = reinterpret_cast<R*>(p.Qe) + (size_t)s.run[src] * p.run_qe;
-  atomicAdd(&Qe[((size_t)g * B + b) * NSLOT + e * LPE + qq], R(inc));
-}
-
-// receivers: evaluate the predicted Taylor expansion at the sample times in
-// [t^n, t^{n+1}) of every receiver whose element was predicted at this level
-template <class R, int O, int M>
-__global__ void k_receivers(KPtrs p, LevelArgs a, RecArgs r) {
-  constexpr int B = edg_gen::Ref<O>::B;
-  const int run = r.run0 + (int)blockIdx.y;
-  select_run<R>(p, run);
-  const int t = blockIdx.x * blockDim.x + threadIdx.x;
-  const int rec = t / LPE, q = t % LPE;
-  if (rec >= r.n) return;
-  double* const out = r.out + (size_t)run * r.n * r.ns * LPE;
-  const int elem = r.elem[rec];
-  if (elem >= a.end) return;
-  const int cl = cluster_of(a, elem);
-  const double dt = a.dt[cl];
-  const int n = step_new_of(a, cl);
-  const double t0 = (double)n * dt, t1 = (double)(n + 1) * dt;
-  const R* D = reinterpret_cast<const R*>(p.recD) + (size_t)r.slot[rec] * O * LPE * B;
-  double val[O];
-  for (int d = 0; d < O; ++d) {
-    double v = 0.0;
-    for (int b = 0; b < B; ++b) v += (double)D[((size_t)d * LPE + q) * B + b] * r.phi[(size_t)rec * B + b];
-    val[d] = v;
-  }
-  // step n takes the samples in [t0 - eps, t1 - eps), eps = 1e-9 dt: a sample
-  // on (or within rounding of) a step boundary belongs to the step that
-  // starts there, whichever way the two sides round the boundary
-  const double eps = 1e-9 * dt, lo = t0 - eps, hi = t1 - eps;
-  long long s = (long long)floor(lo / r.dt_sample) - 1;
-  if (s < 0) s = 0;
-  for (; s < r.ns && (double)s * r.dt_sample < hi; ++s) {
-    const double ts = (double)s * r.dt_sample;
-    if (ts < lo) continue;
-    const double x = ts - t0;
-    double acc = 0.0, pw = 1.0, fact = 1.0;
-    for (int d = 0; d < O; ++d) {
-      acc += pw / fact * val[d];
-      pw *= x;
-      fact *= (double)(d + 1);
+  __shared__ double vals[PT_WAVES][O * LPE];
+  if ((int)blockIdx.x < rec_blocks) {
+    // receivers: evaluate the predicted Taylor expansion at the sample times in
+    // [t^n, t^{n+1}) of every receiver whose element was predicted at this level
+    const RecArgs& r = pt.r;
+    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int item = (int)blockIdx.x * PT_WAVES + w;
+    const int run = item / r.n, rec = item % r.n;
+    if (run < r.runs && r.elem[rec] < a.end) {
+      select_run<R>(p, run);
+      double* const out = r.out + (size_t)run * r.n * r.ns * LPE;
+      const int cl = cluster_of(a, r.elem[rec]);
+      const double dt = a.dt[cl];
+      const int n = step_new_of(a, cl);
+      const double t0 = (double)n * dt, t1 = (double)(n + 1) * dt;
+      // step n takes the samples in [t0 - eps, t1 - eps), eps = 1e-9 dt: a sample
+      // on (or within rounding of) a step boundary belongs to the step that
+      // starts there, whichever way the two sides round the boundary
+      const double eps = 1e-9 * dt, lo = t0 - eps, hi = t1 - eps;
+      long long s = (long long)floor(lo / r.dt_sample) - 1;
+      if (s < 0) s = 0;
+      while (s < r.ns && (double)s * r.dt_sample < lo) ++s;
+      if (s < r.ns && (double)s * r.dt_sample < hi) {   // (uniform over the wave)
+        if (lane < O * LPE) {
+          const R* D = reinterpret_cast<const R*>(p.recD) + ((size_t)r.slot[rec] * O * LPE + lane) * B;
+          const double* phi = r.phi + (size_t)rec * B;
+          double v = 0.0;
+          for (int b = 0; b < B; ++b) v += (double)D[b] * phi[b];
+          vals[w][lane] = v;
+        }
+        wave_lds_sync();
+        if (lane < LPE)
+          for (; s < r.ns && (double)s * r.dt_sample < hi; ++s) {
+            const double x = (double)s * r.dt_sample - t0;
+            double acc = 0.0, pw = 1.0, fact = 1.0;
+#pragma unroll
+            for (int d = 0; d < O; ++d) {
+              acc += pw / fact * vals[w][d * LPE + lane];
+              pw *= x;
+              fact *= (double)(d + 1);
+            }
+            out[((size_t)rec * r.ns + s) * LPE + lane] = acc;
+          }
+      }
     }
-    out[((size_t)rec * r.ns + s) * LPE + q] = acc;
+  } else {
+    // sources of the steps that end at the next level
+    const SrcArgs& s = pt.s;
+    const int src = (int)blockIdx.x - rec_blocks;
+    const int qq = threadIdx.x / B, b = threadIdx.x % B;
+    if (src < s.n && qq < 6 && s.elem[src] < pt.src_end) {
+      const int elem = s.elem[src];
+      const int cl = cluster_of(a, elem);
+      const double dt = a.dt[cl];
+      const int n = step_new_of(a, cl, 1) - 1;
+      const double t0 = (double)n * dt, t1 = (double)(n + 1) * dt;
+      const double w = stf_antiderivative(s.kind[src], s.par[2 * src], s.par[2 * src + 1], t1) -
+                       stf_antiderivative(s.kind[src], s.par[2 * src], s.par[2 * src + 1], t0);
+      const double inc = -s.moment[6 * src + qq] * s.phi[(size_t)src * B + b] * s.inv_det[src] * w;
+      const int g = elem / EPW, e = elem % EPW;
+      R* Qe = reinterpret_cast<R*>(p.Qe) + (size_t)s.run[src] * p.run_qe;
+      atomicAdd(&Qe[((size_t)g * B + b) * NSLOT + e * LPE + qq], R(inc));
+    }
+  }
+  if (pt.tick) {
+    // every block has read the clock before it takes its ticket
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      __threadfence();
+      unsigned* const ticket = reinterpret_cast<unsigned*>(pt.tick + 1);
+      if (atomicAdd(ticket, 1u) == gridDim.x - 1) {
+        *ticket = 0u;
+        *pt.tick += pt.tick_by;
+      }
+    }
   }
 }
 
 }  // namespace
 
-// advance the device level clock by d finest steps (end of a cycle)
-__global__ void k_tick(long long* clock, long long d) {
-  if (blockIdx.x == 0 && threadIdx.x == 0) clock[0] += d;
+__global__ void k_clock(long long* clock, long long set, int keep) {
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    clock[0] = set + (keep ? clock[0] : 0ll);
+    clock[1] = 0;
+  }
 }
 
-int launch_tick(long long* clock, long long d, hipStream_t st) {
-  hipLaunchKernelGGL(k_tick, dim3(1), dim3(64), 0, st, clock, d);
+int launch_clock(long long* clock, long long set, int keep, hipStream_t st) {
+  hipLaunchKernelGGL(k_clock, dim3(1), dim3(64), 0, st, clock, set, keep);
   return (int)hipGetLastError();
 }
 
@@ -909,26 +944,19 @@ int launch_level(const KPtrs& p, const LevelArgs& a, int runs, hipStream_t st) {
 }
 
 template <class R, int O, int M>
-int launch_sources(const KPtrs& p, const LevelArgs& a, const SrcArgs& s, hipStream_t st) {
-  if (s.n <= 0) return 0;
-  constexpr int B = edg_gen::Ref<O>::B;
-  const int total = s.n * 6 * B;
-  hipLaunchKernelGGL((k_sources<R, O, M>), dim3((total + 255) / 256), dim3(256), 0, st, p, a, s);
-  return (int)hipGetLastError();
-}
-
-template <class R, int O, int M>
-int launch_receivers(const KPtrs& p, const LevelArgs& a, const RecArgs& r, int runs, hipStream_t st) {
-  if (r.n <= 0 || runs <= 0) return 0;
-  const int total = r.n * LPE;
-  hipLaunchKernelGGL((k_receivers<R, O, M>), dim3((total + 127) / 128, runs), dim3(128), 0, st, p, a, r);
+int launch_points(const KPtrs& p, const LevelArgs& a, const PointArgs& q, hipStream_t st) {
+  const long long items = (long long)q.r.n * q.r.runs;
+  const int rec_blocks = (int)((items + PT_WAVES - 1) / PT_WAVES);
+  const int blocks = rec_blocks + q.s.n;
+  if (blocks <= 0) return q.tick ? launch_clock(q.tick, q.tick_by, 1, st) : 0;
+  static_assert(6 * edg_gen::Ref<O>::B <= 64 * PT_WAVES && O * LPE <= 64, "one block per source, one wave per receiver");
+  hipLaunchKernelGGL((k_points<R, O, M>), dim3((unsigned)blocks), dim3(64 * PT_WAVES), 0, st, p, a, q, rec_blocks);
   return (int)hipGetLastError();
 }
 
 #define EDG_INST(R, O, M)                                                                        \
   template int launch_level<R, O, M>(const KPtrs&, const LevelArgs&, int, hipStream_t);         \
-  template int launch_sources<R, O, M>(const KPtrs&, const LevelArgs&, const SrcArgs&, hipStream_t); \
-  template int launch_receivers<R, O, M>(const KPtrs&, const LevelArgs&, const RecArgs&, int, hipStream_t);
+  template int launch_points<R, O, M>(const KPtrs&, const LevelArgs&, const PointArgs&, hipStream_t);
 
 EDG_KERNEL_INSTANCES
 

@@ -50,13 +50,12 @@ struct LevelArgs {
   int n_clusters;
   int cl_end[MAX_CLUSTERS];     // padded end of cluster l (multiple of EPW)
   int cl_vend[MAX_CLUSTERS];    // end of cluster l's real elements (the rest is padding)
-  // The level being processed is *clock + jrel (finest steps from t = 0; the
-  // clock is device memory so that a captured cycle can be replayed): at
-  // level G cluster l (active iff G is a multiple of 2^l) ends its step
-  // G/2^l - 1 and starts step G/2^l.  A start-of-advance prediction uses
-  // jrel = 0 at a synchronisation point.
+  // The level being processed (finest steps from t = 0) is *clock + level: in a
+  // captured cycle the clock is device memory that the replays advance, else it
+  // points to a zero.  At level G cluster l (active iff G is a multiple of 2^l)
+  // ends its step G/2^l - 1 and starts step G/2^l.
   const long long* clock;
-  int jrel;
+  long long level;
   int xcd_remap;     // 1: the workgroups of one XCD take a contiguous range of element groups
   int trace_mfma;    // 1: the traces of faces 0 and 1 on the matrix cores (two-wave FP32 kernel)
   // workgroup order shuffle (debug; 0 = off): workgroup id w runs the work of
@@ -87,13 +86,26 @@ struct SrcArgs {
 
 struct RecArgs {
   int n;
+  int runs;               // every receiver of runs 0 .. runs - 1
   const int* elem;
   const int* slot;
   const double* phi;      // [n][B]
   double dt_sample;
   long long ns;
-  int run0;               // runs run0 + blockIdx.y take part
   double* out;            // [run][n][ns][9]
+};
+
+// What runs between the launch of level j and that of level j + 1: the
+// receivers sample the predictions of level j (the launch's LevelArgs), the
+// sources of the steps that end at level j + 1 are added; tick (not null): the
+// last workgroup to finish adds tick_by to the clock *tick (its tickets are
+// counted in tick[1])
+struct PointArgs {
+  RecArgs r;
+  SrcArgs s;
+  int src_end;            // internal slots [0, src_end) end a step at level j + 1
+  long long* tick;
+  long long tick_by;
 };
 
 // materials in device memory, caller's element order: rho, vp, vs [K];
@@ -138,13 +150,12 @@ int launch_get_dofs(const DofTables& t, long long k0, long long n, double* dofs,
 
 template <class R, int O, int M>
 int launch_level(const KPtrs& p, const LevelArgs& a, int runs, hipStream_t st);
-int launch_tick(long long* clock, long long d, hipStream_t st);
+// *clock = set + *clock * keep (keep 0 or 1), ticket counter zeroed
+int launch_clock(long long* clock, long long set, int keep, hipStream_t st);
 // zero `words` 32-bit words at p (a fill kernel: no memset node in a capture)
 int launch_zero_words(void* p, size_t words, hipStream_t st);
 template <class R, int O, int M>
-int launch_sources(const KPtrs& p, const LevelArgs& a, const SrcArgs& s, hipStream_t st);
-template <class R, int O, int M>
-int launch_receivers(const KPtrs& p, const LevelArgs& a, const RecArgs& r, int runs, hipStream_t st);
+int launch_points(const KPtrs& p, const LevelArgs& a, const PointArgs& q, hipStream_t st);
 
 // instantiated (precision, order, mechanisms) combinations
 #define EDG_FOR_EACH_VARIANT(X) \
