@@ -274,7 +274,7 @@ struct AdjLds {
   static constexpr int up(int v, int m, int r) { return v + ((r - v % m) % m + m) % m; }
   static constexpr int BS = B % 2 ? B : B + 1;       // odd row stride
   static constexpr int FS = FP + 1;
-  static constexpr int NSL = 20;                     // 18 read pairs, unread dummy 18, zero row 19
+  static constexpr int NSL = 27;                     // forward products: 18 read pairs and an unread dummy; transposed: [row][reference direction]
   static constexpr int GRAD = NSL * BS;
   static constexpr int COUP = 6 * BS;
   static constexpr int RX = LPE * BS;
@@ -333,7 +333,7 @@ __device__ __forceinline__ void ld_words(const R* base, int l, R* v) {
 }
 
 // (row, direction) -> gradient slot: velocity rows all directions, stress row
-// (i, j) directions i and j; 18 = not read, 19 = zeros
+// (i, j) directions i and j; 18 = not read
 __device__ __forceinline__ int aslot(int row, int dir) {
   constexpr int T[9][3] = {{9, 18, 18}, {18, 10, 18}, {18, 18, 11}, {12, 13, 18}, {18, 14, 15},
                            {16, 18, 17}, {0, 1, 2}, {3, 4, 5}, {6, 7, 8}};
@@ -342,14 +342,16 @@ __device__ __forceinline__ int aslot(int row, int dir) {
   return (int)((w >> (5 * row)) & 31);
 }
 
-// Waves per SIMD the registers are budgeted for.  FP64: one (up to 512
-// registers; at two, 250-790 B a lane spill: O = 5 m=3 12k tets 1,288 us per
-// reverse cycle against 718).  FP32: three where at most 28 registers spill
-// for it (m=0 O = 4 97k tets 931 us against 1,119 at two; O = 3 m=3 838 against
-// 888), two at O >= 4 m=3 (O = 5: 2,221 us against 3,835 at three).
+// Waves per SIMD the registers are budgeted for (us per reverse cycle of two
+// clusters).  FP32: three; 144-166 registers without a spill but at O = 5 m=3,
+// where 112 B a lane spill and still pay (37k tets 761 against 800 at two, 4.6k
+// tets 147 against 160); four at O = 4 m=0 spill 116 B: 305 -> 363.  FP64: one
+// (up to 512 registers), two at O = 4, whose 57 KB of LDS leave room for a second
+// workgroup (10k tets m=0 249 -> 184, m=3 363 -> 314, at 576 tets 80 -> 83; at
+// O = 3, 140 B of spills, 161 -> 189; at O = 5 the LDS holds one workgroup).
 template <class R, int O, int M>
 constexpr int adj_occ() {
-  return sizeof(R) == 8 ? 1 : (M == 0 || O <= 3) ? 3 : 2;
+  return sizeof(R) == 4 ? 3 : O == 4 ? 2 : 1;
 }
 
 // One reverse level: the transposed prediction of the steps that start here
@@ -488,46 +490,47 @@ void k_adjoint(KPtrs p, APtrs ad, LevelArgs a) {
   auto st6 = [&](int at6, int d, const R* v) { st_words<6, SC::OL>(SW + at6 + d * SC::EPW6, l1, v); };
   auto ld6 = [&](int at6, int d, R* v) { ld_words<6, SC::OL>(SW + at6 + d * SC::EPW6, l1, v); };
 
-  int qi = 0, qj = 0;
-  if (q < 3) { qi = q; qj = q; }
-  else if (q == 3) { qi = 0; qj = 1; }
-  else if (q == 4) { qi = 1; qj = 2; }
-  else if (q == 5) { qi = 0; qj = 2; }
-  const R delta = q < 3 ? R(1) : R(0);
-
-  R G[9];
+  // This lane's parameters and LDS offsets.  Formed twice, before and after the
+  // face phases (from opaque copies of the lane's row and address), so that they
+  // hold no registers there, where the reverse flux needs the most.
+  struct LanePar {
+    R G[9], rho_inv, lam, mu, al[MM], bl[MM], wabc, wde, wc;
+    int qi, qj, sa, sb, sc, sd, se;
+  };
+  auto lane_par = [&](const R* Pl, int ql, LanePar& x) {
+    const bool st = ql < 6;
+    x.qi = x.qj = 0;
+    if (ql < 3) { x.qi = ql; x.qj = ql; }
+    else if (ql == 3) { x.qi = 0; x.qj = 1; }
+    else if (ql == 4) { x.qi = 1; x.qj = 2; }
+    else if (ql == 5) { x.qi = 0; x.qj = 2; }
 #pragma unroll
-  for (int c = 0; c < 9; ++c) G[c] = P[c];
-  const R rho_inv = P[9], lam = P[10], mu = P[11];
-  R al[MM], bl[MM];
+    for (int c = 0; c < 9; ++c) x.G[c] = Pl[c];
+    x.rho_inv = Pl[9];
+    x.lam = Pl[10];
+    x.mu = Pl[11];
 #pragma unroll
-  for (int l = 0; l < MM; ++l) {
-    al[l] = M > 0 ? P[14 + 2 * l] : R(0);
-    bl[l] = M > 0 ? P[15 + 2 * l] : R(0);
-  }
-  // gradient slots this lane writes (forward products) and the star-product
-  // reads: stress row ij: lam delta div v + mu (d_j v_i + d_i v_j) + coupling;
-  // velocity row i: rho_inv sum_d d_d sigma_id
-  R* const gw0 = grad + aslot(q, 0) * BS;
-  R* const gw1 = grad + aslot(q, 1) * BS;
-  R* const gw2 = grad + aslot(q, 2) * BS;
-  int sa, sb, sc, sd, se;
-  R wabc, wde, wc;
-  if (is_stress) {
-    sa = aslot(6, 0) * BS; sb = aslot(7, 1) * BS; sc = aslot(8, 2) * BS;
-    sd = aslot(6 + qi, qj) * BS; se = aslot(6 + qj, qi) * BS;
-    wabc = lam * delta; wde = mu; wc = R(1);
-  } else {
-    const int i = q - 6;
-    sa = aslot(sym_index(i, 0), 0) * BS; sb = aslot(sym_index(i, 1), 1) * BS; sc = aslot(sym_index(i, 2), 2) * BS;
-    sd = sa; se = sb;
-    wabc = rho_inv; wde = R(0); wc = R(0);
-  }
+    for (int l = 0; l < MM; ++l) {
+      x.al[l] = M > 0 ? Pl[14 + 2 * l] : R(0);
+      x.bl[l] = M > 0 ? Pl[15 + 2 * l] : R(0);
+    }
+    // the star products: stress row ij: lam delta div v + mu (d_j v_i + d_i v_j)
+    // + coupling; velocity row i: rho_inv sum_d d_d sigma_id
+    if (st) {
+      x.sa = aslot(6, 0) * BS; x.sb = aslot(7, 1) * BS; x.sc = aslot(8, 2) * BS;
+      x.sd = aslot(6 + x.qi, x.qj) * BS; x.se = aslot(6 + x.qj, x.qi) * BS;
+      x.wabc = ql < 3 ? x.lam : R(0); x.wde = x.mu; x.wc = R(1);
+    } else {
+      const int i = ql - 6;
+      x.sa = aslot(sym_index(i, 0), 0) * BS; x.sb = aslot(sym_index(i, 1), 1) * BS;
+      x.sc = aslot(sym_index(i, 2), 2) * BS;
+      x.sd = x.sa; x.se = x.sb;
+      x.wabc = x.rho_inv; x.wde = R(0); x.wc = R(0);
+    }
+  };
   const int cs = (is_stress ? q : 0) * BS;
-  // transposed products read this row's gradient adjoints: the used slots, else zeros
-  const R* const gt0 = grad + (aslot(q, 0) == 18 ? 19 : aslot(q, 0)) * BS;
-  const R* const gt1 = grad + (aslot(q, 1) == 18 ? 19 : aslot(q, 1)) * BS;
-  const R* const gt2 = grad + (aslot(q, 2) == 18 ? 19 : aslot(q, 2)) * BS;
+  // the row's combined gradient adjoints, one row per reference direction
+  R* const yr = grad + q * 3 * BS;
 
   for (int i = threadIdx.x; i < EPW * NGS; i += 64 * W) gsh[i] = 0.0;
 
@@ -573,6 +576,13 @@ void k_adjoint(KPtrs p, APtrs ad, LevelArgs a) {
   // ---------------------------------------------- forward recompute: D_d, T, T2
   R te[NBX], t2[NBX];
   {
+    LanePar x;
+    lane_par(P, q, x);
+    const int sa = x.sa, sb = x.sb, sc = x.sc, sd = x.sd, se = x.se;
+    // gradient slots this lane writes
+    R* const gw0 = grad + aslot(q, 0) * BS;
+    R* const gw1 = grad + aslot(q, 1) * BS;
+    R* const gw2 = grad + aslot(q, 2) * BS;
     const R* Se = reinterpret_cast<const R*>(ad.Se) + (size_t)g * B * NSLOT;
     const R* Sa = reinterpret_cast<const R*>(ad.Sa) + (size_t)g * JB * MM * 6 * NSLOT;
     R dm[MM][6];
@@ -604,7 +614,7 @@ void k_adjoint(KPtrs p, APtrs ad, LevelArgs a) {
         R full[B];
 #pragma unroll
         for (int b = 0; b < B; ++b) full[b] = rx[q * BS + b];
-        RF::template ck_grad_w<W>(w, full, G, gw0, gw1, gw2);
+        RF::template ck_grad_w<W>(w, full, x.G, gw0, gw1, gw2);
       }
       __syncthreads();
       if (own) {
@@ -623,7 +633,7 @@ void k_adjoint(KPtrs p, APtrs ad, LevelArgs a) {
           for (int l = 0; l < MM; ++l) {
             const R tr = dm[l][0] + dm[l][1] + dm[l][2];
 #pragma unroll
-            for (int c = 0; c < 6; ++c) cp[c] -= bl[l] * dm[l][c] + (c < 3 ? al[l] * tr : R(0));
+            for (int c = 0; c < 6; ++c) cp[c] -= x.bl[l] * dm[l][c] + (c < 3 ? x.al[l] * tr : R(0));
 #pragma unroll
             for (int c = 0; c < 6; ++c) dm[l][c] = om[l] * (eps[c] - dm[l][c]);
           }
@@ -646,8 +656,8 @@ void k_adjoint(KPtrs p, APtrs ad, LevelArgs a) {
           nx[lb] = R(0);
           if (has(lb)) {
             sab[lb] = grad[sa + b] + grad[sb + b] + grad[sc + b];
-            const R cq = M > 0 ? wc * coup[cs + b] : R(0);
-            nx[lb] = wabc * sab[lb] + wde * (grad[sd + b] + grad[se + b]) + cq;
+            const R cq = M > 0 ? x.wc * coup[cs + b] : R(0);
+            nx[lb] = x.wabc * sab[lb] + x.wde * (grad[sd + b] + grad[se + b]) + cq;
           }
         }
         if (!is_stress && act) stV(d, sab);
@@ -809,21 +819,39 @@ void k_adjoint(KPtrs p, APtrs ad, LevelArgs a) {
 
   // ---------------------------------------------- volume kernel
   // V = -(lam delta div v + mu (d_j v_i + d_i v_j)) (stress), -rho_inv div sigma (velocity), -omega_l eps (memory)
+  LanePar x;
+  {
+    const R* Pl = P;
+    int ql = q;
+    asm volatile("" : "+v"(Pl), "+v"(ql));
+    lane_par(Pl, ql, x);
+  }
+  const R rho_inv = x.rho_inv, lam = x.lam, mu = x.mu;
+  const int qi = x.qi, qj = x.qj, sa = x.sa, sb = x.sb, sc = x.sc;
+  R al[MM], bl[MM];
+#pragma unroll
+  for (int l = 0; l < MM; ++l) { al[l] = x.al[l]; bl[l] = x.bl[l]; }
 #pragma unroll
   for (int lb = 0; lb < NBX; ++lb) le[lb] = has(lb) ? at(Le, (base + lb) * NSLOT + slot) : R(0);
-  if (act)
+  // the directions of this row's gradient-entry adjoints (write_y) and their
+  // columns of G', re-read by lane-dependent index (selecting from the register
+  // copy would put that into scratch memory)
+  const int vi = is_stress ? 0 : q - 6;
+  const int k0 = is_stress ? qj : vi, k1 = is_stress ? qi : (vi + 1) % 3, k2 = is_stress ? 0 : (vi + 2) % 3;
+  R g0[3], g1[3], g2[3];
 #pragma unroll
-    for (int lb = 0; lb < NBX; ++lb)
-      if (has(lb)) rx[q * BS + base + lb] = te[lb];
-  __syncthreads();
+  for (int c = 0; c < 3; ++c) {
+    g0[c] = P[3 * c + k0];
+    g1[c] = P[3 * c + k1];
+    g2[c] = P[3 * c + k2];
+  }
   {
+    // (the row exchange still holds the time integrals of the last face phase)
     R full[B];
 #pragma unroll
     for (int b = 0; b < B; ++b) full[b] = rx[q * BS + b];
-    RF::template vol_grad_w<W>(w, full, G, gw0, gw1, gw2);
+    RF::template vol_grad_w<W>(w, full, x.G, grad + aslot(q, 0) * BS, grad + aslot(q, 1) * BS, grad + aslot(q, 2) * BS);
   }
-  if (threadIdx.x < 64 && act)      // zero row for the transposed products (written once, never overwritten)
-    for (int b = q; b < BS; b += LPE) grad[19 * BS + b] = R(0);
   __syncthreads();
   // Material words, summed in registers over the whole kernel: a product's
   // adjoint rows x paired with the strain rates give dJ/dlam (tr x tr eps) and
@@ -845,8 +873,7 @@ void k_adjoint(KPtrs p, APtrs ad, LevelArgs a) {
     }
   }
   // exchange: elastic adjoint rows, omega-weighted memory-variable adjoints
-  // (own modes: the rows and coupling rows write_gb reads, and the gradient
-  // slots it overwrites, are those of its own wave's modes)
+  // (own modes: the rows and coupling rows that write_y reads)
   if (act)
 #pragma unroll
     for (int lb = 0; lb < NBX; ++lb)
@@ -854,7 +881,7 @@ void k_adjoint(KPtrs p, APtrs ad, LevelArgs a) {
   wave_lds_sync();
   if (own) {
     const int b = base + q;
-    R eps[6], x[6];
+    R eps[6], xr[6];
     eps[0] = grad[aslot(6, 0) * BS + b];
     eps[1] = grad[aslot(7, 1) * BS + b];
     eps[2] = grad[aslot(8, 2) * BS + b];
@@ -862,8 +889,8 @@ void k_adjoint(KPtrs p, APtrs ad, LevelArgs a) {
     eps[4] = R(0.5) * (grad[aslot(7, 2) * BS + b] + grad[aslot(8, 1) * BS + b]);
     eps[5] = R(0.5) * (grad[aslot(6, 2) * BS + b] + grad[aslot(8, 0) * BS + b]);
 #pragma unroll
-    for (int c = 0; c < 6; ++c) x[c] = rx[c * BS + b];
-    strain_words(eps, x, -1.0);
+    for (int c = 0; c < 6; ++c) xr[c] = rx[c * BS + b];
+    strain_words(eps, xr, -1.0);
     if (M > 0) {
       R lv[6 * MM];
 #pragma unroll
@@ -899,61 +926,65 @@ void k_adjoint(KPtrs p, APtrs ad, LevelArgs a) {
     }
   }
   wave_lds_sync();
-  // gradient-entry adjoints of this row, own modes, into its slots (sign s:
-  // -1 for the volume kernel, +1 for the time kernel's next derivative)
-  // Branch-free: every lane forms its three (row, direction) entries as
-  //   A rx[r] + C coup[c] + L (rx[0] + rx[1] + rx[2]):
-  // velocity row i, direction k: A = (1 + delta_ik) mu on exchange row
-  //   sym(i, k), C = 1 (i = k) or 1/2 on coupling row sym(i, k) (anelastic
-  //   only), L = delta_ik lam on the normal-stress rows;
-  // stress row (qi, qj), direction k in {qi, qj}: A = rho_inv on the velocity
-  //   row of the other index; directions a stress row does not use write nothing
-  auto write_gb = [&](const R sgn) {
+  // Gradient-entry adjoints of this row, own modes, combined with G' to the
+  // reference directions (sign s: -1 for the volume kernel, +1 for the time
+  // kernel's next derivative).  Combined here, mode by mode, they cost nine
+  // multiply-adds per own mode instead of nine per mode in every wave's
+  // product.  Branch-free, every lane up to three (row, direction) entries:
+  //   velocity row i, directions i, i + 1, i + 2 (mod 3): (1 + delta) mu on
+  //     exchange row sym(i, k), 1 or 1/2 on coupling row sym(i, k) (anelastic
+  //     only), in the first lam on the sum of the normal-stress rows;
+  //   stress row (qi, qj), directions qj and, off the diagonal, qi: rho_inv on
+  //     the velocity row of the other index; the rest zero
+  const int r0 = (is_stress ? 6 + qi : vi) * BS, r1 = (is_stress ? 6 + qj : sym_index(vi, k1)) * BS,
+            r2 = (is_stress ? 0 : sym_index(vi, k2)) * BS;
+  const int c0 = is_stress ? 0 : vi * BS;          // (coupling rows: as r1, r2 in velocity lanes, unused else)
+  auto write_y = [&](const R sgn) {
+    const R A0 = sgn * (is_stress ? rho_inv : R(2) * mu), Lw = is_stress ? R(0) : sgn * lam;
+    const R A1 = sgn * (is_stress ? (qi == qj ? R(0) : rho_inv) : mu), A2 = is_stress ? R(0) : sgn * mu;
+    const R C0 = is_stress ? R(0) : sgn, C1 = R(0.5) * C0;
+    const int x1 = is_stress ? 0 : r1, x2 = is_stress ? 0 : r2;   // coupling rows
+    // reads of three modes, then their stores (a store may alias the next
+    // mode's reads for the compiler, which would wait for each)
+    constexpr int CH = 3;
 #pragma unroll
-    for (int k = 0; k < 3; ++k) {
-      int rrow, crow;
-      R A, C, Lw;
-      bool wr;
-      if (!is_stress) {
-        const int i = q - 6, sk = sym_index(i, k);
-        rrow = sk;
-        crow = sk;
-        A = (i == k ? R(2) : R(1)) * mu;
-        C = i == k ? R(1) : R(0.5);
-        Lw = i == k ? lam : R(0);
-        wr = act;
-      } else {
-        const int iv = k == qj ? qi : (k == qi ? qj : -1);
-        rrow = 6 + (iv < 0 ? 0 : iv);
-        crow = 0;
-        A = rho_inv;
-        C = R(0);
-        Lw = R(0);
-        wr = act && iv >= 0;
-      }
-      // all reads of a direction, then its stores (the stores may alias the
-      // exchange rows for the compiler, so interleaving them would serialise
-      // every read behind the previous store)
-      R v[NBX];
+    for (int l0 = 0; l0 < NBX; l0 += CH) {
+      R y[CH][3];
 #pragma unroll
-      for (int lb = 0; lb < NBX; ++lb) {
-        const int b = base + lb;
-        v[lb] = R(0);
-        if (has(lb)) {
-          v[lb] = A * rx[rrow * BS + b] + Lw * (rx[b] + rx[BS + b] + rx[2 * BS + b]);
-          if (M > 0) v[lb] += C * coup[crow * BS + b];
+      for (int k = 0; k < CH; ++k) {
+        const int lb = l0 + k, b = base + lb;
+        if (lb < NBX && has(lb)) {
+          R v0 = A0 * rx[r0 + b] + Lw * (rx[b] + rx[BS + b] + rx[2 * BS + b]);
+          R v1 = A1 * rx[r1 + b], v2 = A2 * rx[r2 + b];
+          if (M > 0) {
+            v0 += C0 * coup[c0 + b];
+            v1 += C1 * coup[x1 + b];
+            v2 += C1 * coup[x2 + b];
+          }
+#pragma unroll
+          for (int c = 0; c < 3; ++c) y[k][c] = g0[c] * v0 + g1[c] * v1 + g2[c] * v2;
         }
       }
-      R* const dst = grad + aslot(q, k) * BS;
-      if (wr)
+      if (act)
 #pragma unroll
-        for (int lb = 0; lb < NBX; ++lb)
-          if (has(lb)) dst[base + lb] = sgn * v[lb];
+        for (int k = 0; k < CH; ++k)
+          if (l0 + k < NBX && has(l0 + k))
+#pragma unroll
+            for (int c = 0; c < 3; ++c) yr[c * BS + base + l0 + k] = y[k][c];
     }
   };
-  write_gb(R(-1));
+  // adds a transposed product of the combined adjoints to v
+  auto add_product = [&](const bool vol, R (&v)[NBX]) {
+    R out[NBX];
+    if (vol) RF::template vol_grad_T_w<W>(w, yr, yr + BS, yr + 2 * BS, out);
+    else RF::template ck_grad_T_w<W>(w, yr, yr + BS, yr + 2 * BS, out);
+#pragma unroll
+    for (int lb = 0; lb < NBX; ++lb) v[lb] += out[lb];
+  };
+  // (no barrier: the wave's modes of these rows were read in the wave alone)
+  write_y(R(-1));
   __syncthreads();
-  RF::template vol_grad_T_w<W>(w, gt0, gt1, gt2, G, lte);
+  add_product(true, lte);
   // (no barrier: the reverse loop's first LDS writes are the wave's own
   // modes of the exchange rows, which the transposed product does not read)
 
@@ -1026,9 +1057,9 @@ void k_adjoint(KPtrs p, APtrs ad, LevelArgs a) {
         for (int c = 0; c < 6; ++c) x[c] = rx[c * BS + base + q];
         strain_words(eps, x, 1.0);
       }
-      write_gb(R(1));
+      write_y(R(1));
       __syncthreads();
-      RF::template ck_grad_T_w<W>(w, gt0, gt1, gt2, G, cur);
+      add_product(false, cur);
       // (no barrier: the coupling block below writes the wave's own modes of
       // the exchange and coupling rows, which the transposed product does
       // not read; the next iteration's products follow its first barrier)

@@ -12,8 +12,9 @@
 //   trace    : p_i = t F~_i for the four faces (the surface kernel's T F~_i)
 //   lift     : acc += sum_i p_i F^_i with F^_i = F~_i^T (orthonormal basis, so
 //              the inverse mass matrix is the identity on the reference tet)
-//   ck_grad_T, vol_grad_T : the transposes of ck_grad and vol_grad (adjoint
-//              kernels); trace and lift are each other's transposes
+//   ck_grad_T, vol_grad_T : the transposes of ck_grad and vol_grad after the
+//              combination with G' (adjoint kernels); trace and lift are each
+//              other's transposes
 //
 // Usage: gen_refmats <out_header> <order>...
 #include <cstdio>
@@ -71,74 +72,8 @@ int main(int argc, char** argv) {
     std::fprintf(f, "  static constexpr int B = %d, F = %d, FP = %d;\n", B, F, FP);
     std::fprintf(f, "  static constexpr int NNZ_K = %d, NNZ_F = %d;\n", nnzK[0] + nnzK[1] + nnzK[2],
                  nnzF[0] + nnzF[1] + nnzF[2] + nnzF[3]);
-    // ck_grad / vol_grad
-    for (int vol = 0; vol < 2; ++vol) {
-      std::fprintf(f, "  template <class R> __device__ static __forceinline__ void %s(const R* __restrict__ d, const R* __restrict__ G, R* __restrict__ out) {\n",
-                   vol ? "vol_grad" : "ck_grad");
-      for (int b = 0; b < B; ++b) {
-        for (int c = 0; c < 3; ++c) {
-          std::string s;
-          bool first = true;
-          for (int bb = 0; bb < B; ++bb) {
-            const double k = vol ? Kd[(c * B + bb) * B + b] : Kd[(c * B + b) * B + bb];
-            if (std::fabs(k) > ZERO_TOL) term(s, first, k, "d[" + std::to_string(bb) + "]");
-          }
-          if (first) s = "R(0)";
-          std::fprintf(f, "    const R x%d_%d = %s;\n", c, b, s.c_str());
-        }
-        for (int dd = 0; dd < 3; ++dd)
-          std::fprintf(f, "    out[%d] = G[%d]*x0_%d + G[%d]*x1_%d + G[%d]*x2_%d;\n", dd * B + b, dd, b, 3 + dd, b,
-                       6 + dd, b);
-      }
-      std::fprintf(f, "  }\n");
-    }
-    // transposes of ck_grad / vol_grad (adjoint kernels): with
-    // y_k = sum_d G[3k+d] g[d] (g: the three physical-direction rows),
-    // ck_grad_T adds sum_k K'_k^T y_k and vol_grad_T adds sum_k K'_k y_k
-    for (int vol = 0; vol < 2; ++vol) {
-      std::fprintf(f, "  template <class R> __device__ static __forceinline__ void %s(const R* __restrict__ g, const R* __restrict__ G, R* __restrict__ acc) {\n",
-                   vol ? "vol_grad_T" : "ck_grad_T");
-      // one direction at a time keeps B values of y live, not 3B
-      for (int c = 0; c < 3; ++c) {
-        for (int b = 0; b < B; ++b) {
-          bool used = false;
-          for (int bb = 0; bb < B && !used; ++bb) {
-            const double k = vol ? Kd[(c * B + bb) * B + b] : Kd[(c * B + b) * B + bb];
-            used = std::fabs(k) > ZERO_TOL;
-          }
-          if (used)
-            std::fprintf(f, "    const R y%d_%d = G[%d]*g[%d] + G[%d]*g[%d] + G[%d]*g[%d];\n", c, b, 3 * c, b, 3 * c + 1,
-                         B + b, 3 * c + 2, 2 * B + b);
-        }
-        for (int bb = 0; bb < B; ++bb) {
-          std::string s;
-          bool first = true;
-          for (int b = 0; b < B; ++b) {
-            const double k = vol ? Kd[(c * B + bb) * B + b] : Kd[(c * B + b) * B + bb];
-            if (std::fabs(k) > ZERO_TOL) term(s, first, k, "y" + std::to_string(c) + "_" + std::to_string(b));
-          }
-          if (!first) std::fprintf(f, "    acc[%d] += %s;\n", bb, s.c_str());
-        }
-      }
-      std::fprintf(f, "  }\n");
-    }
-    // trace
-    std::fprintf(f, "  template <class R> __device__ static __forceinline__ void trace(const R* __restrict__ t, R* __restrict__ p) {\n");
-    for (int i = 0; i < 4; ++i)
-      for (int ff = 0; ff < FP; ++ff) {
-        std::string s;
-        bool first = true;
-        if (ff < F)
-          for (int b = 0; b < B; ++b) {
-            const double v = M.Ft[(i * B + b) * F + ff];
-            if (std::fabs(v) > ZERO_TOL) term(s, first, v, "t[" + std::to_string(b) + "]");
-          }
-        if (first) s = "R(0)";
-        std::fprintf(f, "    p[%d] = %s;\n", i * FP + ff, s.c_str());
-      }
-    std::fprintf(f, "  }\n");
-    // trace onto one face: p[0..FP) for face i
-    for (int i = 0; i < 4; ++i) {
+    // trace onto one sparse face: p[0..FP) for face i
+    for (int i = 2; i < 4; ++i) {
       std::fprintf(f, "  template <class R> __device__ static __forceinline__ void trace_f%d(const R* __restrict__ t, R* __restrict__ p) {\n", i);
       for (int ff = 0; ff < FP; ++ff) {
         std::string s;
@@ -169,19 +104,6 @@ int main(int argc, char** argv) {
         }
       std::fprintf(f, "};\n");
     }
-    // lift
-    std::fprintf(f, "  template <class R> __device__ static __forceinline__ void lift(const R* __restrict__ p, R* __restrict__ acc) {\n");
-    for (int b = 0; b < B; ++b) {
-      std::string s;
-      bool first = true;
-      for (int i = 0; i < 4; ++i)
-        for (int ff = 0; ff < F; ++ff) {
-          const double v = M.Ft[(i * B + b) * F + ff];
-          if (std::fabs(v) > ZERO_TOL) term(s, first, v, "p[" + std::to_string(i * FP + ff) + "]");
-        }
-      if (!first) std::fprintf(f, "    acc[%d] += %s;\n", b, s.c_str());
-    }
-    std::fprintf(f, "  }\n");
     // ---- W-wave splits (W = 2, 4): wave P of W owns the elementwise modes
     // [mb(W, P), mb(W, P + 1)), computes a contiguous range of stiffness
     // outputs balanced by cost and the trace chunks tchunk(W, P, .).
@@ -361,43 +283,37 @@ int main(int argc, char** argv) {
         }
         std::fprintf(f, "  }\n");
       }
-    // transposed stiffness: full input rows g0, g1, g2 (one per physical
-    // direction), outputs for the wave's own modes, relative to its first
+    // transposed stiffness: full input rows y0, y1, y2 (one per reference
+    // direction: the physical-gradient adjoints combined with G'), outputs
+    // for the wave's own modes (assigned, all entries: see lift)
     for (int W = 2; W <= 4; W += 2)
       for (int vol = 0; vol < 2; ++vol)
         for (int P = 0; P < W; ++P) {
-          const int lo = mbs[W][P], hi = mbs[W][P + 1];
-          std::fprintf(f, "  template <class R> __device__ static __forceinline__ void %s_w%dp%d(const R* g0, const R* g1, const R* g2, const R* __restrict__ G, R* __restrict__ acc) {\n",
+          int nbx = 0;
+          for (int P2 = 0; P2 < W; ++P2) nbx = std::max(nbx, mbs[W][P2 + 1] - mbs[W][P2]);
+          std::fprintf(f, "  template <class R> __device__ static __forceinline__ void %s_w%dp%d(const R* y0, const R* y1, const R* y2, R* __restrict__ out) {\n",
                        vol ? "vol_grad_T" : "ck_grad_T", W, P);
-          for (int c = 0; c < 3; ++c) {
-            for (int b = 0; b < B; ++b) {
-              bool used = false;
-              for (int bb = lo; bb < hi && !used; ++bb) {
-                const double k = vol ? Kd[(c * B + bb) * B + b] : Kd[(c * B + b) * B + bb];
-                used = std::fabs(k) > ZERO_TOL;
-              }
-              if (used)
-                std::fprintf(f, "    const R y%d_%d = G[%d]*g0[%d] + G[%d]*g1[%d] + G[%d]*g2[%d];\n", c, b, 3 * c, b,
-                             3 * c + 1, b, 3 * c + 2, b);
-            }
-            for (int bb = lo; bb < hi; ++bb) {
-              std::string t;
-              bool first = true;
-              for (int b = 0; b < B; ++b) {
-                const double k = vol ? Kd[(c * B + bb) * B + b] : Kd[(c * B + b) * B + bb];
-                if (std::fabs(k) > ZERO_TOL) term(t, first, k, "y" + std::to_string(c) + "_" + std::to_string(b));
-              }
-              if (!first) std::fprintf(f, "    acc[%d] += %s;\n", bb - lo, t.c_str());
-            }
+          for (int lb = 0; lb < nbx; ++lb) {
+            const int bb = mbs[W][P] + lb;
+            std::string t;
+            bool first = true;
+            if (bb < mbs[W][P + 1])
+              for (int c = 0; c < 3; ++c)
+                for (int b = 0; b < B; ++b) {
+                  const double k = vol ? Kd[(c * B + bb) * B + b] : Kd[(c * B + b) * B + bb];
+                  if (std::fabs(k) > ZERO_TOL) term(t, first, k, "y" + std::to_string(c) + "[" + std::to_string(b) + "]");
+                }
+            if (first) t = "R(0)";
+            std::fprintf(f, "    out[%d] = %s;\n", lb, t.c_str());
           }
           std::fprintf(f, "  }\n");
         }
     const char* gp = "const R* __restrict__ d, const R* __restrict__ G, R* g0, R* g1, R* g2";
     dispatch("ck_grad", gp, "d, G, g0, g1, g2");
     dispatch("vol_grad", gp, "d, G, g0, g1, g2");
-    const char* gtp = "const R* g0, const R* g1, const R* g2, const R* __restrict__ G, R* __restrict__ acc";
-    dispatch("ck_grad_T", gtp, "g0, g1, g2, G, acc");
-    dispatch("vol_grad_T", gtp, "g0, g1, g2, G, acc");
+    const char* gtp = "const R* y0, const R* y1, const R* y2, R* __restrict__ out";
+    dispatch("ck_grad_T", gtp, "y0, y1, y2, out");
+    dispatch("vol_grad_T", gtp, "y0, y1, y2, out");
     dispatch("trace", "const R* __restrict__ t, R* __restrict__ p", "t, p");
     dispatch("lift", "const R* __restrict__ p, R* __restrict__ out", "p, out");
     std::fprintf(f, "};\n");
