@@ -286,8 +286,8 @@ int edg_autotune(edg_ctx* ctx, int32_t cycles, edg_plan* best, double* ms_per_cy
  * edg_set_sources and edg_rewind. */
 int edg_set_checkpointing(edg_ctx* ctx, int32_t every_cycles);
 
-/* Back to t = 0: DOFs, buffers and recorded seismograms are zeroed;
- * materials, clusters, time steps, sources and receivers stay.  With
+/* Back to t = 0: DOFs and recorded seismograms are zeroed (the face buffers
+ * are rewritten by the first steps before they are read); materials, clusters, time steps, sources and receivers stay.  With
  * edg_upload_materials (which keeps clusters and time steps) this re-runs a
  * simulation for perturbed materials. */
 int edg_rewind(edg_ctx* ctx);
