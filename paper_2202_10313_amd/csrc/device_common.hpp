@@ -140,8 +140,8 @@ __device__ __forceinline__ void wave_lds_sync() {
 }
 
 // Steps of cluster cl at the processed level (see LevelArgs::clock), dl levels on.
-__device__ __forceinline__ int step_new_of(const LevelArgs& a, int cl, int dl = 0) {
-  return (int)((*a.clock + a.level + dl) >> cl);
+__device__ __forceinline__ int step_new_of(const LevelArgs& a, int cl) {
+  return (int)((*a.clock + a.level) >> cl);
 }
 __device__ __forceinline__ int step_fin_of(const LevelArgs& a, int cl) { return step_new_of(a, cl) - 1; }
 
@@ -150,19 +150,25 @@ __device__ __forceinline__ int step_fin_of(const LevelArgs& a, int cl) { return 
 // range of the (run-major) group space, so neighbouring elements share that
 // XCD's L2.  A bijection for any grid size; so is the optional affine shuffle
 // after it (a debug aid: it changes which groups run together and first).
+// The first a.points workgroups of each row of the grid (a multiple of 8, so the
+// XCDs stay as dealt) take no group.
 __device__ __forceinline__ void group_and_run(const LevelArgs& a, int& g, int& run) {
-  const int nx = gridDim.x;
-  int lin = blockIdx.x + blockIdx.y * nx;
+  const int nx = a.groups;
+  int lin = (int)blockIdx.x - a.points + (int)blockIdx.y * nx;
   if (a.xcd_remap) {
-    const int total = nx * gridDim.y;
+    const int total = nx * a.runs;
     const int q = total / 8, r = total % 8;
     const int x = lin % 8, k = lin / 8;
     lin = x < r ? x * (q + 1) + k : r * (q + 1) + (x - r) * q + k;
   }
   if (a.shuf_mul)   // the host keeps lin * shuf_mul + shuf_add below 2^32
-    lin = (int)(((unsigned)lin * (unsigned)a.shuf_mul + (unsigned)a.shuf_add) % (unsigned)(nx * gridDim.y));
-  g = lin % nx;
-  run = a.run0 + lin / nx;
+    lin = (int)(((unsigned)lin * (unsigned)a.shuf_mul + (unsigned)a.shuf_add) % (unsigned)(nx * a.runs));
+  g = lin;
+  run = a.run0;
+  if (a.runs > 1) {
+    g = lin % nx;
+    run += lin / nx;
+  }
 }
 
 // State arrays are stacked run after run: the pointers of one run.

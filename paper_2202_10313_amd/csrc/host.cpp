@@ -87,7 +87,8 @@ struct edg_ctx {
   };
   std::vector<std::vector<Source>> src_of_run;
   int n_src = 0;
-  DevBuf s_run, s_elem, s_kind, s_par, s_mom, s_phi, s_idet;
+  int src_per_run = 0;              // the most sources of a run
+  DevBuf s_first, s_inc, s_elem, s_kind, s_par, s_mom, s_phi, s_idet;
   // receivers
   int n_rec = 0;
   int64_t rec_ns = 0;
@@ -100,7 +101,7 @@ struct edg_ctx {
   edg_plan plan{0, 0, 0};
   uint64_t shuf_seq = 0;             // launches shuffled so far (EDG_FLAG_SHUFFLE)
   DevBuf dbg;                        // non-finite count and first index (EDG_FLAG_CHECK_FINITE)
-  DevBuf dclock;                     // captured cycles: the level they start from, tickets; a zero (device)
+  DevBuf dclock;                     // captured cycles: two clocks that take turns; a zero (device)
   hipGraphExec_t cycle_exec = nullptr;
   hipGraph_t cycle_graph = nullptr;
 
@@ -649,34 +650,14 @@ int64_t locate(edg_ctx* c, const double* x, double xi_sorted[3]) {
   return -1;
 }
 
-template <class R, int O, int M>
-struct Launch {
-  static int level(const KPtrs& p, const LevelArgs& a, int runs, hipStream_t s) {
-    return launch_level<R, O, M>(p, a, runs, s);
-  }
-  static int pts(const KPtrs& p, const LevelArgs& a, const PointArgs& q, hipStream_t s) {
-    return launch_points<R, O, M>(p, a, q, s);
-  }
-};
+typedef int (*LevelFn)(const KPtrs&, LevelArgs, const PointArgs&, int, hipStream_t);
 
-typedef int (*LevelFn)(const KPtrs&, const LevelArgs&, int, hipStream_t);
-typedef int (*PtsFn)(const KPtrs&, const LevelArgs&, const PointArgs&, hipStream_t);
-
-struct Fns {
-  LevelFn level = nullptr;
-  PtsFn pts = nullptr;
-};
-
-Fns pick(int fp64, int O, int M) {
-  Fns f;
-#define EDG_PICK(R, OO, MM)                                                         \
-  if ((std::is_same<R, double>::value == (fp64 != 0)) && O == OO && M == MM) {      \
-    f.level = &Launch<R, OO, MM>::level;                                            \
-    f.pts = &Launch<R, OO, MM>::pts;                                                \
-  }
+LevelFn pick(int fp64, int O, int M) {
+#define EDG_PICK(R, OO, MM) \
+  if ((std::is_same<R, double>::value == (fp64 != 0)) && O == OO && M == MM) return &launch_level<R, OO, MM>;
   EDG_FOR_EACH_VARIANT(EDG_PICK)
 #undef EDG_PICK
-  return f;
+  return nullptr;
 }
 
 KPtrs kptrs(const edg_ctx* c) {
@@ -808,12 +789,12 @@ int check_finite(edg_ctx* c) {
 }
 
 // one LTS level for all runs, in chunks of plan.run_chunk runs per launch
-int launch_runs(edg_ctx* c, const Fns& fn, const KPtrs& p, LevelArgs a) {
+int launch_runs(edg_ctx* c, LevelFn fn, const KPtrs& p, LevelArgs a, const PointArgs& pt) {
   const int chunk = c->plan.run_chunk > 0 ? std::min(c->plan.run_chunk, c->runs) : c->runs;
   for (int r0 = 0; r0 < c->runs; r0 += chunk) {
     a.run0 = r0;
     shuffle_args(c, a, std::min(chunk, c->runs - r0));
-    const int rc = fn.level(p, a, std::min(chunk, c->runs - r0), c->stream);
+    const int rc = fn(p, a, pt, std::min(chunk, c->runs - r0), c->stream);
     if (rc) return fail(c, EDG_EHIP, std::string("level kernel launch: ") + hipGetErrorString((hipError_t)rc));
   }
   return 0;
@@ -847,17 +828,17 @@ void drop_graph(edg_ctx* c) {
   c->cycle_graph = nullptr;
 }
 
-int launch_timed(edg_ctx* c, const Fns& fn, const KPtrs& p, const LevelArgs& a, int64_t upd) {
+int launch_timed(edg_ctx* c, LevelFn fn, const KPtrs& p, const LevelArgs& a, const PointArgs& pt, int64_t upd) {
   int rc;
   if ((rc = timed_begin(c, upd, 1))) return rc;
-  if ((rc = launch_runs(c, fn, p, a))) return rc;
+  if ((rc = launch_runs(c, fn, p, a, pt))) return rc;
   return timed_end(c);
 }
 
 }  // namespace
 
 edg_ctx::~edg_ctx() {
-  for (DevBuf* b : {&Qe, &Qa, &P, &FI, &T1, &T2, &T3, &RecD, &s_run, &s_elem, &s_kind, &s_par, &s_mom, &s_phi,
+  for (DevBuf* b : {&Qe, &Qa, &P, &FI, &T1, &T2, &T3, &RecD, &s_first, &s_inc, &s_elem, &s_kind, &s_par, &s_mom, &s_phi,
                     &s_idet, &r_elem, &r_slot, &r_phi, &r_out, &dclock, &aLe, &aLa, &aS0, &aS3, &aDe,
                     &agacc, &arecDb, &aseis, &ahist, &afinal, &amat, &agrad, &dmat, &dflag, &d_i2u, &d_nbr, &dbg, &d_u2i, &d_code, &d_mats, &dofstage})
     dev_free(*b);
@@ -883,7 +864,7 @@ int edg_create(const edg_config* cfg, edg_ctx** out) {
   if (cfg->n_runs < 1 || cfg->n_runs > MAX_RUNS) return EDG_EINVAL;
   if (cfg->n_clusters < 1 || cfg->n_clusters > MAX_CLUSTERS) return EDG_EINVAL;
   if (!(cfg->cfl > 0) || cfg->lambda > 1.0 || (cfg->lambda > 0 && cfg->lambda <= 0.5)) return EDG_EINVAL;
-  if (!pick(cfg->fp64, cfg->order, cfg->mechanisms).level) return EDG_EINVAL;
+  if (!pick(cfg->fp64, cfg->order, cfg->mechanisms)) return EDG_EINVAL;
   if (cfg->flags & ~(EDG_FLAG_GRAPH | EDG_FLAG_POISON | EDG_FLAG_SHUFFLE | EDG_FLAG_CHECK_FINITE |
                      EDG_FLAG_POISON_EARLY))
     return EDG_EINVAL;
@@ -1298,14 +1279,21 @@ int edg_set_sources(edg_ctx* c, int32_t run, int64_t n, const double* xyz, const
     src.phi = eval_basis(c->O, xi);
     list.push_back(std::move(src));
   }
+  std::stable_sort(list.begin(), list.end(), [](const auto& x, const auto& y) { return x.elem < y.elem; });
   c->src_of_run[run] = std::move(list);
   drop_graph(c);
-  // the device list holds the sources of every run
-  std::vector<int> rn, el, kd;
+  // the device list holds the sources of every run, by element, and where each
+  // element group's begin
+  std::vector<int> el, kd, first;
   std::vector<double> pr, mo, phi, idet;
-  for (int r = 0; r < c->runs; ++r)
+  size_t per_run = 0;
+  for (int r = 0; r < c->runs; ++r) {
+    per_run = std::max(per_run, c->src_of_run[r].size());
+    for (int64_t g = 0, i = 0; g <= c->G; ++g) {
+      while (i < (int64_t)c->src_of_run[r].size() && c->src_of_run[r][i].elem < g * EPW) ++i;
+      first.push_back((int)(el.size() + i));
+    }
     for (const auto& src : c->src_of_run[r]) {
-      rn.push_back(r);
       el.push_back(src.elem);
       kd.push_back(src.kind);
       pr.insert(pr.end(), src.par, src.par + 2);
@@ -1313,9 +1301,12 @@ int edg_set_sources(edg_ctx* c, int32_t run, int64_t n, const double* xyz, const
       phi.insert(phi.end(), src.phi.begin(), src.phi.end());
       idet.push_back(src.idet);
     }
-  const size_t ns = rn.size();
+  }
+  const size_t ns = el.size();
   int rc;
-  if ((rc = dev_upload(c, c->s_run, rn.data(), ns * sizeof(int)))) return rc;
+  c->n_src = 0;   // (none until all of the list is there)
+  if ((rc = dev_upload(c, c->s_first, first.data(), ns ? first.size() * sizeof(int) : 0))) return rc;
+  if ((rc = dev_alloc(c, c->s_inc, 2 * ns * 6 * c->B * (c->cfg.fp64 ? sizeof(double) : sizeof(float))))) return rc;
   if ((rc = dev_upload(c, c->s_elem, el.data(), ns * sizeof(int)))) return rc;
   if ((rc = dev_upload(c, c->s_kind, kd.data(), ns * sizeof(int)))) return rc;
   if ((rc = dev_upload(c, c->s_par, pr.data(), pr.size() * sizeof(double)))) return rc;
@@ -1323,6 +1314,7 @@ int edg_set_sources(edg_ctx* c, int32_t run, int64_t n, const double* xyz, const
   if ((rc = dev_upload(c, c->s_phi, phi.data(), phi.size() * sizeof(double)))) return rc;
   if ((rc = dev_upload(c, c->s_idet, idet.data(), ns * sizeof(double)))) return rc;
   c->n_src = (int)ns;
+  c->src_per_run = (int)per_run;
   return EDG_OK;
 }
 
@@ -1340,7 +1332,10 @@ int edg_set_receivers(edg_ctx* c, int64_t n, const double* xyz, double dt_sample
     if (k < 0) return fail(c, EDG_EINVAL, "receiver " + std::to_string(r) + " is outside the mesh");
     const int64_t ki = c->user_to_internal[k];
     el[r] = (int)ki;
-    if (rs_slot[ki] < 0) rs_slot[ki] = nslots++;
+    if (rs_slot[ki] < 0) {
+      rs_slot[ki] = nslots;
+      nslots += ki < c->cl_end[0] ? 2 : 1;   // (see KPtrs::recD)
+    }
     slot[r] = rs_slot[ki];
     auto v = eval_basis(c->O, xi);
     std::copy(v.begin(), v.end(), phi.begin() + r * c->B);
@@ -1369,32 +1364,36 @@ int edg_set_receivers(edg_ctx* c, int64_t n, const double* xyz, double dt_sample
 namespace {
 
 struct AdvanceArgs {
-  Fns fn;
+  LevelFn fn;
   KPtrs p;
-  SrcArgs sa;
-  RecArgs ra;
+  PointArgs pt;
 };
 
 AdvanceArgs advance_args(edg_ctx* c) {
   AdvanceArgs A;
   A.fn = pick(c->cfg.fp64, c->O, c->M);
   A.p = kptrs(c);
-  A.sa.n = c->n_src;
-  A.sa.run = (const int*)c->s_run.p;
-  A.sa.elem = (const int*)c->s_elem.p;
-  A.sa.kind = (const int*)c->s_kind.p;
-  A.sa.par = (const double*)c->s_par.p;
-  A.sa.moment = (const double*)c->s_mom.p;
-  A.sa.phi = (const double*)c->s_phi.p;
-  A.sa.inv_det = (const double*)c->s_idet.p;
-  A.ra.n = c->n_rec;
-  A.ra.elem = (const int*)c->r_elem.p;
-  A.ra.slot = (const int*)c->r_slot.p;
-  A.ra.phi = (const double*)c->r_phi.p;
-  A.ra.dt_sample = c->rec_dt;
-  A.ra.ns = c->rec_ns;
-  A.ra.runs = c->runs;
-  A.ra.out = (double*)c->r_out.p;
+  SrcArgs& sa = A.pt.s;
+  sa.n = c->n_src;
+  sa.per_run = c->src_per_run;
+  sa.first = (const int*)(c->n_src ? c->s_first.p : (char*)c->dclock.p + 2 * sizeof(long long));
+  sa.row = c->n_src ? (int)c->G + 1 : 0;
+  sa.col = c->n_src ? 1 : 0;
+  sa.elem = (const int*)c->s_elem.p;
+  sa.kind = (const int*)c->s_kind.p;
+  sa.par = (const double*)c->s_par.p;
+  sa.moment = (const double*)c->s_mom.p;
+  sa.phi = (const double*)c->s_phi.p;
+  sa.inv_det = (const double*)c->s_idet.p;
+  sa.inc = c->s_inc.p;
+  RecArgs& ra = A.pt.r;
+  ra.n = c->n_rec;
+  ra.elem = (const int*)c->r_elem.p;
+  ra.slot = (const int*)c->r_slot.p;
+  ra.phi = (const double*)c->r_phi.p;
+  ra.dt_sample = c->rec_dt;
+  ra.ns = c->rec_ns;
+  ra.out = (double*)c->r_out.p;
   return A;
 }
 
@@ -1412,47 +1411,34 @@ int64_t level_updates(const edg_ctx* c, int lmax) {
   return u;
 }
 
-// The receivers of level j's predictions (if asked), then the sources of the
-// steps that end at level j + 1: one launch (see PointArgs).  a: level j's
-// arguments.
-int launch_points_after(edg_ctx* c, const AdvanceArgs& A, const KPtrs& p, const LevelArgs& a, int64_t j, bool receivers,
-                        int64_t tick = 0) {
-  PointArgs q;
-  q.r = A.ra;
-  if (!receivers) q.r.n = 0;
-  q.s = A.sa;
-  q.src_end = c->cl_end[level_lmax(c, j + 1)];
-  q.tick = tick ? (long long*)c->dclock.p : nullptr;
-  q.tick_by = tick;
-  const int rc = A.fn.pts(p, a, q, c->stream);
-  return rc ? fail(c, EDG_EHIP, std::string("point kernel: ") + hipGetErrorString((hipError_t)rc)) : 0;
-}
-
 // The launches of one LTS cycle (Sec. V-B: per finest level the fused
-// finish-and-predict launch, then the receivers of the new predictions and the
-// sources of the steps that end at the next level), j0 levels after the level
-// the arguments count from.  `last`: the final level only finishes (no
-// prediction is needed after the advance).  `timed`: per-level events.
-// `captured`: levels count from the device clock, which the cycle's last
-// launch moves on.
-int emit_cycle(edg_ctx* c, const AdvanceArgs& A, int64_t j0, bool last, bool timed, bool captured) {
+// finish-and-predict launch, with the points beside it, see PointArgs), j0
+// levels after the level the arguments count from.  `last`: the final level
+// only finishes (no prediction is needed after the advance).  `timed`:
+// per-level events.  clk >= 0: a captured cycle, its levels count from the
+// device clock clk, and its last launch sets the other one.
+int emit_cycle(edg_ctx* c, const AdvanceArgs& A, int64_t j0, bool last, bool timed, int clk) {
   const int64_t per = (int64_t)1 << (c->cfg.n_clusters - 1);
   int rc;
   for (int64_t j = 1; j <= per; ++j) {
     const int lmax = level_lmax(c, j);
     LevelArgs a = base_args(c);
-    if (captured) a.clock = (const long long*)c->dclock.p;
-    a.level = (captured ? 0 : c->level + j0) + j;
+    if (clk >= 0) {
+      a.clock = (const long long*)c->dclock.p + clk;
+      if (j == per) {
+        a.next = (long long*)c->dclock.p + (1 - clk);
+        a.tick = per;
+      }
+    }
+    a.level = (clk >= 0 ? 0 : c->level + j0) + j;
     a.end = c->cl_end[lmax];
-    const bool fin = last && j == per;
-    a.kind = fin ? KIND_NEIGHBOR : KIND_FUSED;
+    a.kind = last && j == per ? KIND_NEIGHBOR : KIND_FUSED;
     if (timed) {
-      if ((rc = launch_timed(c, A.fn, A.p, a, level_updates(c, lmax)))) return rc;
-    } else if ((rc = launch_runs(c, A.fn, A.p, a))) {
+      if ((rc = launch_timed(c, A.fn, A.p, a, A.pt, level_updates(c, lmax)))) return rc;
+    } else if ((rc = launch_runs(c, A.fn, A.p, a, A.pt))) {
       return rc;
     }
     if ((rc = poison_after(c, A.p, a))) return rc;
-    if (!fin && (rc = launch_points_after(c, A, A.p, a, j, true, captured && j == per ? per : 0))) return rc;
   }
   return 0;
 }
@@ -1464,12 +1450,13 @@ int64_t cycle_updates(const edg_ctx* c) {
   return u;
 }
 
-// capture one full (non-final) cycle as a graph: only kernel launches, no
-// memory set or copy nodes
-int capture_cycle(edg_ctx* c, const AdvanceArgs& A) {
+// capture two full (non-final) cycles as a graph, the second on the clock that
+// the first sets and back: only kernel launches, no memory set or copy nodes
+int capture_cycles(edg_ctx* c, const AdvanceArgs& A) {
   drop_graph(c);
   HIPCHK(c, hipStreamBeginCapture(c->stream, hipStreamCaptureModeThreadLocal));
-  const int rc = emit_cycle(c, A, 0, false, false, true);
+  int rc = 0;
+  for (int clk = 0; clk < 2 && !rc; ++clk) rc = emit_cycle(c, A, 0, false, false, clk);
   hipGraph_t g = nullptr;
   const hipError_t e = hipStreamEndCapture(c->stream, &g);
   if (rc) {
@@ -1518,23 +1505,21 @@ int advance_cycles(edg_ctx* c, int64_t nc, char* traces = nullptr) {
   a.end = c->cl_end[Nc - 1];
   int rc = poison_all(c, A.p);
   if (rc) return rc;
-  rc = timed ? launch_timed(c, A.fn, A.p, a, 0) : launch_runs(c, A.fn, A.p, a);
+  rc = timed ? launch_timed(c, A.fn, A.p, a, A.pt, 0) : launch_runs(c, A.fn, A.p, a, A.pt);
   if (rc) return rc;
-  if ((rc = launch_points_after(c, A, A.p, a, 0, true))) return rc;
-  if (graph && nc > 1 && (rc = launch_clock((long long*)c->dclock.p, (long long)c->level, 0, c->stream)))
+  // pairs of cycles that are not the last replay the graph
+  const int64_t pairs = graph ? (nc - 1) / 2 : 0;
+  if (pairs > 0 && (rc = launch_clock((long long*)c->dclock.p, (long long)c->level, c->stream)))
     return fail(c, EDG_EHIP, std::string("clock kernel: ") + hipGetErrorString((hipError_t)rc));
-  for (int64_t k = 0; k < nc; ++k) {
-    const bool last = k + 1 == nc;
-    if (graph && !last) {
-      if (!c->cycle_exec && (rc = capture_cycle(c, A))) return rc;
-      if ((rc = timed_begin(c, cycle_updates(c), (int)per))) return rc;
-      HIPCHK(c, hipGraphLaunch(c->cycle_exec, c->stream));
-      if ((rc = timed_end(c))) return rc;
-    } else if ((rc = emit_cycle(c, A, k * per, last, timed, false))) {
-      return rc;
-    }
-    c->updates += cycle_updates(c);
+  for (int64_t k = 0; k < pairs; ++k) {
+    if (!c->cycle_exec && (rc = capture_cycles(c, A))) return rc;
+    if ((rc = timed_begin(c, 2 * cycle_updates(c), 2 * (int)per))) return rc;
+    HIPCHK(c, hipGraphLaunch(c->cycle_exec, c->stream));
+    if ((rc = timed_end(c))) return rc;
   }
+  for (int64_t k = 2 * pairs; k < nc; ++k)
+    if ((rc = emit_cycle(c, A, k * per, k + 1 == nc, timed, -1))) return rc;
+  c->updates += nc * cycle_updates(c);
   c->level += nc * per;
   HIPCHK(c, hipStreamSynchronize(c->stream));
   if ((rc = check_finite(c))) return rc;
@@ -1630,6 +1615,8 @@ int run_recorded_levels(edg_ctx* c, const AdvanceArgs& A, const KPtrs& p, int64_
   };
   int rc;
   LevelArgs a = base_args(c);
+  PointArgs pt = A.pt;
+  if (!own) pt.r.n = 0;
   a.run0 = 0;
   if ((rc = poison_all(c, p))) return rc;
   for (int64_t j = 0; j <= (own ? J : J - 1); ++j) {
@@ -1640,9 +1627,8 @@ int run_recorded_levels(edg_ctx* c, const AdvanceArgs& A, const KPtrs& p, int64_
     a.rec_e = j < J ? (void*)hist_rec_e(c, j) : nullptr;
     a.rec_a = (j < J && wa) ? (void*)hist_rec_a(c, j) : nullptr;
     shuffle_args(c, a, 1);
-    if ((rc = chk(A.fn.level(p, a, 1, c->stream), "level kernel"))) return rc;
+    if ((rc = chk(A.fn(p, a, pt, 1, c->stream), "level kernel"))) return rc;
     if ((rc = poison_after(c, p, a))) return rc;
-    if (j < (own ? J : J - 1) && (rc = launch_points_after(c, A, p, a, j, own))) return rc;
   }
   return 0;
 }
@@ -1880,7 +1866,7 @@ int adjoint_sweep(edg_ctx* c, const double* dj_seis, const double* dj_q, double*
   HIPCHK(c, hipStreamSynchronize(c->stream));
   // the replays run on a state of their own, so the context's DOFs stay
   // those of the final time; one run at a time, so the run stride of the
-  // state is zero (the sources of run r land in the same state)
+  // state is zero
   char* rep_state = (char*)c->afinal.p;
 
   const AdvanceArgs A0 = advance_args(c);
@@ -1914,7 +1900,7 @@ int adjoint_sweep(edg_ctx* c, const double* dj_seis, const double* dj_q, double*
       a.kind = j == J ? KIND_ADJ_UPDATE : j > 0 ? KIND_ADJ_FUSED : KIND_ADJ_PREDICT;
       if (j < J) {
         if (c->n_rec > 0 && dj_seis &&
-            (e = chk(launch_receivers_adj<R, O, M>(p, ad, a, A0.ra, seis_b, c->stream), "receiver adjoint kernel")))
+            (e = chk(launch_receivers_adj<R, O, M>(p, ad, a, A0.pt.r, seis_b, c->stream), "receiver adjoint kernel")))
           return e;
         ad.Se = hist_e(j);
         ad.Sa = hist_a(j);
@@ -1940,24 +1926,10 @@ int adjoint_sweep(edg_ctx* c, const double* dj_seis, const double* dj_q, double*
     }
   } graphs_guard{graphs};
   const size_t nqb = (size_t)c->K * c->NQ * c->B, nsb = (size_t)c->n_rec * c->rec_ns * LPE;
-  size_t src_off = 0;
   for (int run = 0; run < c->runs; ++run) {
-    // this run's sources (the device list holds the runs in order)
+    // this run's sources (a replay's launches have one run, the first)
     AdvanceArgs A = A0;
-    const size_t ns_run = c->src_of_run[run].size();
-    if (ns_run > 0) {
-      A.sa.n = (int)ns_run;
-      A.sa.run += src_off;
-      A.sa.elem += src_off;
-      A.sa.kind += src_off;
-      A.sa.par += 2 * src_off;
-      A.sa.moment += 6 * src_off;
-      A.sa.phi += (size_t)c->B * src_off;
-      A.sa.inv_det += src_off;
-    } else {
-      A.sa.n = 0;
-    }
-    src_off += ns_run;
+    A.pt.s.first += (size_t)run * A.pt.s.row;
     for (DevBuf* b : {&c->aLe, &c->aLa, &c->aseis}) HIPCHK(c, hipMemsetAsync(b->p, 0, b->bytes, c->stream));
     HIPCHK(c, hipStreamSynchronize(c->stream));
     if (dj_q) {
@@ -2013,7 +1985,7 @@ int adjoint_sweep(edg_ctx* c, const double* dj_seis, const double* dj_q, double*
           if (e != hipSuccess) return fail(c, EDG_EHIP, std::string("adjoint graph capture: ") + hipGetErrorString(e));
           HIPCHK(c, hipGraphInstantiate(&graphs[gi].x, graphs[gi].g, nullptr, nullptr, 0));
         }
-        if ((rc = chk(launch_clock((long long*)c->dclock.p, (long long)L0, 0, c->stream), "clock kernel"))) return rc;
+        if ((rc = chk(launch_clock((long long*)c->dclock.p, (long long)L0, c->stream), "clock kernel"))) return rc;
         HIPCHK(c, hipGraphLaunch(graphs[gi].x, c->stream));
       } else if ((rc = backward(a, L0, J))) {
         return rc;

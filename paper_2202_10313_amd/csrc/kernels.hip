@@ -137,6 +137,98 @@ constexpr int level_occ() {
   return sizeof(R) == 8 ? (O >= 4 ? 1 : 2) : (O <= 3 || (W == 4 && !(O == 5 && M > 0))) ? 4 : 2;
 }
 
+// Point sources: Q[stress] += -M phi(x_s) / |det J| * (S(t1) - S(t0)) for the
+// step of the source's element.
+__device__ __forceinline__ double stf_antiderivative(int kind, double p0, double p1, double t) {
+  if (kind == 0) {  // Ricker moment rate: S = (t - t0) exp(-a (t - t0)^2), a = (pi fc)^2
+    const double a = (M_PI * p0) * (M_PI * p0);
+    const double tau = t - p1;
+    return tau * exp(-a * tau * tau);
+  }
+  // Hann moment rate on [t0, t0 + T]
+  const double tau = t - p0;
+  if (tau <= 0.0) return 0.0;
+  if (tau >= p1) return 1.0;
+  return (tau - p1 / (2.0 * M_PI) * sin(2.0 * M_PI * tau / p1)) / p1;
+}
+
+// The points of a level launch (see PointArgs), one wave each, beside the element
+// groups.  As a launch of their own between two levels they cost 4.9 us per
+// level of nothing but latency (three launches before that: 12); here nothing
+// waits for them, since a sample reads the derivatives of the step before and a
+// source is evaluated one level ahead.  Measured (us per shot): 5k tets O = 4 m=3
+// 1,095 -> 885, five-cluster basin 8k O = 5 1,237 -> 1,105, 62k 4,985 -> 4,870,
+// 997k 20,270 -> 20,160; a mesh without points pays 0.4 us a level for the branch
+// and the longer argument block (plane wave check 642 -> 666).
+// vals: LDS of O x 9 doubles per wave.
+template <class R, int O, int KIND, int W>
+__device__ __forceinline__ void level_points(const KPtrs& p, const LevelArgs& a, const PointArgs& pt, double* vals) {
+  constexpr int B = edg_gen::Ref<O>::B, D = O * LPE;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int item = (int)blockIdx.x * W + w, run = a.run0 + (int)blockIdx.y;
+  const long long level = *a.clock + a.level;
+  const int n_rec = KIND != KIND_PREDICT ? pt.r.n : 0;
+  if (item < n_rec) {
+    // a receiver: evaluate the Taylor expansion predicted at level - 1 at the
+    // sample times in its step, its lanes (d, q) forming the O x 9 derivative
+    // values before nine of them sample
+    const RecArgs& r = pt.r;
+    const int elem = r.elem[item], cl = cluster_of(a, elem);
+    if ((level - 1) & ((1ll << cl) - 1)) return;    // no step started there
+    const double dt = a.dt[cl];
+    const int n = (int)((level - 1) >> cl);
+    const double t0 = (double)n * dt, t1 = (double)(n + 1) * dt;
+    // step n takes the samples in [t0 - eps, t1 - eps), eps = 1e-9 dt: a sample
+    // on (or within rounding of) a step boundary belongs to the step that
+    // starts there, whichever way the two sides round the boundary
+    const double eps = 1e-9 * dt, lo = t0 - eps, hi = t1 - eps;
+    long long s = (long long)floor(lo / r.dt_sample) - 1;
+    if (s < 0) s = 0;
+    while (s < r.ns && (double)s * r.dt_sample < lo) ++s;
+    if (!(s < r.ns && (double)s * r.dt_sample < hi)) return;   // (uniform over the wave)
+    double* const v = vals + w * D;
+    if (lane < D) {
+      const R* x = reinterpret_cast<const R*>(p.recD) + (size_t)run * p.run_recd +
+                   ((size_t)(r.slot[item] + (cl == 0 ? n & 1 : 0)) * D + lane) * B;
+      const double* phi = r.phi + (size_t)item * B;
+      double acc = 0.0;
+#pragma unroll 5
+      for (int b = 0; b < B; ++b) acc += (double)x[b] * phi[b];
+      v[lane] = acc;
+    }
+    wave_lds_sync();
+    double* const out = r.out + ((size_t)run * r.n + item) * r.ns * LPE;
+    if (lane < LPE)
+      for (; s < r.ns && (double)s * r.dt_sample < hi; ++s) {
+        const double x = (double)s * r.dt_sample - t0;
+        double acc = 0.0, pw = 1.0, fact = 1.0;
+#pragma unroll
+        for (int d = 0; d < O; ++d) {
+          acc += pw / fact * v[d * LPE + lane];
+          pw *= x;
+          fact *= (double)(d + 1);
+        }
+        out[s * LPE + lane] = acc;
+      }
+  } else if (KIND != KIND_NEIGHBOR && pt.s.n > 0) {
+    // a source of a step that ends at level + 1
+    const SrcArgs& s = pt.s;
+    const int* const first = s.first + (size_t)run * s.row;
+    const int src = first[0] + (item - n_rec);
+    if (src >= first[s.row - 1]) return;
+    const int cl = cluster_of(a, s.elem[src]);
+    if ((level + 1) & ((1ll << cl) - 1)) return;
+    const double dt = a.dt[cl];
+    const int n = (int)((level + 1) >> cl) - 1;
+    const double t0 = (double)n * dt, t1 = (double)(n + 1) * dt;
+    const double f = stf_antiderivative(s.kind[src], s.par[2 * src], s.par[2 * src + 1], t1) -
+                     stf_antiderivative(s.kind[src], s.par[2 * src], s.par[2 * src + 1], t0);
+    R* const inc = reinterpret_cast<R*>(s.inc) + ((size_t)((level + 1) & 1) * s.n + src) * (6 * B);
+    for (int k = lane; k < 6 * B; k += 64)
+      inc[k] = R(-s.moment[6 * src + k / B] * s.phi[(size_t)src * B + k % B] * s.inv_det[src] * f);
+  }
+}
+
 // KIND is the launch kind (KIND_PREDICT, KIND_FUSED, KIND_NEIGHBOR) as a
 // template parameter: one code path per kernel keeps the register allocation
 // of the fused path free of the neighbour-only exit.  TM: the traces of faces
@@ -144,7 +236,7 @@ constexpr int level_occ() {
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 template <class R, int O, int M, int KIND, int W, bool TM = false>
 __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(level_occ<R, O, M, W>(), 4)))
-void k_level(KPtrs p, LevelArgs a) {
+void k_level(LevelArgs a, KPtrs p, PointArgs pt) {
   using RF = edg_gen::Ref<O>;
   using L = LevelLds<R, O, M>;
   constexpr int B = RF::B, F = RF::F, FP = RF::FP;
@@ -154,7 +246,7 @@ void k_level(KPtrs p, LevelArgs a) {
   constexpr int NTC = RF::template ntc<W>, NCH = FP / 4;   // trace chunks per wave and per face
   constexpr int JW = (NBX + LPE - 1) / LPE;      // owned memory modes per lane
   constexpr int JB = (B + LPE - 1) / LPE;        // memory-variable layout
-  __shared__ R lds[L::TOTAL];
+  __shared__ __align__(16) R lds[L::TOTAL];
   // per element and face: normal, area ratio, neighbour impedances (the face
   // words of the parameter table; a boundary face holds the element's own),
   // the inverse sums of both sides' impedances and the boundary kind, staged
@@ -164,6 +256,12 @@ void k_level(KPtrs p, LevelArgs a) {
   // per element: flags and own B3 slot, for the matrix-core trace's exports
   __shared__ int tme[TM ? EPW * 2 : 1];
 
+  if ((int)blockIdx.x < a.points) {
+    static_assert(W * O * LPE * sizeof(double) <= L::TOTAL * sizeof(R) && O * LPE <= 64, "a wave per point");
+    level_points<R, O, KIND, W>(p, a, pt, reinterpret_cast<double*>(lds));
+    return;
+  }
+
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // wave (uniform)
   const int lane = threadIdx.x & 63;
   const int e = lane / LPE, r = lane % LPE;
@@ -172,6 +270,13 @@ void k_level(KPtrs p, LevelArgs a) {
   int g, run;
   group_and_run(a, g, run);
   select_run<R>(p, run);
+  // the group's sources (asked for here: their count is needed in mid-kernel)
+  int src0 = 0, src1 = 0;
+  if constexpr (KIND != KIND_PREDICT) {
+    const int* const first = pt.s.first + (size_t)run * pt.s.row + (size_t)g * pt.s.col;
+    src0 = first[0];
+    src1 = first[1];
+  }
   const int elem = g * EPW + ec;
   const int cl = cluster_of(a, g * EPW);        // one cluster per workgroup (uniform)
   const bool valid = (e < EPW) && (elem < a.cl_vend[cl]);
@@ -388,6 +493,16 @@ void k_level(KPtrs p, LevelArgs a) {
         for (int f = 0; f < FP; ++f) pf[i * FP + f] = fac[((i * 2 + 0) * LPE + q) * FS + f];
       RF::template lift_w<W>(w, pf, da);
     }
+    // the group's sources, if any (uniform)
+    for (int src = src0; src < src1; ++src) {
+      const SrcArgs& s = pt.s;
+      const R* const inc = reinterpret_cast<const R*>(s.inc) +
+                           ((size_t)((*a.clock + a.level) & 1) * s.n + src) * (6 * B) + q * B + base;
+      if (is_stress && s.elem[src] == elem)   // (lane 63 as lane 54: both write the exchange)
+#pragma unroll
+        for (int lb = 0; lb < NBX; ++lb)
+          if (has(lb)) qe[lb] += inc[lb];
+    }
     if (M > 0) {
       // the stress lanes hold the lifted strain-rate rows: the memory
       // variables of a mode take them (times omega) in the lane that owns the
@@ -492,7 +607,8 @@ void k_level(KPtrs p, LevelArgs a) {
       if (has(lb)) rx[q * BS + base + lb] = qe[lb];
     }
   }
-  R* const rd = reinterpret_cast<R*>(p.recD) + ((size_t)(rec_slot >= 0 ? rec_slot : 0) * O * LPE + q) * B + base;
+  R* const rd = reinterpret_cast<R*>(p.recD) +
+                ((size_t)(rec_slot >= 0 ? rec_slot + (cl == 0 ? nn & 1 : 0) : 0) * O * LPE + q) * B + base;
   if (rec_slot >= 0 && valid)
 #pragma unroll
     for (int lb = 0; lb < NBX; ++lb)
@@ -756,6 +872,8 @@ void k_level(KPtrs p, LevelArgs a) {
     }
   }
 
+  if (KIND == KIND_FUSED && a.next != nullptr && g == 0 && run == a.run0 && threadIdx.x == 0)
+    *a.next = *a.clock + a.tick;
   if (valid) {
     const int sl = fresh(slot);
     const int msl = RF::template nines<W> ? sl : fresh(mslot);
@@ -775,121 +893,14 @@ void k_level(KPtrs p, LevelArgs a) {
   }
 }
 
-// point sources: Q[stress] += -M phi(x_s) / |det J| * (S(t1) - S(t0)) for the
-// step of the source's element that ends at this level
-__device__ double stf_antiderivative(int kind, double p0, double p1, double t) {
-  if (kind == 0) {  // Ricker moment rate: S = (t - t0) exp(-a (t - t0)^2), a = (pi fc)^2
-    const double a = (M_PI * p0) * (M_PI * p0);
-    const double tau = t - p1;
-    return tau * exp(-a * tau * tau);
-  }
-  // Hann moment rate on [t0, t0 + T]
-  const double tau = t - p0;
-  if (tau <= 0.0) return 0.0;
-  if (tau >= p1) return 1.0;
-  return (tau - p1 / (2.0 * M_PI) * sin(2.0 * M_PI * tau / p1)) / p1;
-}
-
-// The points of a mesh between two levels (see PointArgs), one launch: sources
-// and receivers touch different data, and at small meshes each launch costs as
-// much as a sixth of a level (5k tets, O = 4: level 17 us, source and receiver
-// kernels 3.4 and 4.5 us, clock tick 3.9 us per cycle when they ran apart).
-// Blocks [0, rec_blocks): one wave per receiver and run, its lanes (d, q)
-// forming the O x 9 derivative values before nine of them sample; the others:
-// one block per source.
-constexpr int PT_WAVES = 4;
-template <class R, int O, int M>
-__global__ __launch_bounds__(64 * PT_WAVES) void k_points(KPtrs p, LevelArgs a, PointArgs pt, int rec_blocks) {
-  constexpr int B = edg_gen::Ref<O>::B;
-  __shared__ double vals[PT_WAVES][O * LPE];
-  if ((int)blockIdx.x < rec_blocks) {
-    // receivers: evaluate the predicted Taylor expansion at the sample times in
-    // [t^n, t^{n+1}) of every receiver whose element was predicted at this level
-    const RecArgs& r = pt.r;
-    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int item = (int)blockIdx.x * PT_WAVES + w;
-    const int run = item / r.n, rec = item % r.n;
-    if (run < r.runs && r.elem[rec] < a.end) {
-      select_run<R>(p, run);
-      double* const out = r.out + (size_t)run * r.n * r.ns * LPE;
-      const int cl = cluster_of(a, r.elem[rec]);
-      const double dt = a.dt[cl];
-      const int n = step_new_of(a, cl);
-      const double t0 = (double)n * dt, t1 = (double)(n + 1) * dt;
-      // step n takes the samples in [t0 - eps, t1 - eps), eps = 1e-9 dt: a sample
-      // on (or within rounding of) a step boundary belongs to the step that
-      // starts there, whichever way the two sides round the boundary
-      const double eps = 1e-9 * dt, lo = t0 - eps, hi = t1 - eps;
-      long long s = (long long)floor(lo / r.dt_sample) - 1;
-      if (s < 0) s = 0;
-      while (s < r.ns && (double)s * r.dt_sample < lo) ++s;
-      if (s < r.ns && (double)s * r.dt_sample < hi) {   // (uniform over the wave)
-        if (lane < O * LPE) {
-          const R* D = reinterpret_cast<const R*>(p.recD) + ((size_t)r.slot[rec] * O * LPE + lane) * B;
-          const double* phi = r.phi + (size_t)rec * B;
-          double v = 0.0;
-          for (int b = 0; b < B; ++b) v += (double)D[b] * phi[b];
-          vals[w][lane] = v;
-        }
-        wave_lds_sync();
-        if (lane < LPE)
-          for (; s < r.ns && (double)s * r.dt_sample < hi; ++s) {
-            const double x = (double)s * r.dt_sample - t0;
-            double acc = 0.0, pw = 1.0, fact = 1.0;
-#pragma unroll
-            for (int d = 0; d < O; ++d) {
-              acc += pw / fact * vals[w][d * LPE + lane];
-              pw *= x;
-              fact *= (double)(d + 1);
-            }
-            out[((size_t)rec * r.ns + s) * LPE + lane] = acc;
-          }
-      }
-    }
-  } else {
-    // sources of the steps that end at the next level
-    const SrcArgs& s = pt.s;
-    const int src = (int)blockIdx.x - rec_blocks;
-    const int qq = threadIdx.x / B, b = threadIdx.x % B;
-    if (src < s.n && qq < 6 && s.elem[src] < pt.src_end) {
-      const int elem = s.elem[src];
-      const int cl = cluster_of(a, elem);
-      const double dt = a.dt[cl];
-      const int n = step_new_of(a, cl, 1) - 1;
-      const double t0 = (double)n * dt, t1 = (double)(n + 1) * dt;
-      const double w = stf_antiderivative(s.kind[src], s.par[2 * src], s.par[2 * src + 1], t1) -
-                       stf_antiderivative(s.kind[src], s.par[2 * src], s.par[2 * src + 1], t0);
-      const double inc = -s.moment[6 * src + qq] * s.phi[(size_t)src * B + b] * s.inv_det[src] * w;
-      const int g = elem / EPW, e = elem % EPW;
-      R* Qe = reinterpret_cast<R*>(p.Qe) + (size_t)s.run[src] * p.run_qe;
-      atomicAdd(&Qe[((size_t)g * B + b) * NSLOT + e * LPE + qq], R(inc));
-    }
-  }
-  if (pt.tick) {
-    // every block has read the clock before it takes its ticket
-    __syncthreads();
-    if (threadIdx.x == 0) {
-      __threadfence();
-      unsigned* const ticket = reinterpret_cast<unsigned*>(pt.tick + 1);
-      if (atomicAdd(ticket, 1u) == gridDim.x - 1) {
-        *ticket = 0u;
-        *pt.tick += pt.tick_by;
-      }
-    }
-  }
-}
-
 }  // namespace
 
-__global__ void k_clock(long long* clock, long long set, int keep) {
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
-    clock[0] = set + (keep ? clock[0] : 0ll);
-    clock[1] = 0;
-  }
+__global__ void k_clock(long long* clock, long long set) {
+  if (blockIdx.x == 0 && threadIdx.x == 0) *clock = set;
 }
 
-int launch_clock(long long* clock, long long set, int keep, hipStream_t st) {
-  hipLaunchKernelGGL(k_clock, dim3(1), dim3(64), 0, st, clock, set, keep);
+int launch_clock(long long* clock, long long set, hipStream_t st) {
+  hipLaunchKernelGGL(k_clock, dim3(1), dim3(64), 0, st, clock, set);
   return (int)hipGetLastError();
 }
 
@@ -919,44 +930,40 @@ template <int O>
 constexpr int LEVEL_W = O >= 4 ? 4 : 2;
 
 template <class R, int O, int M, int W, bool TM = false>
-static void launch_kind(const LevelArgs& a, dim3 grid, const KPtrs& p, hipStream_t st) {
+static void launch_kind(const LevelArgs& a, const PointArgs& pt, const KPtrs& p, hipStream_t st) {
+  const dim3 grid((unsigned)(a.groups + a.points), a.runs);
   if (a.kind == KIND_FUSED)
-    hipLaunchKernelGGL((k_level<R, O, M, KIND_FUSED, W, TM>), grid, dim3(64 * W), 0, st, p, a);
+    hipLaunchKernelGGL((k_level<R, O, M, KIND_FUSED, W, TM>), grid, dim3(64 * W), 0, st, a, p, pt);
   else if (a.kind == KIND_PREDICT)
-    hipLaunchKernelGGL((k_level<R, O, M, KIND_PREDICT, W, TM>), grid, dim3(64 * W), 0, st, p, a);
+    hipLaunchKernelGGL((k_level<R, O, M, KIND_PREDICT, W, TM>), grid, dim3(64 * W), 0, st, a, p, pt);
   else
-    hipLaunchKernelGGL((k_level<R, O, M, KIND_NEIGHBOR, W>), grid, dim3(64 * W), 0, st, p, a);
+    hipLaunchKernelGGL((k_level<R, O, M, KIND_NEIGHBOR, W>), grid, dim3(64 * W), 0, st, a, p, pt);
 }
 
 template <class R, int O, int M>
-int launch_level(const KPtrs& p, const LevelArgs& a, int runs, hipStream_t st) {
-  const int groups = (a.end + EPW - 1) / EPW;
-  if (groups <= 0 || runs <= 0) return 0;
-  const dim3 grid(groups, runs);
+int launch_level(const KPtrs& p, LevelArgs a, const PointArgs& pt, int runs, hipStream_t st) {
+  if (runs <= 0) return 0;
+  const bool tm = std::is_same<R, float>::value && O >= 4 && a.trace_mfma;
+  const int waves = tm ? 2 : LEVEL_W<O>;
+  // a wave per point; rows of a multiple of eight workgroups (see group_and_run)
+  const long long items = (a.kind == KIND_PREDICT ? 0ll : pt.r.n) +
+                          (a.kind == KIND_NEIGHBOR || pt.s.n == 0 ? 0 : pt.s.per_run);
+  a.groups = (a.end + EPW - 1) / EPW;
+  a.points = (int)(((items + waves - 1) / waves + 7) / 8 * 8);
+  a.runs = runs;
+  if (a.groups + a.points == 0) return 0;   // (a level of a cluster without elements still has its points)
   if constexpr (std::is_same<R, float>::value && O >= 4) {
-    if (a.trace_mfma) {
-      launch_kind<R, O, M, 2, true>(a, grid, p, st);
+    if (tm) {
+      launch_kind<R, O, M, 2, true>(a, pt, p, st);
       return (int)hipGetLastError();
     }
   }
-  launch_kind<R, O, M, LEVEL_W<O>>(a, grid, p, st);
+  launch_kind<R, O, M, LEVEL_W<O>>(a, pt, p, st);
   return (int)hipGetLastError();
 }
 
-template <class R, int O, int M>
-int launch_points(const KPtrs& p, const LevelArgs& a, const PointArgs& q, hipStream_t st) {
-  const long long items = (long long)q.r.n * q.r.runs;
-  const int rec_blocks = (int)((items + PT_WAVES - 1) / PT_WAVES);
-  const int blocks = rec_blocks + q.s.n;
-  if (blocks <= 0) return q.tick ? launch_clock(q.tick, q.tick_by, 1, st) : 0;
-  static_assert(6 * edg_gen::Ref<O>::B <= 64 * PT_WAVES && O * LPE <= 64, "one block per source, one wave per receiver");
-  hipLaunchKernelGGL((k_points<R, O, M>), dim3((unsigned)blocks), dim3(64 * PT_WAVES), 0, st, p, a, q, rec_blocks);
-  return (int)hipGetLastError();
-}
-
-#define EDG_INST(R, O, M)                                                                        \
-  template int launch_level<R, O, M>(const KPtrs&, const LevelArgs&, int, hipStream_t);         \
-  template int launch_points<R, O, M>(const KPtrs&, const LevelArgs&, const PointArgs&, hipStream_t);
+#define EDG_INST(R, O, M) \
+  template int launch_level<R, O, M>(const KPtrs&, LevelArgs, const PointArgs&, int, hipStream_t);
 
 EDG_KERNEL_INSTANCES
 

@@ -37,31 +37,42 @@ struct KPtrs {
   void* T1;          // [run][2][Kp][4][9][FP] B1 face traces (parity of the step)
   void* T2;          // [run][2][N2][4][9][FP] B2 face traces of elements with a finer neighbour
   void* T3;          // [run][2][N3][4][9][FP] B3 face traces of elements with a coarser neighbour
-  void* recD;        // [run][slots][O][9][B] time derivatives of receiver elements
+  // [run][slots][O][9][B] time derivatives of receiver elements; two slots, by
+  // step parity, in cluster 0, whose next step overwrites them in the launch
+  // that samples them
+  void* recD;
   long long Kp;      // padded element count (multiple of 7)
   long long N2, N3;  // B2 / B3 slots per parity
   long long run_qe, run_qa, run_t1, run_t2, run_t3, run_recd;   // per-run strides (words)
 };
 
 struct LevelArgs {
-  int run0;          // runs run0 + blockIdx.y take part
-  int end;           // internal slots [0, end) take part (clusters are contiguous, finest first)
-  int kind;
+  // what a workgroup needs before its first address, in one cache line
+  int groups;        // element groups of a run (set at the launch, as are points and runs)
+  int points;        // workgroups of points before them, per run (see PointArgs)
+  int runs;          // runs run0 .. run0 + runs - 1 take part
+  int run0;
+  int xcd_remap;     // 1: the workgroups of one XCD take a contiguous range of element groups
+  // workgroup order shuffle (debug; 0 = off): workgroup id w runs the work of
+  // id (w * shuf_mul + shuf_add) mod (workgroups of the launch), shuf_mul
+  // coprime with that count and (count - 1) * shuf_mul + shuf_add < 2^32
+  int shuf_mul, shuf_add;
   int n_clusters;
-  int cl_end[MAX_CLUSTERS];     // padded end of cluster l (multiple of EPW)
-  int cl_vend[MAX_CLUSTERS];    // end of cluster l's real elements (the rest is padding)
   // The level being processed (finest steps from t = 0) is *clock + level: in a
   // captured cycle the clock is device memory that the replays advance, else it
   // points to a zero.  At level G cluster l (active iff G is a multiple of 2^l)
   // ends its step G/2^l - 1 and starts step G/2^l.
   const long long* clock;
   long long level;
-  int xcd_remap;     // 1: the workgroups of one XCD take a contiguous range of element groups
-  int trace_mfma;    // 1: the traces of faces 0 and 1 on the matrix cores (two-wave FP32 kernel)
-  // workgroup order shuffle (debug; 0 = off): workgroup id w runs the work of
-  // id (w * shuf_mul + shuf_add) mod (workgroups of the launch), shuf_mul
-  // coprime with that count and (count - 1) * shuf_mul + shuf_add < 2^32
-  int shuf_mul, shuf_add;
+  // not null: a captured cycle's last launch sets the clock of the cycle after
+  // it to its own + tick (two clocks take turns: no launch reads the one it sets)
+  long long* next;
+  long long tick;
+  int end;           // internal slots [0, end) take part (clusters are contiguous, finest first)
+  int kind;
+  int cl_end[MAX_CLUSTERS];     // padded end of cluster l (multiple of EPW)
+  int cl_vend[MAX_CLUSTERS];    // end of cluster l's real elements (the rest is padding)
+  int trace_mfma;    // 1: the traces of faces 0 and 1 on the matrix cores (FP32, O >= 4, on two waves per group)
   double dt[MAX_CLUSTERS];
   double tc[MAX_CLUSTERS][MAX_ORDER];  // dt^{d+1}/(d+1)!
   double th[MAX_CLUSTERS][MAX_ORDER];  // (dt/2)^{d+1}/(d+1)!
@@ -74,38 +85,40 @@ struct LevelArgs {
 };
 
 struct SrcArgs {
-  int n;
-  const int* run;         // [n] run of each source
+  // [run][groups + 1]: first[g] .. first[g + 1] are the run's sources in group
+  // g; the arrays below hold the sources run by run, by element in each.  With
+  // no source: two zeros, and row and col, the strides of the run and of the
+  // group, are 0.
+  const int* first;
+  int row, col;
+  int n;                  // sources of all runs (0: the rest is not read)
+  int per_run;            // the most sources of a run
   const int* elem;
   const int* kind;
   const double* par;      // [n][2]
   const double* moment;   // [n][6]
   const double* phi;      // [n][B]
   const double* inv_det;  // [n]
+  void* inc;              // [2][n][6][B] what a source adds to its element, by level parity
 };
 
 struct RecArgs {
   int n;
-  int runs;               // every receiver of runs 0 .. runs - 1
   const int* elem;
-  const int* slot;
+  const int* slot;        // first slot of the receiver's element in recD
   const double* phi;      // [n][B]
   double dt_sample;
   long long ns;
   double* out;            // [run][n][ns][9]
 };
 
-// What runs between the launch of level j and that of level j + 1: the
-// receivers sample the predictions of level j (the launch's LevelArgs), the
-// sources of the steps that end at level j + 1 are added; tick (not null): the
-// last workgroup to finish adds tick_by to the clock *tick (its tickets are
-// counted in tick[1])
+// The points of a launch of level j: its first workgroups sample the receivers
+// in the steps that started at level j - 1 and evaluate what the sources of the
+// steps that end at level j + 1 add; the element groups add what the launch
+// before evaluated for the steps that end at j.
 struct PointArgs {
-  RecArgs r;
   SrcArgs s;
-  int src_end;            // internal slots [0, src_end) end a step at level j + 1
-  long long* tick;
-  long long tick_by;
+  RecArgs r;
 };
 
 // materials in device memory, caller's element order: rho, vp, vs [K];
@@ -149,13 +162,11 @@ int launch_get_dofs(const DofTables& t, long long k0, long long n, double* dofs,
                     hipStream_t st);
 
 template <class R, int O, int M>
-int launch_level(const KPtrs& p, const LevelArgs& a, int runs, hipStream_t st);
-// *clock = set + *clock * keep (keep 0 or 1), ticket counter zeroed
-int launch_clock(long long* clock, long long set, int keep, hipStream_t st);
+int launch_level(const KPtrs& p, LevelArgs a, const PointArgs& pt, int runs, hipStream_t st);
+// *clock = set
+int launch_clock(long long* clock, long long set, hipStream_t st);
 // zero `words` 32-bit words at p (a fill kernel: no memset node in a capture)
 int launch_zero_words(void* p, size_t words, hipStream_t st);
-template <class R, int O, int M>
-int launch_points(const KPtrs& p, const LevelArgs& a, const PointArgs& q, hipStream_t st);
 
 // instantiated (precision, order, mechanisms) combinations
 #define EDG_FOR_EACH_VARIANT(X) \
