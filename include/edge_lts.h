@@ -81,8 +81,8 @@ typedef struct {
   uint32_t flags;      /* EDG_FLAG_* (EDG_EINVAL for other bits) */
 } edg_config;
 
-#define EDG_FLAG_GRAPH 1u  /* replay every full LTS cycle but the last of an edg_advance_to call as one
-                              captured HIP graph (kernel nodes only; recaptured after a change of
+#define EDG_FLAG_GRAPH 1u  /* replay the full LTS cycles of an edg_advance_to call, but the last one or
+                              two, in pairs as one captured HIP graph (kernel nodes only; recaptured after a change of
                               sources, receivers, clusters or launch plan); edg_adjoint replays the
                               backward levels of its segments as graphs captured once per segment
                               length in that call */
@@ -111,7 +111,7 @@ typedef struct {
                          groups (neighbour traces then stay in that XCD's L2) */
   int32_t run_chunk;  /* runs per launch (0 = all runs in one launch) */
   int32_t trace_mfma; /* 1: the traces of faces 0 and 1 as one dense product on the matrix cores
-                         (two-wave FP32 kernel, orders 4 and 5; elsewhere ignored).  Results
+                         (FP32, orders 4 and 5; elsewhere ignored).  Results
                          agree with the vector-ALU traces to FP32 rounding, not bit for bit. */
 } edg_plan;
 

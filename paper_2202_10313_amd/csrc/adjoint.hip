@@ -43,14 +43,17 @@
 // memory-variable mode.  Reference-matrix products are the generated
 // straight-line code and its transposes; row-mixing products go through LDS.
 //
-// What bounds it: vector issue (51-64% of the SIMDs' cycles) and LDS / barrier
-// latency at two or three waves per SIMD; 2.2-3.0 TB/s of memory traffic.
+// What bounds it: vector issue (52-64% of the SIMDs' cycles) and LDS / barrier
+// latency at three waves per SIMD; 2.1-3.8 TB/s of memory traffic.
 // Measured per reverse cycle of two clusters, 97k tets, FP32 (before: two
 // launches per level with neighbour slots updated in place, two waves at O = 4
 // and 5 that kept every step's sums, coupling adjoints and Qbar in 0.24 MB of
 // scratch per group, one wave otherwise): O = 5 m=3 3,490 -> 2,220 us, O = 4
 // m=3 2,290 -> 1,550, m=0 1,330 -> 908, O = 3 m=3 1,540 -> 766; FP64 O = 5 m=3
-// 12k tets 7,220 -> 718 (3.8 KB of spills a lane before).
+// 12k tets 7,220 -> 718 (3.8 KB of spills a lane before).  Combining the rows
+// of the transposed products with G' before the exchange and forming the lane's
+// parameters twice (37k tets): O = 5 m=3 820 -> 761, O = 4 m=3 555 -> 458, m=0
+// 330 -> 306, O = 3 m=3 276 -> 245; FP64 O = 5 m=3 10k 624 -> 590.
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
