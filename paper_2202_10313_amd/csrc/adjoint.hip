@@ -363,7 +363,7 @@ constexpr int adj_occ() {
 // the update at the end of a segment (KIND_ADJ_UPDATE), only the prediction at
 // its start (KIND_ADJ_PREDICT).
 template <class R, int O, int M, int KIND>
-__global__ __launch_bounds__(64 * ADJ_W<O>) __attribute__((amdgpu_waves_per_eu(adj_occ<R, O, M>(), 4)))
+__global__ __launch_bounds__(64 * ADJ_W<O>) __attribute__((amdgpu_waves_per_eu(adj_occ<R, O, M>(), 8)))
 void k_adjoint(KPtrs p, APtrs ad, LevelArgs a) {
   using RF = edg_gen::Ref<O>;
   using L = AdjLds<R, O, M>;

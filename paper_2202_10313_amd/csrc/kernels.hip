@@ -132,6 +132,9 @@ __device__ __forceinline__ int gslot(int row, int dir) {
 // 1,879), two at O = 5 m=3 (it takes 168, three waves) and for the two-wave form
 // of O >= 4; FP64 O >= 4 one, so that nothing spills (41k tets O = 5 m=0 919 ->
 // 884 us, m=3 1,862 -> 1,835).
+// (At least that many, up to the eight the hardware has: an upper bound of four,
+// as before, is kept by allocating registers that nothing uses.  FP32 m=0, two
+// clusters, us per cycle: O = 2 303k tets 247 -> 217, O = 4 762 -> 702.)
 template <class R, int O, int M, int W>
 constexpr int level_occ() {
   return sizeof(R) == 8 ? (O >= 4 ? 1 : 2) : (O <= 3 || (W == 4 && !(O == 5 && M > 0))) ? 4 : 2;
@@ -235,7 +238,7 @@ __device__ __forceinline__ void level_points(const KPtrs& p, const LevelArgs& a,
 // 0 and 1 (the two densest) as one dense product on the matrix cores.
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 template <class R, int O, int M, int KIND, int W, bool TM = false>
-__global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(level_occ<R, O, M, W>(), 4)))
+__global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(level_occ<R, O, M, W>(), 8)))
 void k_level(LevelArgs a, KPtrs p, PointArgs pt) {
   using RF = edg_gen::Ref<O>;
   using L = LevelLds<R, O, M>;
