@@ -77,7 +77,14 @@ struct LevelLds {
   static constexpr int B = RF::B, FP = RF::FP;
   static constexpr int up(int v, int m, int r) { return v + ((r - v % m) % m + m) % m; }
   static constexpr int BS = B % 2 ? B : B + 1;                 // row stride of mode rows (odd)
-  static constexpr int FS = FP + 1;                            // row stride of face rows (odd)
+  // Face rows hold the F face modes at the least odd stride: the face area is
+  // the larger one below O = 5, and its padding to FP kept a workgroup off the CU
+  // (FP64 O = 4 55 -> 47 KB, two -> three; 41k tets m=0 279 -> 242 us per cycle,
+  // 3.9k tets O = 3 plane wave check 667 -> 640 us; FP32 O = 4 m=0 303k 706 ->
+  // 688).  FP32 O = 4 m=3 has no registers for a fifth (98k 418 -> 420): padded.
+  static constexpr bool FPAD = sizeof(R) == 4 && O == 4 && M > 0;
+  static constexpr int FS = FPAD ? FP + 1 : RF::F | 1;         // row stride of face rows (odd)
+  static constexpr int FW = FPAD ? FP : RF::F;                 // words of a face row
   static constexpr int GRAD = 19 * BS;          // 18 used (row, dir) pairs + 1 dummy row
   static constexpr int COUP = 6 * BS;
   static constexpr int RX = LPE * BS;
@@ -455,7 +462,7 @@ void k_level(LevelArgs a, KPtrs p, PointArgs pt) {
       R* dmn = fac + ((i * 2 + 0) * LPE + q) * FS;
       R* dpl = fac + ((i * 2 + 1) * LPE + q) * FS;
 #pragma unroll
-      for (int f = 0; f < FP; ++f) {
+      for (int f = 0; f < L::FW; ++f) {
         dmn[f] = vown[ii][f];
         dpl[f] = none[ii] ? R(0) : v1[ii][f] - v2[ii][f];
       }
@@ -493,7 +500,7 @@ void k_level(LevelArgs a, KPtrs p, PointArgs pt) {
 #pragma unroll
       for (int i = 0; i < 4; ++i)
 #pragma unroll
-        for (int f = 0; f < FP; ++f) pf[i * FP + f] = fac[((i * 2 + 0) * LPE + q) * FS + f];
+        for (int f = 0; f < FP; ++f) pf[i * FP + f] = f < L::FW ? fac[((i * 2 + 0) * LPE + q) * FS + f] : R(0);
       RF::template lift_w<W>(w, pf, da);
     }
     // the group's sources, if any (uniform)
