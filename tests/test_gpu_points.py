@@ -1,5 +1,4 @@
-"""Sources and receivers between two levels (one launch) and the level count of
-captured cycles: every combination of sources, receivers and runs, replayed
+"""Sources and receivers of the levels and the level count of captured cycles: every combination of sources, receivers and runs, replayed
 cycles with host reads in between against eager launches, bit for bit."""
 import numpy as np
 import pytest
