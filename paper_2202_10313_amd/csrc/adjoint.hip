@@ -38,6 +38,24 @@
 // adjoint-weighted partial derivative to per-element FP64 words (NG);
 // k_material_gradient applies the chain rule to rho, vp, vs.
 //
+// dJ/drho of the products (at fixed vp, vs) is not formed from their derivatives
+// in 1/rho and in the moduli: those cancel, to 1e-12 of either where the recorded
+// stresses depend on rho through lam/rho and mu/rho only (two steps from rest),
+// and FP32 sums left rounding there (1e5 times the exact value, FP64 1e-3 of it).
+// Every product is linear in a state (stresses s, the rest z = velocities and
+// memory variables); rho multiplies its part s <- z and divides its part z <- s,
+// so with P the projection on z and L the product, rho dL/drho = L P - P L.
+// Summed over the Cauchy-Kowalevski recursion and the volume kernel, <adjoint of
+// the output, (L P - P L) input> telescopes to
+//   <D_0 adjoint, P D_0> - <receivers' part of the D_d adjoint, P D_d>, all d,
+//   - <flux part of the time integral's adjoint, P T> (T and the half step's)
+//   - <Qbar, P V>, V the volume term,
+// whose terms have the size of the result: 6e-8 .. 1.4e-7 of the exact value in
+// FP32 there, 9e-16 in FP64, at the same time (97k tets, a reverse cycle,
+// O = 5 m=3 and O = 4 m=0: within 1%).  Of V's memory rows, -omega (eps + T^theta),
+// the T^theta part is paired through Lambda_d (T^theta is linear in the strain
+// rates of the recursion and in the start-of-step memory variables).
+//
 // Work mapping: as the forward k_level, W waves per 7 elements, lane 9e + q of
 // wave w holds row q of element e for the wave's modes and at most one
 // memory-variable mode.  Reference-matrix products are the generated
@@ -290,8 +308,8 @@ struct AdjLds {
 // Per-wave scratch in device memory, in 16-byte lane pieces side by side (one
 // coalesced transfer of up to 1 KB per instruction): what the reverse loop
 // needs of each forward derivative D_d and cannot hold on chip.
-//   VX [O - 1]: the velocity rows' gradient sums d_d sigma_id (own modes; 21
-//               lanes, padded to 24)
+//   VX [O - 1]: the velocity rows' gradient sums d_d sigma_id, in groups with a
+//               receiver (own modes; 21 lanes, padded to 24)
 //   EP [O - 1]: the strain rate of the lane's owned mode (6 words)
 //   LM [O]:     Lambda_d of the owned mode (6 words, M > 0)
 template <class R, int O, int M>
@@ -379,6 +397,7 @@ void k_adjoint(KPtrs p, APtrs ad, LevelArgs a) {
   static_assert(NBX <= LPE, "at most one owned memory mode per lane");
   __shared__ R lds[L::TOTAL];
   __shared__ double gsh[KIND == KIND_ADJ_UPDATE ? 1 : EPW * NGS];
+  __shared__ double grsh[KIND == KIND_ADJ_UPDATE ? 1 : 64 * W];
   constexpr int FSTW = 17;
   __shared__ R fst[KIND == KIND_ADJ_UPDATE ? 1 : EPW * 4 * FSTW];
   __shared__ int fnb[EPW * 4], fcd[EPW * 4], fax[EPW * 4];
@@ -576,6 +595,20 @@ void k_adjoint(KPtrs p, APtrs ad, LevelArgs a) {
     evalid[ec] = valid ? 1 : 0;
   }
 
+  // rho dJ/drho of the products (see the head of the file), this lane's part: in
+  // LDS during the face phases, the register peak, then in a register
+  double* const grl = grsh + threadIdx.x;
+  *grl = 0.0;
+  // - <x, velocity rows of the row exchange>, own modes
+  auto pair_exchange = [&](const R (&x)[NBX]) {
+    double s = 0.0;
+    if (!is_stress)
+#pragma unroll
+      for (int lb = 0; lb < NBX; ++lb)
+        if (has(lb)) s += (double)(x[lb] * rx[q * BS + base + lb]);
+    *grl -= s;
+  };
+
   // ---------------------------------------------- forward recompute: D_d, T, T2
   R te[NBX], t2[NBX];
   {
@@ -663,7 +696,7 @@ void k_adjoint(KPtrs p, APtrs ad, LevelArgs a) {
             nx[lb] = x.wabc * sab[lb] + x.wde * (grad[sd + b] + grad[se + b]) + cq;
           }
         }
-        if (!is_stress && act) stV(d, sab);
+        if (!is_stress && rec_slot >= 0 && act) stV(d, sab);
         if (act)
 #pragma unroll
           for (int lb = 0; lb < NBX; ++lb)
@@ -817,8 +850,13 @@ void k_adjoint(KPtrs p, APtrs ad, LevelArgs a) {
     }
     __syncthreads();
   };
-  if (any_b2) face_phase(true, t2, lt2);
+  // (the row exchange holds the integrals of the phase until the next writes it)
+  if (any_b2) {
+    face_phase(true, t2, lt2);
+    pair_exchange(lt2);
+  }
   face_phase(false, te, lte);
+  pair_exchange(lte);
 
   // ---------------------------------------------- volume kernel
   // V = -(lam delta div v + mu (d_j v_i + d_i v_j)) (stress), -rho_inv div sigma (velocity), -omega_l eps (memory)
@@ -858,9 +896,8 @@ void k_adjoint(KPtrs p, APtrs ad, LevelArgs a) {
   __syncthreads();
   // Material words, summed in registers over the whole kernel: a product's
   // adjoint rows x paired with the strain rates give dJ/dlam (tr x tr eps) and
-  // dJ/dmu (2 x : eps), mode by mode in the lane that owns the mode; the
-  // velocity rows with their gradient sums give dJ/d(1/rho).
-  double gl = 0.0, gm = 0.0, gr = 0.0;
+  // dJ/dmu (2 x : eps), mode by mode in the lane that owns the mode.
+  double gl = 0.0, gm = 0.0, gr = *grl;
   auto strain_words = [&](const R* eps, const R* x, const double sign) {
     double s = 0.0;
 #pragma unroll
@@ -869,11 +906,13 @@ void k_adjoint(KPtrs p, APtrs ad, LevelArgs a) {
     gl += sign * (double)((x[0] + x[1] + x[2]) * (eps[0] + eps[1] + eps[2]));
   };
   if (!is_stress) {
+    double s = 0.0;
 #pragma unroll
     for (int lb = 0; lb < NBX; ++lb) {
       const int b = base + lb;
-      if (has(lb)) gr -= (double)(le[lb] * (grad[sa + b] + grad[sb + b] + grad[sc + b]));
+      if (has(lb)) s += (double)(le[lb] * (grad[sa + b] + grad[sb + b] + grad[sc + b]));
     }
+    gr += (double)rho_inv * s;
   }
   // exchange: elastic adjoint rows, omega-weighted memory-variable adjoints
   // (own modes: the rows and coupling rows that write_y reads)
@@ -925,6 +964,7 @@ void k_adjoint(KPtrs p, APtrs ad, LevelArgs a) {
 #pragma unroll
           for (int l = 0; l < MM; ++l) v += om[l] * lv[l * 6 + c];
           coup[c * BS + b] = v;
+          gr += (double)(v * eps[c]);
         }
     }
   }
@@ -1018,6 +1058,7 @@ void k_adjoint(KPtrs p, APtrs ad, LevelArgs a) {
     for (int c = 0; c < 6; ++c) gab[2 * l + 1] -= (double)(f * Pl[l][c] * x[c]);
   };
   R* const recDb = reinterpret_cast<R*>(ad.recDb);
+  const R* const Seg = reinterpret_cast<const R*>(ad.Se) + (size_t)g * B * NSLOT;
 #pragma unroll 1
   for (int d = O - 1; d >= 0; --d) {
     asm volatile("" : "+v"(slot), "+s"(base), "+v"(l1), "+v"(lvx));
@@ -1025,23 +1066,36 @@ void k_adjoint(KPtrs p, APtrs ad, LevelArgs a) {
     const bool more = d + 1 < O;
     R cur[NBX];
     // the step's scratch operands in one batch
-    R vx[NBX], eps[6], lm[6];
+    R eps[6], lm[6], l1m[6];
 #pragma unroll
-    for (int lb = 0; lb < NBX; ++lb) vx[lb] = R(0);
-#pragma unroll
-    for (int c = 0; c < 6; ++c) { eps[c] = R(0); lm[c] = R(0); }
+    for (int c = 0; c < 6; ++c) { eps[c] = R(0); lm[c] = R(0); l1m[c] = R(0); }
     if (M > 0 && own) ld6(SC::LM, d, lm);
-    if (more) {
-      if (own) ld6(SC::EP, d, eps);
-      if (!is_stress) ldV(d, vx);
+    if (more && own) {
+      ld6(SC::EP, d, eps);
+      if (M > 0) ld6(SC::LM, d + 1, l1m);
     }
 #pragma unroll
     for (int lb = 0; lb < NBX; ++lb) cur[lb] = c_d * lte[lb] + h_d * lt2[lb];
     if (rec_slot >= 0 && valid) {
+      R vx[NBX];                                  // D_d (d > 0: times rho), velocity rows
+#pragma unroll
+      for (int lb = 0; lb < NBX; ++lb) vx[lb] = R(0);
+      if (!is_stress) {
+        if (d > 0) ldV(d - 1, vx);
+        else
+#pragma unroll
+          for (int lb = 0; lb < NBX; ++lb)
+            if (has(lb)) vx[lb] = at(Seg, (base + lb) * NSLOT + slot);
+      }
       R* rd = recDb + (((size_t)rec_slot * O + d) * LPE + q) * B + base;
 #pragma unroll
       for (int lb = 0; lb < NBX; ++lb)
-        if (has(lb)) { cur[lb] += rd[lb]; rd[lb] = R(0); }
+        if (has(lb)) {
+          const R v = rd[lb];
+          cur[lb] += v;
+          rd[lb] = R(0);
+          if (!is_stress) gr -= (double)(v * (d > 0 ? rho_inv * vx[lb] : vx[lb]));
+        }
     }
     if (more) {
       if (act)
@@ -1051,14 +1105,14 @@ void k_adjoint(KPtrs p, APtrs ad, LevelArgs a) {
       // (coup holds the omega-weighted sums of the next memory-variable
       // adjoint, written by the coupling block of the step before)
       __syncthreads();
-      if (!is_stress)
-#pragma unroll
-        for (int lb = 0; lb < NBX; ++lb) gr += (double)(nbe[lb] * vx[lb]);
       if (own) {
         R x[6];
 #pragma unroll
         for (int c = 0; c < 6; ++c) x[c] = rx[c * BS + base + q];
         strain_words(eps, x, 1.0);
+        if (M > 0)
+#pragma unroll
+          for (int c = 0; c < 6; ++c) gr += (double)(l1m[c] * eps[c]);
       }
       write_y(R(1));
       __syncthreads();
@@ -1127,13 +1181,20 @@ void k_adjoint(KPtrs p, APtrs ad, LevelArgs a) {
       for (int d = O - 1; d >= 0; --d) C0 = R(a.tc[cl][d]) - om[l] * C0;
       const R pt = al[l] * (Pl[l][0] + Pl[l][1] + Pl[l][2]);
 #pragma unroll
-      for (int c = 0; c < 6; ++c)
-        lv[l * 6 + c] -= om[l] * C0 * lv[l * 6 + c] + (bl[l] * Pl[l][c] + (c < 3 ? pt : R(0)));
+      for (int c = 0; c < 6; ++c) {
+        const R sp = bl[l] * Pl[l][c] + (c < 3 ? pt : R(0));
+        lv[l * 6 + c] -= om[l] * C0 * lv[l * 6 + c] + sp;
+        gr -= (double)(sp * dm[l][c]);
+      }
     }
     if (valid)
 #pragma unroll
       for (int k = 0; k < 6 * MM; ++k) at(La, k * NSLOT + mword) = lv[k];
   }
+  if (!is_stress)
+#pragma unroll
+    for (int lb = 0; lb < NBX; ++lb)
+      if (has(lb)) gr += (double)(nbe[lb] * at(Seg, (base + lb) * NSLOT + slot));
 #pragma unroll
   for (int lb = 0; lb < NBX; ++lb) {
     le[lb] += nbe[lb];
@@ -1145,14 +1206,14 @@ void k_adjoint(KPtrs p, APtrs ad, LevelArgs a) {
 #pragma unroll
   for (int ww = 0; ww < W; ++ww) {
     if (w == ww && valid) {
+      gadd(gs, NG_RHO, gr);
       if (own) {
-        gadd(gs, 1, gl);
-        gadd(gs, 2, gm);
+        gadd(gs, NG_RHO + 1, gl);
+        gadd(gs, NG_RHO + 2, gm);
         if (M > 0)
 #pragma unroll
           for (int k = 0; k < 2 * MM; ++k) gadd(gs, 5 + k, gab[k]);
       }
-      if (!is_stress) gadd(gs, 0, gr);
     }
     __syncthreads();
   }
@@ -1199,10 +1260,13 @@ __global__ void k_material_gradient(const double* gacc, const int* FI, const dou
   if (rho > 0.0) {
     const double* x = gacc + k * NG;
     for (int t = 0; t < 5; ++t) add_param(g, t, x[t], rho, vp, vs);
+    // the products: rho at fixed vp, vs, then the moduli's vp, vs
+    g[0] += x[NG_RHO] / rho;
+    g[1] += x[NG_RHO + 1] * 2 * rho * vp;
+    g[2] += (x[NG_RHO + 2] - 2 * x[NG_RHO + 1]) * 2 * rho * vs;
     for (int l = 0; l < M; ++l) {   // a_l = rho vp^2 Yp - 2 rho vs^2 Ys, b_l = 2 rho vs^2 Ys
       const double yp = mat[k * mw + 3 + 2 * l], ys = mat[k * mw + 4 + 2 * l];
       const double ga = x[5 + 2 * l], gb = x[6 + 2 * l];
-      g[0] += ga * (vp * vp * yp - 2 * vs * vs * ys) + gb * 2 * vs * vs * ys;
       g[1] += ga * 2 * rho * vp * yp;
       g[2] += -ga * 4 * rho * vs * ys + gb * 4 * rho * vs * ys;
     }

@@ -12,11 +12,16 @@ constexpr int KIND_ADJ_FUSED = 5;    // transposed predictions, then transposed 
 constexpr int adj_rows(int M) { return M > 0 ? 15 : 9; }
 // Per-element gradient words (internal order, FP64): derivatives of the
 // adjoint pairing in the parameters the kernels read.
-//   [0] 1/rho  [1] lam  [2] mu  [3] Zp  [4] Zs  [5+2l] a_l  [6+2l] b_l
+//   [0] 1/rho  [1] lam  [2] mu  [3] Zp  [4] Zs of the own flux
+//   [5+2l] a_l  [6+2l] b_l  of the products (time and volume kernel)
 //   [11+2i], [12+2i]  the neighbour impedances Zp, Zs of face i (own flux)
 //   [19+7f+0..6]      (1/rho, lam, mu, Zp, Zs, Zp+, Zs+) of the flux of the
 //                     element across face f (its neighbour-data part)
-constexpr int NG = 48;
+//   [NG_RHO]          rho times the products' derivative in rho at fixed vp, vs
+//                     (through 1/rho and all moduli, the anelastic ones too)
+//   [NG_RHO+1, +2]    lam, mu of the products
+constexpr int NG_RHO = 47;
+constexpr int NG = 50;
 
 struct APtrs {
   void* Le;          // adjoint of the elastic rows (Qe layout)
