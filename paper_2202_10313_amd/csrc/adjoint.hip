@@ -254,10 +254,10 @@ __device__ __forceinline__ const T& at(const T* base, uint32_t i) {
 }
 
 // adds v to the element's gradient word w (LDS, FP64).  The elements' word
-// arrays are NGS = NG + 1 doubles apart: with a stride of NG = 48 doubles the
-// same word of every other element fell into one bank, so an atomic of a
-// wave serialised over four elements' lanes
-constexpr int NGS = NG + 1;
+// arrays are an odd number of doubles apart: with a stride of 48 the same word of
+// every other element fell into one bank, so an atomic of a wave serialised over
+// four elements' lanes
+constexpr int NGS = NG | 1;
 __device__ __forceinline__ void gadd(double* gs, int w, double v) { atomicAdd(gs + w, v); }
 
 // v of the lane that DPP control CTRL names (a permutation within 16-lane rows)
@@ -279,6 +279,15 @@ __device__ __forceinline__ R seg_sum(R v) {
   v += dpp<0x4e>(v);                       // quad_perm 2 3 0 1
   if (SEG > 4) v += dpp<0x141>(v);         // row_half_mirror
   if (SEG > 8) v += dpp<0x140>(v);         // row_mirror
+  return v;
+}
+
+// This lane's number, formed anew where it is used: kept in a register over the
+// face phases it is spilled and reloaded at every use (FP64 O = 4: 50 -> 59 us a
+// level of 5k tets).
+__device__ __forceinline__ int lane_id() {
+  int v;
+  asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(v));
   return v;
 }
 
@@ -397,7 +406,7 @@ void k_adjoint(KPtrs p, APtrs ad, LevelArgs a) {
   static_assert(NBX <= LPE, "at most one owned memory mode per lane");
   __shared__ R lds[L::TOTAL];
   __shared__ double gsh[KIND == KIND_ADJ_UPDATE ? 1 : EPW * NGS];
-  __shared__ double grsh[KIND == KIND_ADJ_UPDATE ? 1 : 64 * W];
+  __shared__ double grsh[KIND == KIND_ADJ_UPDATE ? 1 : W * NSLOT];
   constexpr int FSTW = 17;
   __shared__ R fst[KIND == KIND_ADJ_UPDATE ? 1 : EPW * 4 * FSTW];
   __shared__ int fnb[EPW * 4], fcd[EPW * 4], fax[EPW * 4];
@@ -597,7 +606,7 @@ void k_adjoint(KPtrs p, APtrs ad, LevelArgs a) {
 
   // rho dJ/drho of the products (see the head of the file), this lane's part: in
   // LDS during the face phases, the register peak, then in a register
-  double* const grl = grsh + threadIdx.x;
+  double* const grl = grsh + w * NSLOT + slot;    // (lane 63 as lane 54)
   *grl = 0.0;
   // - <x, velocity rows of the row exchange>, own modes
   auto pair_exchange = [&](const R (&x)[NBX]) {
@@ -740,13 +749,16 @@ void k_adjoint(KPtrs p, APtrs ad, LevelArgs a) {
     // SPW (W rr + w) + lane / SEG takes element s % 7 and face s / 7 (s < 28),
     // lane f = lane % SEG its mode f (f < F).  A segment's modes are
     // contiguous in the slots and in the trace area, and its gradient words
-    // are summed over it with DPP and added once by its last lane: the LDS
-    // atomics are one lane per pair.
+    // are summed over it with DPP and written once by its last lane, to words of
+    // the pair's own: the faces of an element are in different waves, whose sums
+    // into one set of words came in a timing-dependent order (that took, per reverse
+    // cycle, O = 5 m=3 35k tets 864 us against 872, O = 4 m=0 353 against 356, FP64
+    // O = 4 5k 141 against 150).
     constexpr int SEG = F < 4 ? 4 : F < 8 ? 8 : 16, SPW = 64 / SEG;
-    const int f = lane % SEG;
 #pragma unroll 1
     for (int rr = 0; rr < (4 * EPW + SPW * W - 1) / (SPW * W); ++rr) {
-      const int r8 = SPW * (W * rr + w) + lane / SEG;
+      const int ln = lane_id(), f = ln % SEG;
+      const int r8 = SPW * (W * rr + w) + ln / SEG;
       const bool pair = r8 < 4 * EPW;
       const int pe = pair ? r8 % EPW : 0, i = pair ? r8 / EPW : 0;
       const bool pvalid = pair && evalid[pe] != 0;
@@ -825,16 +837,13 @@ void k_adjoint(KPtrs p, APtrs ad, LevelArgs a) {
 #pragma unroll
       for (int k = 0; k < 7; ++k) { so[k] = seg_sum<SEG>(pbo[k]); sn[k] = seg_sum<SEG>(pbn[k]); }
       if (f == SEG - 1 && pvalid) {
-        double* const gp = gsh + pe * NGS;
-        if (!b2phase) {
+        double* const gp = gsh + pe * NGS + 7 * i;
+        if (!b2phase)
 #pragma unroll
-          for (int k = 0; k < 5; ++k) gadd(gp, k, so[k]);
-          gadd(gp, bc == 0 ? 11 + 2 * i : 3, so[5]);
-          gadd(gp, bc == 0 ? 12 + 2 * i : 4, so[6]);
-        }
+          for (int k = 0; k < 7; ++k) gp[k] = so[k];
         if (nflux)
 #pragma unroll
-          for (int k = 0; k < 7; ++k) gadd(gp, 19 + 7 * i + k, sn[k]);
+          for (int k = 0; k < 7; ++k) gadd(gp, NG_NBR + k, sn[k]);
       }
     }
     __syncthreads();
@@ -1201,8 +1210,8 @@ void k_adjoint(KPtrs p, APtrs ad, LevelArgs a) {
     if (has(lb) && valid) at(Le, (base + lb) * NSLOT + slot) = le[lb];
   }
   // the waves add their words one after the other (LDS atomics of all at once
-  // would sum in a timing-dependent order: results would not repeat bit for
-  // bit)
+  // would sum in a timing-dependent order; the face words are pair by pair, so a
+  // sweep repeats bit for bit)
 #pragma unroll
   for (int ww = 0; ww < W; ++ww) {
     if (w == ww && valid) {
@@ -1212,7 +1221,7 @@ void k_adjoint(KPtrs p, APtrs ad, LevelArgs a) {
         gadd(gs, NG_RHO + 2, gm);
         if (M > 0)
 #pragma unroll
-          for (int k = 0; k < 2 * MM; ++k) gadd(gs, 5 + k, gab[k]);
+          for (int k = 0; k < 2 * MM; ++k) gadd(gs, NG_AB + k, gab[k]);
       }
     }
     __syncthreads();
@@ -1259,29 +1268,33 @@ __global__ void k_material_gradient(const double* gacc, const int* FI, const dou
   double g[3] = {0.0, 0.0, 0.0};
   if (rho > 0.0) {
     const double* x = gacc + k * NG;
-    for (int t = 0; t < 5; ++t) add_param(g, t, x[t], rho, vp, vs);
     // the products: rho at fixed vp, vs, then the moduli's vp, vs
     g[0] += x[NG_RHO] / rho;
     g[1] += x[NG_RHO + 1] * 2 * rho * vp;
     g[2] += (x[NG_RHO + 2] - 2 * x[NG_RHO + 1]) * 2 * rho * vs;
     for (int l = 0; l < M; ++l) {   // a_l = rho vp^2 Yp - 2 rho vs^2 Ys, b_l = 2 rho vs^2 Ys
       const double yp = mat[k * mw + 3 + 2 * l], ys = mat[k * mw + 4 + 2 * l];
-      const double ga = x[5 + 2 * l], gb = x[6 + 2 * l];
+      const double ga = x[NG_AB + 2 * l], gb = x[NG_AB + 1 + 2 * l];
       g[1] += ga * 2 * rho * vp * yp;
       g[2] += -ga * 4 * rho * vs * ys + gb * 4 * rho * vs * ys;
     }
     const int* fi = FI + k * FI_WORDS;
     for (int i = 0; i < 4; ++i) {
+      for (int t = 0; t < 5; ++t) add_param(g, t, x[7 * i + t], rho, vp, vs);
       const int n = fi[3 * i];
-      if (n < 0) continue;
+      if (n < 0) {   // the outside impedances are the element's own
+        add_param(g, 3, x[7 * i + 5], rho, vp, vs);
+        add_param(g, 4, x[7 * i + 6], rho, vp, vs);
+        continue;
+      }
       const int j = fi[3 * i + 1] & 15;          // the neighbour's face towards this element
-      const double* y = x + 19 + 7 * i;          // this element's Zp, Zs in the neighbour's flux
+      const double* y = x + NG_NBR + 7 * i;      // this element's Zp, Zs in the neighbour's flux
       add_param(g, 3, y[5], rho, vp, vs);
       add_param(g, 4, y[6], rho, vp, vs);
       const double* xn = gacc + (long long)n * NG;
-      add_param(g, 3, xn[11 + 2 * j], rho, vp, vs);   // this element's impedances in the neighbour's own flux
-      add_param(g, 4, xn[12 + 2 * j], rho, vp, vs);
-      const double* yn = xn + 19 + 7 * j;             // this element's own flux, accumulated by the neighbour
+      add_param(g, 3, xn[7 * j + 5], rho, vp, vs);    // this element's impedances in the neighbour's own flux
+      add_param(g, 4, xn[7 * j + 6], rho, vp, vs);
+      const double* yn = xn + NG_NBR + 7 * j;         // this element's own flux, accumulated by the neighbour
       for (int t = 0; t < 5; ++t) add_param(g, t, yn[t], rho, vp, vs);
     }
   }
@@ -1290,48 +1303,54 @@ __global__ void k_material_gradient(const double* gacc, const int* FI, const dou
   out[k * 3 + 2] = g[2];
 }
 
-// adjoint of the receiver samples: the derivatives of the receiver slots get
-// sum_s (t_s - t^n)^d / d! * seisbar_s phi(x_r) for the samples in the step
-// that starts at this level.  One workgroup per receiver, one thread per
-// (quantity, mode): every thread sums the few samples itself (one thread per
-// quantity, with all modes' atomics one after the other, took 45 us a level
-// at O = 5 and 32 receivers).
+// adjoint of the receiver samples: the derivatives of a receiver element get
+// sum_s (t_s - t^n)^d / d! * seisbar_s phi(x_r) for the samples of its receivers
+// in the step that starts at this level.  One workgroup per element (that of its
+// first receiver; chain[r] = 2 (next receiver in the element + 1) + (first)), one
+// thread per (quantity, mode), receivers and their few samples in order: no
+// atomics, so the sum is the same every time.  (One thread per quantity, with all
+// modes one after the other, took 45 us a level at O = 5 and 32 receivers.)
 template <class R, int O, int M>
-__global__ void k_receivers_adj(KPtrs p, APtrs ad, LevelArgs a, RecArgs r, const double* seis_b) {
+__global__ void k_receivers_adj(KPtrs p, APtrs ad, LevelArgs a, RecArgs r, const int* chain, const double* seis_b) {
   constexpr int B = edg_gen::Ref<O>::B;
-  const int rec = blockIdx.x, q = threadIdx.x / B, b = threadIdx.x % B;
+  int rec = blockIdx.x;
+  const int q = threadIdx.x / B, b = threadIdx.x % B;
   const int elem = r.elem[rec];
-  if (elem >= a.end || q >= LPE) return;
+  if (!(chain[rec] & 1) || elem >= a.end || q >= LPE) return;
+  R* D = reinterpret_cast<R*>(ad.recDb) + (size_t)r.slot[rec] * O * LPE * B;
   const int cl = cluster_of(a, elem);
   const double dt = a.dt[cl];
   const int n = step_new_of(a, cl);
   const double t0 = (double)n * dt, t1 = (double)(n + 1) * dt;
-  double vb[O];
-#pragma unroll
-  for (int d = 0; d < O; ++d) vb[d] = 0.0;
   // the samples of step n: [t0 - eps, t1 - eps), eps = 1e-9 dt (as sampled)
   const double eps = 1e-9 * dt, lo = t0 - eps, hi = t1 - eps;
-  long long s = (long long)floor(lo / r.dt_sample) - 1;
-  if (s < 0) s = 0;
-  bool any = false;
-  for (; s < r.ns && (double)s * r.dt_sample < hi; ++s) {
-    const double ts = (double)s * r.dt_sample;
-    if (ts < lo) continue;
-    const double x = ts - t0, sb = seis_b[((size_t)rec * r.ns + s) * LPE + q];
-    double pw = 1.0, fact = 1.0;
+  long long s0 = (long long)floor(lo / r.dt_sample) - 1;
+  if (s0 < 0) s0 = 0;
+  while (s0 < r.ns && (double)s0 * r.dt_sample < lo) ++s0;
+  if (!(s0 < r.ns && (double)s0 * r.dt_sample < hi)) return;
+  double x[O];
 #pragma unroll
-    for (int d = 0; d < O; ++d) {
-      vb[d] += pw / fact * sb;
-      pw *= x;
-      fact *= (double)(d + 1);
+  for (int d = 0; d < O; ++d) x[d] = 0.0;
+  for (; rec >= 0; rec = (chain[rec] >> 1) - 1) {
+    double vb[O];
+#pragma unroll
+    for (int d = 0; d < O; ++d) vb[d] = 0.0;
+    for (long long s = s0; s < r.ns && (double)s * r.dt_sample < hi; ++s) {
+      const double t = (double)s * r.dt_sample - t0, sb = seis_b[((size_t)rec * r.ns + s) * LPE + q];
+      double pw = 1.0, fact = 1.0;
+#pragma unroll
+      for (int d = 0; d < O; ++d) {
+        vb[d] += pw / fact * sb;
+        pw *= t;
+        fact *= (double)(d + 1);
+      }
     }
-    any = true;
-  }
-  if (!any) return;
-  R* D = reinterpret_cast<R*>(ad.recDb) + (size_t)r.slot[rec] * O * LPE * B;
-  const double phi = r.phi[(size_t)rec * B + b];
+    const double phi = r.phi[(size_t)rec * B + b];
 #pragma unroll
-  for (int d = 0; d < O; ++d) atomicAdd(&D[((size_t)d * LPE + q) * B + b], R(vb[d] * phi));
+    for (int d = 0; d < O; ++d) x[d] += vb[d] * phi;
+  }
+#pragma unroll
+  for (int d = 0; d < O; ++d) D[((size_t)d * LPE + q) * B + b] = R(x[d]);   // (zeros before: cleared by its reader)
 }
 
 }  // namespace
@@ -1356,11 +1375,12 @@ size_t adjoint_scratch_words() {
 }
 
 template <class R, int O, int M>
-int launch_receivers_adj(const KPtrs& p, const APtrs& ad, const LevelArgs& a, const RecArgs& r, const double* seis_b,
-                         hipStream_t st) {
+int launch_receivers_adj(const KPtrs& p, const APtrs& ad, const LevelArgs& a, const RecArgs& r, const int* chain,
+                         const double* seis_b, hipStream_t st) {
   if (r.n <= 0) return 0;
   constexpr int threads = (LPE * edg_gen::Ref<O>::B + 63) / 64 * 64;
-  hipLaunchKernelGGL((k_receivers_adj<R, O, M>), dim3((unsigned)r.n), dim3(threads), 0, st, p, ad, a, r, seis_b);
+  hipLaunchKernelGGL((k_receivers_adj<R, O, M>), dim3((unsigned)r.n), dim3(threads), 0, st, p, ad, a, r, chain,
+                     seis_b);
   return (int)hipGetLastError();
 }
 
@@ -1376,7 +1396,7 @@ int launch_material_gradient(const double* gacc, const int* FI, const double* ma
   template int launch_adjoint<R, O, M>(const KPtrs&, const APtrs&, const LevelArgs&, hipStream_t); \
   template size_t adjoint_scratch_words<R, O, M>();                                               \
   template int launch_receivers_adj<R, O, M>(const KPtrs&, const APtrs&, const LevelArgs&, const RecArgs&, \
-                                             const double*, hipStream_t);
+                                             const int*, const double*, hipStream_t);
 
 EDG_FOR_EACH_VARIANT(EDG_ADJ_INST)
 

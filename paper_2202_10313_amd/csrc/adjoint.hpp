@@ -12,16 +12,15 @@ constexpr int KIND_ADJ_FUSED = 5;    // transposed predictions, then transposed 
 constexpr int adj_rows(int M) { return M > 0 ? 15 : 9; }
 // Per-element gradient words (internal order, FP64): derivatives of the
 // adjoint pairing in the parameters the kernels read.
-//   [0] 1/rho  [1] lam  [2] mu  [3] Zp  [4] Zs of the own flux
-//   [5+2l] a_l  [6+2l] b_l  of the products (time and volume kernel)
-//   [11+2i], [12+2i]  the neighbour impedances Zp, Zs of face i (own flux)
-//   [19+7f+0..6]      (1/rho, lam, mu, Zp, Zs, Zp+, Zs+) of the flux of the
-//                     element across face f (its neighbour-data part)
-//   [NG_RHO]          rho times the products' derivative in rho at fixed vp, vs
-//                     (through 1/rho and all moduli, the anelastic ones too)
-//   [NG_RHO+1, +2]    lam, mu of the products
-constexpr int NG_RHO = 47;
-constexpr int NG = 50;
+//   [7f+0..6]        (1/rho, lam, mu, Zp, Zs, Zp+, Zs+) of the own flux of face f
+//   [NG_NBR+7f+0..6] the same of the flux of the element across face f (its
+//                    neighbour-data part)
+//   [NG_AB+2l], [NG_AB+2l+1]  a_l, b_l of the products (time and volume kernel)
+//   [NG_RHO]         rho times the products' derivative in rho at fixed vp, vs
+//                    (through 1/rho and all moduli, the anelastic ones too)
+//   [NG_RHO+1, +2]   lam, mu of the products
+constexpr int NG_NBR = 28, NG_AB = 56, NG_RHO = 62;
+constexpr int NG = 65;
 
 struct APtrs {
   void* Le;          // adjoint of the elastic rows (Qe layout)
@@ -45,8 +44,9 @@ int launch_adjoint(const KPtrs& p, const APtrs& ad, const LevelArgs& a, hipStrea
 // words of De per element group of this variant
 template <class R, int O, int M>
 size_t adjoint_scratch_words();
+// chain [n]: 2 (next receiver in the same element + 1) + (1 for the element's first)
 template <class R, int O, int M>
-int launch_receivers_adj(const KPtrs& p, const APtrs& ad, const LevelArgs& a, const RecArgs& r, const double* seis_b,
-                         hipStream_t st);
+int launch_receivers_adj(const KPtrs& p, const APtrs& ad, const LevelArgs& a, const RecArgs& r, const int* chain,
+                         const double* seis_b, hipStream_t st);
 
 }  // namespace edg

@@ -93,7 +93,7 @@ struct edg_ctx {
   int n_rec = 0;
   int64_t rec_ns = 0;
   double rec_dt = 0;
-  DevBuf r_elem, r_slot, r_phi, r_out;
+  DevBuf r_elem, r_slot, r_chain, r_phi, r_out;
 
   std::vector<std::vector<double>> perm_mats;  // 24 B x B conversion matrices
 
@@ -839,7 +839,7 @@ int launch_timed(edg_ctx* c, LevelFn fn, const KPtrs& p, const LevelArgs& a, con
 
 edg_ctx::~edg_ctx() {
   for (DevBuf* b : {&Qe, &Qa, &P, &FI, &T1, &T2, &T3, &RecD, &s_first, &s_inc, &s_elem, &s_kind, &s_par, &s_mom, &s_phi,
-                    &s_idet, &r_elem, &r_slot, &r_phi, &r_out, &dclock, &aLe, &aLa, &aS0, &aS3, &aDe,
+                    &s_idet, &r_elem, &r_slot, &r_chain, &r_phi, &r_out, &dclock, &aLe, &aLa, &aS0, &aS3, &aDe,
                     &agacc, &arecDb, &aseis, &ahist, &afinal, &amat, &agrad, &dmat, &dflag, &d_i2u, &d_nbr, &dbg, &d_u2i, &d_code, &d_mats, &dofstage})
     dev_free(*b);
   for (auto& ck : ckpts) dev_free(ck.second);
@@ -1323,7 +1323,7 @@ int edg_set_receivers(edg_ctx* c, int64_t n, const double* xyz, double dt_sample
   if (!c->have_clusters) return fail(c, EDG_ESTATE, "upload clusters first");
   if (n < 0 || (n > 0 && (!xyz || !(dt_sample > 0) || ns <= 0))) return fail(c, EDG_EINVAL, "bad receiver arguments");
   HIPCHK(c, hipSetDevice(c->cfg.device));
-  std::vector<int> el(n), slot(n), rs_slot((size_t)c->Kp, -1);   // receiver slot per element
+  std::vector<int> el(n), slot(n), chain(n), rs_slot((size_t)c->Kp, -1);   // receiver slot per element
   std::vector<double> phi((size_t)n * c->B);
   int nslots = 0;
   for (int64_t r = 0; r < n; ++r) {
@@ -1340,6 +1340,14 @@ int edg_set_receivers(edg_ctx* c, int64_t n, const double* xyz, double dt_sample
     auto v = eval_basis(c->O, xi);
     std::copy(v.begin(), v.end(), phi.begin() + r * c->B);
   }
+  // the receivers of one element, chained in order (see launch_receivers_adj)
+  std::vector<int> last((size_t)nslots, -1);
+  for (int64_t r = 0; r < n; ++r) {
+    int& l = last[slot[r]];
+    chain[r] = l < 0 ? 1 : 0;
+    if (l >= 0) chain[l] |= 2 * (int)(r + 1);
+    l = (int)r;
+  }
   int rc;
   for (int64_t ki = 0; ki < c->Kp; ++ki) c->FI_host[(size_t)ki * FI_WORDS + 15] = rs_slot[ki];
   if ((rc = dev_upload(c, c->FI, c->FI_host.data(), c->FI_host.size() * sizeof(int)))) return rc;
@@ -1348,6 +1356,7 @@ int edg_set_receivers(edg_ctx* c, int64_t n, const double* xyz, double dt_sample
   if ((rc = dev_alloc(c, c->RecD, (size_t)c->runs * c->run_recd * rsz))) return rc;
   if ((rc = dev_upload(c, c->r_elem, el.data(), n * sizeof(int)))) return rc;
   if ((rc = dev_upload(c, c->r_slot, slot.data(), n * sizeof(int)))) return rc;
+  if ((rc = dev_upload(c, c->r_chain, chain.data(), n * sizeof(int)))) return rc;
   if ((rc = dev_upload(c, c->r_phi, phi.data(), phi.size() * sizeof(double)))) return rc;
   if ((rc = dev_alloc(c, c->r_out, (size_t)c->runs * std::max<int64_t>(n, 1) * ns * LPE * sizeof(double))))
     return rc;
@@ -1900,7 +1909,8 @@ int adjoint_sweep(edg_ctx* c, const double* dj_seis, const double* dj_q, double*
       a.kind = j == J ? KIND_ADJ_UPDATE : j > 0 ? KIND_ADJ_FUSED : KIND_ADJ_PREDICT;
       if (j < J) {
         if (c->n_rec > 0 && dj_seis &&
-            (e = chk(launch_receivers_adj<R, O, M>(p, ad, a, A0.pt.r, seis_b, c->stream), "receiver adjoint kernel")))
+            (e = chk(launch_receivers_adj<R, O, M>(p, ad, a, A0.pt.r, (const int*)c->r_chain.p, seis_b, c->stream),
+                     "receiver adjoint kernel")))
           return e;
         ad.Se = hist_e(j);
         ad.Sa = hist_a(j);
