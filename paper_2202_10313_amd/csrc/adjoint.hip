@@ -755,6 +755,9 @@ void k_adjoint(KPtrs p, APtrs ad, LevelArgs a) {
     // cycle, O = 5 m=3 35k tets 864 us against 872, O = 4 m=0 353 against 356, FP64
     // O = 4 5k 141 against 150).
     constexpr int SEG = F < 4 ? 4 : F < 8 ? 8 : 16, SPW = 64 / SEG;
+    // (the sums are FP64 up to O = 3, where each costs two or three additions; at
+    // O = 4, 5 FP32 over sixteen lanes, FP64 from there on)
+    typedef typename std::conditional<sizeof(R) == 8 || O <= 3, double, float>::type WS;
 #pragma unroll 1
     for (int rr = 0; rr < (4 * EPW + SPW * W - 1) / (SPW * W); ++rr) {
       const int ln = lane_id(), f = ln % SEG;
@@ -833,9 +836,9 @@ void k_adjoint(KPtrs p, APtrs ad, LevelArgs a) {
         for (int k = 0; k < 9; ++k) pmp[(i * LPE + k) * FS + f] = tb[k];
       }
       // the segment sums, every lane taking part (uniform control flow)
-      R so[7], sn[7];
+      WS so[7], sn[7];
 #pragma unroll
-      for (int k = 0; k < 7; ++k) { so[k] = seg_sum<SEG>(pbo[k]); sn[k] = seg_sum<SEG>(pbn[k]); }
+      for (int k = 0; k < 7; ++k) { so[k] = seg_sum<SEG>(WS(pbo[k])); sn[k] = seg_sum<SEG>(WS(pbn[k])); }
       if (f == SEG - 1 && pvalid) {
         double* const gp = gsh + pe * NGS + 7 * i;
         if (!b2phase)
@@ -904,15 +907,17 @@ void k_adjoint(KPtrs p, APtrs ad, LevelArgs a) {
   }
   __syncthreads();
   // Material words, summed in registers over the whole kernel: a product's
-  // adjoint rows x paired with the strain rates give dJ/dlam (tr x tr eps) and
-  // dJ/dmu (2 x : eps), mode by mode in the lane that owns the mode.
+  // adjoint rows x paired with the strain rates give dJ/dlam (tr x tr eps, row by
+  // row: the rows' FP32 sum would round before FP64) and dJ/dmu (2 x : eps), mode
+  // by mode in the lane that owns the mode.
   double gl = 0.0, gm = 0.0, gr = *grl;
   auto strain_words = [&](const R* eps, const R* x, const double sign) {
     double s = 0.0;
 #pragma unroll
     for (int c = 0; c < 6; ++c) s += (double)(x[c] * (R(2) * eps[c]));
     gm += sign * s;
-    gl += sign * (double)((x[0] + x[1] + x[2]) * (eps[0] + eps[1] + eps[2]));
+    const R div = eps[0] + eps[1] + eps[2];
+    gl += sign * ((double)(x[0] * div) + (double)(x[1] * div) + (double)(x[2] * div));
   };
   if (!is_stress) {
     double s = 0.0;
