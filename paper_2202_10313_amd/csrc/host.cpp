@@ -445,7 +445,7 @@ int ensure_dof_tables(edg_ctx* c, DofTables* t) {
 // keeps the buffer), less where the device has no room for it.
 int reserve_dof_stage(edg_ctx* c, int64_t* n) {
   const size_t per = (size_t)c->NQ * c->B * sizeof(double);
-  int64_t want = std::min<int64_t>(c->K, std::max<int64_t>(1, (int64_t)((64u << 20) / per)));
+  int64_t want = std::min<int64_t>(std::min<int64_t>(c->K, DOF_LAUNCH), std::max<int64_t>(1, (int64_t)((64u << 20) / per)));
   const std::string err = c->err;
   int rc;
   while ((rc = dev_reserve(c, c->dofstage, want * per)) && want > 1) want = (want + 7) / 8;
@@ -462,7 +462,7 @@ int reserve_dof_stage(edg_ctx* c, int64_t* n) {
 template <class R>
 int set_dofs_to(edg_ctx* c, void* dqe, void* dqa, const double* dofs, bool dev = false) {
   DofTables t;
-  int64_t step = c->K;
+  int64_t step = std::min<int64_t>(c->K, DOF_LAUNCH);
   int rc = ensure_dof_tables(c, &t);
   if (rc || (!dev && (rc = reserve_dof_stage(c, &step)))) return rc;
   const size_t per = (size_t)c->NQ * c->B;
@@ -488,7 +488,7 @@ int set_dofs_t(edg_ctx* c, int run, const double* dofs) {
 template <class R>
 int get_dofs_from(edg_ctx* c, const void* dqe, const void* dqa, double* out, bool dev = false) {
   DofTables t;
-  int64_t step = c->K;
+  int64_t step = std::min<int64_t>(c->K, DOF_LAUNCH);
   int rc = ensure_dof_tables(c, &t);
   if (rc || (!dev && (rc = reserve_dof_stage(c, &step)))) return rc;
   const size_t per = (size_t)c->NQ * c->B;

@@ -153,8 +153,13 @@ struct DofTables {
   const double* mats;
   int B, M;
 };
-// dofs: device FP64 [n][9 + 6M][B] of caller elements k0 .. k0 + n - 1; Qe, Qa:
-// one run's state (the matrices are orthogonal, so adjoints convert the same way)
+// elements per launch: one workgroup of 256 threads each, and a launch has fewer
+// than 2^32 threads (device arrays of 2^24 elements in one launch were refused)
+constexpr long long DOF_LAUNCH = 1 << 18;
+static_assert(DOF_LAUNCH * 256 < (1ll << 32), "threads of a launch");
+// dofs: device FP64 [n][9 + 6M][B] of caller elements k0 .. k0 + n - 1, n <=
+// DOF_LAUNCH; Qe, Qa: one run's state (the matrices are orthogonal, so adjoints
+// convert the same way)
 template <class R>
 int launch_set_dofs(const DofTables& t, long long k0, long long n, const double* dofs, R* Qe, R* Qa, hipStream_t st);
 template <class R>

@@ -20,12 +20,11 @@
 #include <hip/hip_runtime.h>
 
 #include "kernels.hpp"
+#include "device_common.hpp"
 
 namespace edg {
 
 namespace {
-
-constexpr int EPW = 7, LPE = 9, NSLOT = EPW * LPE;
 
 // word of quantity q, mode b of internal element ki: index in Qe (q < 9) or Qa
 __device__ __forceinline__ size_t state_index(const DofTables& t, long long ki, int q, int b) {
@@ -86,6 +85,7 @@ __global__ __launch_bounds__(256) void k_get_dofs(DofTables t, long long k0, dou
 template <class R>
 int launch_set_dofs(const DofTables& t, long long k0, long long n, const double* dofs, R* Qe, R* Qa, hipStream_t st) {
   if (n <= 0) return 0;
+  if (n > DOF_LAUNCH) return (int)hipErrorInvalidValue;
   hipLaunchKernelGGL((k_set_dofs<R>), dim3((unsigned)n), dim3(256), 0, st, t, k0, dofs, Qe, Qa);
   return (int)hipGetLastError();
 }
@@ -94,6 +94,7 @@ template <class R>
 int launch_get_dofs(const DofTables& t, long long k0, long long n, double* dofs, const R* Qe, const R* Qa,
                     hipStream_t st) {
   if (n <= 0) return 0;
+  if (n > DOF_LAUNCH) return (int)hipErrorInvalidValue;
   hipLaunchKernelGGL((k_get_dofs<R>), dim3((unsigned)n), dim3(256), 0, st, t, k0, dofs, Qe, Qa);
   return (int)hipGetLastError();
 }
