@@ -8,6 +8,7 @@
 #include <cmath>
 #include <cstdio>
 #include <cstring>
+#include <iterator>
 #include <memory>
 #include <new>
 #include <numeric>
@@ -86,9 +87,10 @@ struct edg_ctx {
     std::vector<double> phi;
   };
   std::vector<std::vector<Source>> src_of_run;
-  int n_src = 0;
-  int src_per_run = 0;              // the most sources of a run
-  DevBuf s_first, s_inc, s_elem, s_kind, s_par, s_mom, s_phi, s_idet;
+  int n_src = 0;                    // source packets of all runs (see SrcArgs)
+  int src_per_run = 0;              // the most packets of a run
+  DevBuf s_group, s_at, s_what, s_run, s_elem, s_first, s_inc, s_kind, s_par, s_mom, s_phi, s_idet;
+  std::vector<int64_t> src_groups;      // the groups with sources, run * G + group
   // receivers
   int n_rec = 0;
   int64_t rec_ns = 0;
@@ -192,6 +194,14 @@ int dev_upload(edg_ctx* c, DevBuf& b, const void* src, size_t bytes) {
   int rc = dev_alloc(c, b, bytes);
   if (rc) return rc;
   HIPCHK(c, hipMemcpy(b.p, src, bytes, hipMemcpyHostToDevice));
+  return 0;
+}
+
+// the same into the buffer that is there, if it is large enough
+int dev_put(edg_ctx* c, DevBuf& b, const void* src, size_t bytes) {
+  int rc = dev_reserve(c, b, bytes);
+  if (rc) return rc;
+  if (bytes) HIPCHK(c, hipMemcpy(b.p, src, bytes, hipMemcpyHostToDevice));
   return 0;
 }
 
@@ -838,7 +848,7 @@ int launch_timed(edg_ctx* c, LevelFn fn, const KPtrs& p, const LevelArgs& a, con
 }  // namespace
 
 edg_ctx::~edg_ctx() {
-  for (DevBuf* b : {&Qe, &Qa, &P, &FI, &T1, &T2, &T3, &RecD, &s_first, &s_inc, &s_elem, &s_kind, &s_par, &s_mom, &s_phi,
+  for (DevBuf* b : {&Qe, &Qa, &P, &FI, &T1, &T2, &T3, &RecD, &s_group, &s_at, &s_what, &s_run, &s_elem, &s_first, &s_inc, &s_kind, &s_par, &s_mom, &s_phi,
                     &s_idet, &r_elem, &r_slot, &r_chain, &r_phi, &r_out, &dclock, &aLe, &aLa, &aS0, &aS3, &aDe,
                     &agacc, &arecDb, &aseis, &ahist, &afinal, &amat, &agrad, &dmat, &dflag, &d_i2u, &d_nbr, &dbg, &d_u2i, &d_code, &d_mats, &dofstage})
     dev_free(*b);
@@ -1185,6 +1195,7 @@ int edg_upload_clusters(edg_ctx* c, const int32_t* cluster) {
   HIPCHK(c, hipMemset(c->T3.p, 0, c->T3.bytes));
   c->n_rec = 0;
   c->n_src = 0;
+  dev_free(c->s_group);
   for (auto& v : c->src_of_run) v.clear();
   drop_graph(c);
   if ((rc = dev_alloc(c, c->dclock, 3 * sizeof(long long)))) return rc;
@@ -1282,38 +1293,76 @@ int edg_set_sources(edg_ctx* c, int32_t run, int64_t n, const double* xyz, const
   std::stable_sort(list.begin(), list.end(), [](const auto& x, const auto& y) { return x.elem < y.elem; });
   c->src_of_run[run] = std::move(list);
   drop_graph(c);
-  // the device list holds the sources of every run, by element, and where each
-  // element group's begin
-  std::vector<int> el, kd, first;
+  // the device lists hold the sources of every run, by element, and where each
+  // element's and each element group's begin
+  std::vector<int> el, first, kd, entries, run_first(1, 0);
+  std::vector<int64_t> groups;
   std::vector<double> pr, mo, phi, idet;
   size_t per_run = 0;
   for (int r = 0; r < c->runs; ++r) {
-    per_run = std::max(per_run, c->src_of_run[r].size());
-    for (int64_t g = 0, i = 0; g <= c->G; ++g) {
-      while (i < (int64_t)c->src_of_run[r].size() && c->src_of_run[r][i].elem < g * EPW) ++i;
-      first.push_back((int)(el.size() + i));
-    }
+    const int begin = (int)el.size();
     for (const auto& src : c->src_of_run[r]) {
-      el.push_back(src.elem);
+      if ((int)el.size() == begin || el.back() != src.elem || (int)kd.size() - first.back() == SRC_PACKET) {
+        const int64_t group = r * c->G + src.elem / EPW;
+        if (groups.empty() || groups.back() != group) {
+          groups.push_back(group);
+          entries.insert(entries.end(), {(int)el.size(), 0});
+        }
+        el.push_back(src.elem);
+        idet.push_back(src.idet);
+        first.push_back((int)kd.size());
+        entries.back() = (int)el.size();
+      }
       kd.push_back(src.kind);
       pr.insert(pr.end(), src.par, src.par + 2);
       mo.insert(mo.end(), src.moment, src.moment + 6);
       phi.insert(phi.end(), src.phi.begin(), src.phi.end());
-      idet.push_back(src.idet);
+    }
+    run_first.push_back((int)el.size());
+    per_run = std::max(per_run, el.size() - begin);
+  }
+  first.push_back((int)kd.size());
+  const size_t ne = el.size(), ns = kd.size();
+  int rc;
+  c->n_src = 0;   // (none until all of the lists are there)
+  // the table of the groups: what the lists before had set is cleared, then set as now
+  if (!c->s_group.p) {
+    if (ne) {
+      if ((rc = dev_alloc(c, c->s_group, (size_t)c->runs * c->G * 2 * sizeof(int)))) return rc;
+      HIPCHK(c, hipMemsetAsync(c->s_group.p, 0, c->s_group.bytes, c->stream));
+    }
+    c->src_groups.clear();
+  }
+  std::vector<int64_t> at;
+  std::set_difference(c->src_groups.begin(), c->src_groups.end(), groups.begin(), groups.end(), std::back_inserter(at));
+  std::vector<int> what(2 * at.size(), 0);
+  at.insert(at.end(), groups.begin(), groups.end());
+  what.insert(what.end(), entries.begin(), entries.end());
+  if (!at.empty()) {
+    if ((rc = dev_put(c, c->s_at, at.data(), at.size() * sizeof(int64_t))) ||
+        (rc = dev_put(c, c->s_what, what.data(), what.size() * sizeof(int)))) {
+      dev_free(c->s_group);
+      return rc;
+    }
+    rc = launch_scatter_pairs((int*)c->s_group.p, (const long long*)c->s_at.p, (const int*)c->s_what.p,
+                              (long long)at.size(), c->stream);
+    if (!rc) rc = (int)hipStreamSynchronize(c->stream);
+    if (rc) {
+      dev_free(c->s_group);
+      return fail(c, EDG_EHIP, std::string("source table kernel: ") + hipGetErrorString((hipError_t)rc));
     }
   }
-  const size_t ns = el.size();
-  int rc;
-  c->n_src = 0;   // (none until all of the list is there)
-  if ((rc = dev_upload(c, c->s_first, first.data(), ns ? first.size() * sizeof(int) : 0))) return rc;
-  if ((rc = dev_alloc(c, c->s_inc, 2 * ns * 6 * c->B * (c->cfg.fp64 ? sizeof(double) : sizeof(float))))) return rc;
-  if ((rc = dev_upload(c, c->s_elem, el.data(), ns * sizeof(int)))) return rc;
-  if ((rc = dev_upload(c, c->s_kind, kd.data(), ns * sizeof(int)))) return rc;
-  if ((rc = dev_upload(c, c->s_par, pr.data(), pr.size() * sizeof(double)))) return rc;
-  if ((rc = dev_upload(c, c->s_mom, mo.data(), mo.size() * sizeof(double)))) return rc;
-  if ((rc = dev_upload(c, c->s_phi, phi.data(), phi.size() * sizeof(double)))) return rc;
-  if ((rc = dev_upload(c, c->s_idet, idet.data(), ns * sizeof(double)))) return rc;
-  c->n_src = (int)ns;
+  c->src_groups = std::move(groups);
+  if ((rc = dev_reserve(c, c->s_inc, 2 * ne * 6 * c->B * (c->cfg.fp64 ? sizeof(double) : sizeof(float))))) return rc;
+  if ((rc = dev_put(c, c->s_run, run_first.data(), run_first.size() * sizeof(int)))) return rc;
+  if ((rc = dev_put(c, c->s_elem, el.data(), ne * sizeof(int)))) return rc;
+  if ((rc = dev_put(c, c->s_first, first.data(), first.size() * sizeof(int)))) return rc;
+  if ((rc = dev_put(c, c->s_kind, kd.data(), ns * sizeof(int)))) return rc;
+  if ((rc = dev_put(c, c->s_par, pr.data(), pr.size() * sizeof(double)))) return rc;
+  if ((rc = dev_put(c, c->s_mom, mo.data(), mo.size() * sizeof(double)))) return rc;
+  if ((rc = dev_put(c, c->s_phi, phi.data(), phi.size() * sizeof(double)))) return rc;
+  if ((rc = dev_put(c, c->s_idet, idet.data(), ne * sizeof(double)))) return rc;
+  c->n_src = (int)ne;
   c->src_per_run = (int)per_run;
   return EDG_OK;
 }
@@ -1385,10 +1434,12 @@ AdvanceArgs advance_args(edg_ctx* c) {
   SrcArgs& sa = A.pt.s;
   sa.n = c->n_src;
   sa.per_run = c->src_per_run;
-  sa.first = (const int*)(c->n_src ? c->s_first.p : (char*)c->dclock.p + 2 * sizeof(long long));
-  sa.row = c->n_src ? (int)c->G + 1 : 0;
-  sa.col = c->n_src ? 1 : 0;
+  sa.group = (const int*)(c->n_src ? c->s_group.p : (char*)c->dclock.p + 2 * sizeof(long long));
+  sa.row = c->n_src ? 2 * (int)c->G : 0;
+  sa.col = c->n_src ? 2 : 0;
+  sa.run_first = (const int*)c->s_run.p;
   sa.elem = (const int*)c->s_elem.p;
+  sa.first = (const int*)c->s_first.p;
   sa.kind = (const int*)c->s_kind.p;
   sa.par = (const double*)c->s_par.p;
   sa.moment = (const double*)c->s_mom.p;
@@ -1939,7 +1990,8 @@ int adjoint_sweep(edg_ctx* c, const double* dj_seis, const double* dj_q, double*
   for (int run = 0; run < c->runs; ++run) {
     // this run's sources (a replay's launches have one run, the first)
     AdvanceArgs A = A0;
-    A.pt.s.first += (size_t)run * A.pt.s.row;
+    A.pt.s.group += (size_t)run * A.pt.s.row;
+    if (c->n_src) A.pt.s.run_first += run;
     for (DevBuf* b : {&c->aLe, &c->aLa, &c->aseis}) HIPCHK(c, hipMemsetAsync(b->p, 0, b->bytes, c->stream));
     HIPCHK(c, hipStreamSynchronize(c->stream));
     if (dj_q) {

@@ -162,6 +162,14 @@ __device__ __forceinline__ double stf_antiderivative(int kind, double p0, double
   return (tau - p1 / (2.0 * M_PI) * sin(2.0 * M_PI * tau / p1)) / p1;
 }
 
+// v of lane i (uniform)
+__device__ __forceinline__ double lane_value(double v, int i) {
+  const unsigned long long u = __builtin_bit_cast(unsigned long long, v);
+  const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)u, i);
+  const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)(u >> 32), i);
+  return __builtin_bit_cast(double, (unsigned long long)hi << 32 | lo);
+}
+
 // The points of a level launch (see PointArgs), one wave each, beside the element
 // groups.  As a launch of their own between two levels they cost 4.9 us per
 // level of nothing but latency (three launches before that: 12); here nothing
@@ -169,7 +177,10 @@ __device__ __forceinline__ double stf_antiderivative(int kind, double p0, double
 // source is evaluated one level ahead.  Measured (us per shot): 5k tets O = 4 m=3
 // 1,095 -> 885, five-cluster basin 8k O = 5 1,237 -> 1,105, 62k 4,985 -> 4,870,
 // 997k 20,270 -> 20,160; a mesh without points pays 0.4 us a level for the branch
-// and the longer argument block (plane wave check 642 -> 666).
+// and the longer argument block (plane wave check 642 -> 666).  The sources of
+// one element are summed in packets of a wavefront, a lane each: 1,024 of them in
+// one element, O = 4, 20 cycles, cost 6,099 us one after another and 305 so (272
+// spread over the mesh).
 // vals: LDS of O x 9 doubles per wave.
 template <class R, int O, int KIND, int W>
 __device__ __forceinline__ void level_points(const KPtrs& p, const LevelArgs& a, const PointArgs& pt, double* vals) {
@@ -221,21 +232,43 @@ __device__ __forceinline__ void level_points(const KPtrs& p, const LevelArgs& a,
         out[s * LPE + lane] = acc;
       }
   } else if (KIND != KIND_NEIGHBOR && pt.s.n > 0) {
-    // a source of a step that ends at level + 1
+    // a packet of sources of one element, in a step that ends at level + 1: each
+    // lane evaluates the moment rate of one, then all of them form the words
     const SrcArgs& s = pt.s;
-    const int* const first = s.first + (size_t)run * s.row;
-    const int src = first[0] + (item - n_rec);
-    if (src >= first[s.row - 1]) return;
-    const int cl = cluster_of(a, s.elem[src]);
+    const int se = s.run_first[run] + (item - n_rec);
+    if (se >= s.run_first[run + 1]) return;
+    const int cl = cluster_of(a, s.elem[se]);
     if ((level + 1) & ((1ll << cl) - 1)) return;
     const double dt = a.dt[cl];
     const int n = (int)((level + 1) >> cl) - 1;
     const double t0 = (double)n * dt, t1 = (double)(n + 1) * dt;
-    const double f = stf_antiderivative(s.kind[src], s.par[2 * src], s.par[2 * src + 1], t1) -
-                     stf_antiderivative(s.kind[src], s.par[2 * src], s.par[2 * src + 1], t0);
-    R* const inc = reinterpret_cast<R*>(s.inc) + ((size_t)((level + 1) & 1) * s.n + src) * (6 * B);
-    for (int k = lane; k < 6 * B; k += 64)
-      inc[k] = R(-s.moment[6 * src + k / B] * s.phi[(size_t)src * B + k % B] * s.inv_det[src] * f);
+    constexpr int NW = (6 * B + 63) / 64;
+    double acc[NW];
+#pragma unroll
+    for (int k = 0; k < NW; ++k) acc[k] = 0.0;
+    const int src0 = s.first[se], m = s.first[se + 1] - src0;
+    const int mine = src0 + (lane < m ? lane : 0);
+    const double f = stf_antiderivative(s.kind[mine], s.par[2 * mine], s.par[2 * mine + 1], t1) -
+                     stf_antiderivative(s.kind[mine], s.par[2 * mine], s.par[2 * mine + 1], t0);
+    const double idet = s.inv_det[se];
+    const double *mo[NW], *ph[NW];
+#pragma unroll
+    for (int k = 0; k < NW; ++k) {
+      const int wd = lane + 64 * k < 6 * B ? lane + 64 * k : 0;
+      mo[k] = s.moment + 6 * (size_t)src0 + wd / B;
+      ph[k] = s.phi + (size_t)src0 * B + wd % B;
+    }
+    static_assert(SRC_PACKET == 64, "a lane per source");
+#pragma unroll 8
+    for (int i = 0; i < m; ++i) {
+      const double fi = lane_value(f, i);
+#pragma unroll
+      for (int k = 0; k < NW; ++k) acc[k] += -mo[k][6 * i] * ph[k][i * B] * idet * fi;
+    }
+    R* const inc = reinterpret_cast<R*>(s.inc) + ((size_t)((level + 1) & 1) * s.n + se) * (6 * B);
+#pragma unroll
+    for (int k = 0; k < NW; ++k)
+      if (lane + 64 * k < 6 * B) inc[lane + 64 * k] = R(acc[k]);
   }
 }
 
@@ -280,12 +313,12 @@ void k_level(LevelArgs a, KPtrs p, PointArgs pt) {
   int g, run;
   group_and_run(a, g, run);
   select_run<R>(p, run);
-  // the group's sources (asked for here: their count is needed in mid-kernel)
+  // the group's source packets (asked for here: their number is needed in mid-kernel)
   int src0 = 0, src1 = 0;
   if constexpr (KIND != KIND_PREDICT) {
-    const int* const first = pt.s.first + (size_t)run * pt.s.row + (size_t)g * pt.s.col;
-    src0 = first[0];
-    src1 = first[1];
+    const int* const s = pt.s.group + (size_t)run * pt.s.row + (size_t)g * pt.s.col;
+    src0 = s[0];
+    src1 = s[1];
   }
   const int elem = g * EPW + ec;
   const int cl = cluster_of(a, g * EPW);        // one cluster per workgroup (uniform)
@@ -503,7 +536,7 @@ void k_level(LevelArgs a, KPtrs p, PointArgs pt) {
         for (int f = 0; f < FP; ++f) pf[i * FP + f] = f < L::FW ? fac[((i * 2 + 0) * LPE + q) * FS + f] : R(0);
       RF::template lift_w<W>(w, pf, da);
     }
-    // the group's sources, if any (uniform)
+    // the group's source packets, if any (uniform)
     for (int src = src0; src < src1; ++src) {
       const SrcArgs& s = pt.s;
       const R* const inc = reinterpret_cast<const R*>(s.inc) +
@@ -914,6 +947,19 @@ int launch_clock(long long* clock, long long set, hipStream_t st) {
   return (int)hipGetLastError();
 }
 
+__global__ __launch_bounds__(256) void k_scatter_pairs(int* p, const long long* at, const int* what, long long n) {
+  const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
+  if (i >= n) return;
+  p[2 * at[i]] = what[2 * i];
+  p[2 * at[i] + 1] = what[2 * i + 1];
+}
+
+int launch_scatter_pairs(int* p, const long long* at, const int* what, long long n, hipStream_t st) {
+  if (n <= 0) return 0;
+  hipLaunchKernelGGL(k_scatter_pairs, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, p, at, what, n);
+  return (int)hipGetLastError();
+}
+
 __global__ void k_zero_words(uint32_t* p, size_t words) {
   const size_t stride = (size_t)gridDim.x * blockDim.x;
   for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < words; i += stride) p[i] = 0u;
@@ -955,7 +1001,7 @@ int launch_level(const KPtrs& p, LevelArgs a, const PointArgs& pt, int runs, hip
   if (runs <= 0) return 0;
   const bool tm = std::is_same<R, float>::value && O >= 4 && a.trace_mfma;
   const int waves = tm ? 2 : LEVEL_W<O>;
-  // a wave per point; rows of a multiple of eight workgroups (see group_and_run)
+  // a wave per point (a source packet is one); rows of a multiple of eight workgroups (see group_and_run)
   const long long items = (a.kind == KIND_PREDICT ? 0ll : pt.r.n) +
                           (a.kind == KIND_NEIGHBOR || pt.s.n == 0 ? 0 : pt.s.per_run);
   a.groups = (a.end + EPW - 1) / EPW;

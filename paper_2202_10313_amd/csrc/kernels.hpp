@@ -84,22 +84,26 @@ struct LevelArgs {
   void* rec_a;
 };
 
+// Sources in packets of up to SRC_PACKET of one element, listed run by run, by
+// element in each run.
+constexpr int SRC_PACKET = 64;
 struct SrcArgs {
-  // [run][groups + 1]: first[g] .. first[g + 1] are the run's sources in group
-  // g; the arrays below hold the sources run by run, by element in each.  With
-  // no source: two zeros, and row and col, the strides of the run and of the
-  // group, are 0.
-  const int* first;
+  // [run][groups][2]: the packets of a group, first and past the last.  With no
+  // source: two zeros, and row and col, the strides of the run and of the group,
+  // are 0.
+  const int* group;
   int row, col;
-  int n;                  // sources of all runs (0: the rest is not read)
-  int per_run;            // the most sources of a run
-  const int* elem;
+  int n;                  // packets of all runs (0: the rest is not read)
+  int per_run;            // the most packets of a run
+  const int* run_first;   // [runs + 1] first packet of a run
+  const int* elem;        // [n] the element
+  const int* first;       // [n + 1] its first source; below by source
   const int* kind;
-  const double* par;      // [n][2]
-  const double* moment;   // [n][6]
-  const double* phi;      // [n][B]
-  const double* inv_det;  // [n]
-  void* inc;              // [2][n][6][B] what a source adds to its element, by level parity
+  const double* par;      // [sources][2]
+  const double* moment;   // [sources][6]
+  const double* phi;      // [sources][B]
+  const double* inv_det;  // [n], of the element
+  void* inc;              // [2][n][6][B] what a packet adds to its element, by level parity
 };
 
 struct RecArgs {
@@ -113,9 +117,9 @@ struct RecArgs {
 };
 
 // The points of a launch of level j: its first workgroups sample the receivers
-// in the steps that started at level j - 1 and evaluate what the sources of the
-// steps that end at level j + 1 add; the element groups add what the launch
-// before evaluated for the steps that end at j.
+// in the steps that started at level j - 1 and sum what the sources of the steps
+// that end at level j + 1 add, packet by packet; the element groups add what the
+// launch before summed for the steps that end at j.
 struct PointArgs {
   SrcArgs s;
   RecArgs r;
@@ -170,6 +174,8 @@ template <class R, int O, int M>
 int launch_level(const KPtrs& p, LevelArgs a, const PointArgs& pt, int runs, hipStream_t st);
 // *clock = set
 int launch_clock(long long* clock, long long set, hipStream_t st);
+// the pair at[i] of p = the pair i of what, i < n
+int launch_scatter_pairs(int* p, const long long* at, const int* what, long long n, hipStream_t st);
 // zero `words` 32-bit words at p (a fill kernel: no memset node in a capture)
 int launch_zero_words(void* p, size_t words, hipStream_t st);
 
