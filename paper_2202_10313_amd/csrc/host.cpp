@@ -1036,6 +1036,7 @@ int upload_materials_device(edg_ctx* c, const double* rho, const double* vp, con
     HIPCHK(c, hipMemcpyAsync(d + 3 * K, yp, K * M * sizeof(double), hipMemcpyDeviceToDevice, c->stream));
     HIPCHK(c, hipMemcpyAsync(d + 3 * K + K * M, ys, K * M * sizeof(double), hipMemcpyDeviceToDevice, c->stream));
   }
+  if (c->omega != om) drop_graph(c);   // it holds the frequencies by value
   c->omega = om;
   c->mat_host_valid = false;
   c->have_mat = true;
@@ -1075,6 +1076,7 @@ int edg_upload_materials(edg_ctx* c, const double* rho, const double* vp, const 
   c->vp.assign(vp, vp + K);
   c->vs.assign(vs, vs + K);
   if (c->M > 0) {
+    if (!std::equal(c->omega.begin(), c->omega.end(), omega, omega + c->M)) drop_graph(c);   // it holds them by value
     c->omega.assign(omega, omega + c->M);
     c->yp.assign(yp, yp + K * c->M);
     c->ys.assign(ys, ys + K * c->M);
