@@ -65,6 +65,7 @@ class Simulation:
         self.t_end = float(t_end)
         self.attn = None if omega is None else (omega, yp, ys)
         self._q0 = None if q0 is None else np.asarray(q0, dtype=np.float64)
+        self._shape = (context.K, context.nq, context.B)     # of the rest state
         self.every = int(checkpoint_every)
         self.generation = 0          # forwards run so far (a backward checks it is still its own)
 
@@ -75,7 +76,7 @@ class Simulation:
         the device (FP64 O = 4, 5k tets, run and gradient 1.53 -> 1.29 ms, most
         of it the array of zeros through the host link)."""
         if self._q0 is None:
-            self._q0 = np.zeros((self.context.K, self.context.nq, self.context.B))
+            self._q0 = np.zeros(self._shape)
         return self._q0
 
     @q0.setter
@@ -91,8 +92,8 @@ class Simulation:
             c.upload_materials(rho, vp, vs, *self.attn)
         c.rewind()
         c.set_checkpointing(self.every)
-        if self._q0 is not None:
-            c.set_initial(self._q0)
+        if self._q0 is not None or self._shape != (c.K, c.nq, c.B):   # (refuses a state of another mesh)
+            c.set_initial(self.q0)
         c.advance_to(self.t_end)
         self.generation += 1
 
