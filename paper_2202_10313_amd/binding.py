@@ -231,8 +231,9 @@ class Context:
 
     def set_receivers(self, xyz, dt_sample, n_samples):
         xyz = _f64(xyz).reshape(-1, 3)
-        self.n_rec, self.n_samples = xyz.shape[0], int(n_samples)
-        self._chk(self._L.edg_set_receivers(self.h, self.n_rec, _ptr(xyz), float(dt_sample), int(n_samples)))
+        n, ns = xyz.shape[0], int(n_samples)
+        self._chk(self._L.edg_set_receivers(self.h, n, _ptr(xyz), float(dt_sample), ns))
+        self.n_rec, self.n_samples = n, ns
 
     # --- stepping and output
     def advance_to(self, t):

@@ -1134,6 +1134,7 @@ int edg_upload_clusters(edg_ctx* c, const int32_t* cluster) {
     cluster_all(K, dt.data(), c->nbr.data(), Nc, c->cfg.lambda, c->cl, c->lam, c->speedup);
   }
   for (int l = 0; l < MAX_CLUSTERS; ++l) c->dt_cl[l] = std::ldexp(c->lam * c->dt_min, l);
+  c->have_clusters = false;   // (until all of its tables and buffers are there)
   // reorder: by cluster, then caller order; every cluster range starts on a
   // group boundary so that a workgroup never mixes clusters
   for (int l = 0; l < MAX_CLUSTERS; ++l) c->cl_count[l] = 0;
@@ -1399,20 +1400,35 @@ int edg_set_receivers(edg_ctx* c, int64_t n, const double* xyz, double dt_sample
     if (l >= 0) chain[l] |= 2 * (int)(r + 1);
     l = (int)r;
   }
-  int rc;
-  for (int64_t ki = 0; ki < c->Kp; ++ki) c->FI_host[(size_t)ki * FI_WORDS + 15] = rs_slot[ki];
-  if ((rc = dev_upload(c, c->FI, c->FI_host.data(), c->FI_host.size() * sizeof(int)))) return rc;
+  if (n > 0 && ns > INT64_MAX / n / c->runs / (int64_t)(LPE * sizeof(double)))
+    return fail(c, EDG_ENOMEM, "the samples' size exceeds the address range");
   const size_t rsz = c->cfg.fp64 ? sizeof(double) : sizeof(float);
-  c->run_recd = (size_t)std::max(nslots, 1) * c->O * LPE * c->B;
-  if ((rc = dev_alloc(c, c->RecD, (size_t)c->runs * c->run_recd * rsz))) return rc;
-  if ((rc = dev_upload(c, c->r_elem, el.data(), n * sizeof(int)))) return rc;
-  if ((rc = dev_upload(c, c->r_slot, slot.data(), n * sizeof(int)))) return rc;
-  if ((rc = dev_upload(c, c->r_chain, chain.data(), n * sizeof(int)))) return rc;
-  if ((rc = dev_upload(c, c->r_phi, phi.data(), phi.size() * sizeof(double)))) return rc;
-  if ((rc = dev_alloc(c, c->r_out, (size_t)c->runs * std::max<int64_t>(n, 1) * ns * LPE * sizeof(double))))
-    return rc;
-  HIPCHK(c, hipMemset(c->r_out.p, 0, c->r_out.bytes));
+  auto put_slots = [&]() {
+    for (int64_t ki = 0; ki < c->Kp; ++ki) c->FI_host[(size_t)ki * FI_WORDS + 15] = rs_slot[ki];
+    return dev_put(c, c->FI, c->FI_host.data(), c->FI_host.size() * sizeof(int));
+  };
+  auto put_all = [&]() {
+    int rc;
+    c->run_recd = (size_t)std::max(nslots, 1) * c->O * LPE * c->B;
+    if ((rc = dev_alloc(c, c->RecD, (size_t)c->runs * c->run_recd * rsz))) return rc;
+    if ((rc = dev_upload(c, c->r_elem, el.data(), n * sizeof(int)))) return rc;
+    if ((rc = dev_upload(c, c->r_slot, slot.data(), n * sizeof(int)))) return rc;
+    if ((rc = dev_upload(c, c->r_chain, chain.data(), n * sizeof(int)))) return rc;
+    if ((rc = dev_upload(c, c->r_phi, phi.data(), phi.size() * sizeof(double)))) return rc;
+    if ((rc = dev_alloc(c, c->r_out, (size_t)c->runs * std::max<int64_t>(n, 1) * ns * LPE * sizeof(double))))
+      return rc;
+    HIPCHK(c, hipMemset(c->r_out.p, 0, c->r_out.bytes));
+    return put_slots();
+  };
   drop_graph(c);
+  c->n_rec = 0;
+  if (const int rc = put_all()) {   // no receivers then: no launch may use the buffers that are there no more
+    const std::string err = c->err;
+    std::fill(rs_slot.begin(), rs_slot.end(), -1);
+    (void)put_slots();
+    c->err = err;
+    return rc;
+  }
   c->n_rec = (int)n;
   c->rec_ns = ns;
   c->rec_dt = dt_sample;
