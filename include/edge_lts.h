@@ -309,8 +309,8 @@ int edg_rewind(edg_ctx* ctx);
  * during the call; the DOFs and the time are those of before the call when it
  * returns.  EDG_ESTATE without checkpoints.  on_device = 1:
  * all six arrays are device pointers; dj_dseis is copied and the gradients
- * are scattered to caller order on the device, while dj_dq and g_q0 (DOF
- * layout conversions done by the host) are staged through host memory. */
+ * are scattered to caller order on the device, and so are dj_dq and g_q0 between
+ * the caller's layout and the library's.  A repeated sweep gives the same bits. */
 int edg_adjoint(edg_ctx* ctx, const double* dj_dseis, const double* dj_dq, double* g_q0, double* g_rho,
                 double* g_vp, double* g_vs, int32_t on_device);
 

@@ -71,7 +71,10 @@
 // 12k tets 7,220 -> 718 (3.8 KB of spills a lane before).  Combining the rows
 // of the transposed products with G' before the exchange and forming the lane's
 // parameters twice (37k tets): O = 5 m=3 820 -> 761, O = 4 m=3 555 -> 458, m=0
-// 330 -> 306, O = 3 m=3 276 -> 245; FP64 O = 5 m=3 10k 624 -> 590.
+// 330 -> 306, O = 3 m=3 276 -> 245; FP64 O = 5 m=3 10k 624 -> 590.  With dJ/drho
+// free of cancelling parts, sums in a fixed order and, up to O = 3, in FP64 (97k
+// tets): O = 5 m=3 2,076 -> 2,124, O = 4 m=3 1,247 -> 1,291, m=0 832 -> 854, O = 3
+// m=3 671 -> 695; FP64 O = 5 m=3 12k 657 -> 659.
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
@@ -373,10 +376,10 @@ __device__ __forceinline__ int aslot(int row, int dir) {
 }
 
 // Waves per SIMD the registers are budgeted for (us per reverse cycle of two
-// clusters).  FP32: three; 144-166 registers without a spill but at O = 5 m=3,
+// clusters).  FP32: three; 144-156 registers without a spill but at O = 5 m=3,
 // where 112 B a lane spill and still pay (37k tets 761 against 800 at two, 4.6k
 // tets 147 against 160); four at O = 4 m=0 spill 116 B: 305 -> 363.  FP64: one
-// (up to 512 registers), two at O = 4, whose 57 KB of LDS leave room for a second
+// (up to 512 registers), two at O = 4, whose 60 KB of LDS leave room for a second
 // workgroup (10k tets m=0 249 -> 184, m=3 363 -> 314, at 576 tets 80 -> 83; at
 // O = 3, 140 B of spills, 161 -> 189; at O = 5 the LDS holds one workgroup).
 template <class R, int O, int M>

@@ -139,7 +139,7 @@ __device__ __forceinline__ void wave_lds_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// Steps of cluster cl at the processed level (see LevelArgs::clock), dl levels on.
+// Steps of cluster cl at the processed level (see LevelArgs::clock).
 __device__ __forceinline__ int step_new_of(const LevelArgs& a, int cl) {
   return (int)((*a.clock + a.level) >> cl);
 }

@@ -50,7 +50,7 @@ namespace {
 // The element update: a workgroup of W waves owns 7 elements.  Lane (e, q) of
 // wave w keeps row q of element e for the modes [mb(w), mb(w + 1)) only
 // (elementwise state is split W ways: no register spill, several workgroups
-// per SIMD); the reference-matrix products that need a whole row read it from
+// per CU); the reference-matrix products that need a whole row read it from
 // the LDS row exchange RX, and their outputs are split between the waves
 // (stiffness and trace outputs balanced by non-zero count, the wave's own
 // modes for the lift).  The gradient exchange holds only the 18 (row,
@@ -977,8 +977,14 @@ int launch_zero_words(void* p, size_t words, hipStream_t st) {
 //   O >= 4  four: FP32 O=5 m=3 2k / 41k / 300k tets 112 / 541 / 2,881 against
 //           144 / 613 / 3,038 with two, m=0 300k 1,931 against 2,216; O=4 m=3
 //           84 / 341 / 1,810 against 100 / 404 / 1,966, 16 runs of 18k 1,879
-//           against 2,037.  FP64 m=3 41k O=5 1,776 against 1,733 (one wave,
-//           spilling 2.4 KB a lane: 9,475), O=4 720 against 1,078 (2,315)
+//           against 2,037.  FP64 O=4 m=3 41k 720 against 1,078 (one wave:
+//           2,315).  FP64 O=5 m=0 1k / 11k / 101k 100 / 285 / 1,771 against 137 /
+//           393 / 2,391; m=3 1k / 5k / 11k 126 / 225 / 525 against 189 / 270 /
+//           565, but 41k / 101k 1,631 / 3,955 against 1,488 / 3,476: with two
+//           rounds and more of workgroups the latency of one is hidden, and what
+//           every wave repeats counts (one cluster, a longer launch: even at 41k).
+//           FP64 at that order is run for convergence on small meshes, so four
+//           stands for all sizes
 //   O <= 3  two: FP32 m=3 300k O=3 1,062 against 1,313 (one: 3,207), O=2 631
 //           against 891 (one: 1,092); FP64 O=3 m=3 41k 412 against 508 (785)
 // Every split gives the same bits (no contraction across expressions).
